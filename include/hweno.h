@@ -210,9 +210,11 @@ int hweno_run_to_time(hweno_handle* h, int64_t* steps_out);
 /* Waits for the handle's stream and reports a pending device-side error. */
 int hweno_sync(hweno_handle* h);
 
-/* Launch configuration of the stage kernels.  tile_rows: rows one
- * workgroup marches through in 2D (8..1024) or cells per tile in 1D (fixed
- * by the kernel, ignored); grid_blocks: workgroups of the persistent launch
+/* Launch configuration of the stage kernels.  tile_rows: the most rows one
+ * workgroup marches through in 2D (8..1024; with one workgroup per tile a
+ * problem too small to fill the GPU is cut into shorter segments, of equal
+ * heights to within one row), ignored in 1D (cells per tile are fixed
+ * by the kernel); grid_blocks: workgroups of the persistent launch
  * (0 = one per tile); use_graph: capture steps as HIP graphs (1) or launch
  * eagerly (0); variant: register allocation of the 2D Euler stage kernels
  * (0: for the occupancy their face arrays comfortably allow; 1: for one

@@ -102,16 +102,61 @@ struct Layout {
     size_t stage_elems;
 };
 
-static int tiles_2d(int nx, int ny, int rows) {
-    return ((nx + STRIP_OUT - 1) / STRIP_OUT) * ((ny + rows - 1) / rows);
-}
-
 static int validate(const hweno_problem* probs, int32_t nprob, const hweno_config* cfg,
                     hweno_handle* h);
 
 namespace hweno {
 int validate_problems(const hweno_problem* probs, int32_t nprob, const hweno_config* cfg) {
     return validate(probs, nprob, cfg, nullptr);
+}
+
+int tiles_2d(int nx, int ny, int rows) {
+    return ((nx + STRIP_OUT - 1) / STRIP_OUT) * ((ny + rows - 1) / rows);
+}
+
+// A workgroup marches its rows one after the other, so a launch with fewer
+// tiles than the GPU has workgroup slots takes as long as one tile however
+// small the problem is (256^2 Euler, FP64, Q = 3: 40 tiles of 32 rows on 256
+// CUs, 108 us a stage, against 30 us as 430 tiles of 3 rows).  Below two
+// rounds of slots the height is the one that minimises
+//     (rows + 3) * (full rounds * c(slots per CU) + c(workgroups left per CU)),
+// rows + 3: marched rows of a tile (two of them halo) and its set-up; c(n):
+// time of one row with n workgroups on a CU relative to one alone.  Measured
+// c(n) = 1 + 0.43 (n - 1) for the four-wave Euler workgroups (a row alone /
+// two to a CU: 2.9 / 4.3 us in FP64 Q = 3, 1.5 / 2.1 us in F32_ACC64 Q = 2)
+// and about 1 + 0.15 (n - 1) for the one-wave scalar ones.  From two rounds on
+// the dispatcher's own balance makes taller segments better (fewer halo rows).
+int split_rows(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg, int cap) {
+    constexpr int64_t NCU = 256;
+    const bool euler = probs[0].flux == HWENO_EULER, f64 = cfg.precision == HWENO_F64;
+    // workgroups that fit a CU (registers and LDS of the kernels)
+    const int slots = !euler ? 12
+                             : cfg.characteristic ? (f64 ? 1 : 2)
+                                                  : (f64 ? 3 : 4) - (cfg.gauss_q == 3 ? 1 : 0);
+    const double g = euler ? 0.43 : 0.15;
+    auto tiles = [&](int rows) {
+        int64_t n = 0;
+        for (int p = 0; p < nprob; ++p) n += tiles_2d(probs[p].nx, probs[p].ny, rows);
+        return n;
+    };
+    if (tiles(cap) >= 2 * NCU * slots) return cap;
+    const int64_t most = std::max(tiles(8), SPLIT_TILES);
+    auto c = [&](int64_t n) { return n > 0 ? 1.0 + g * (double)(n - 1) : 0.0; };
+    auto cost = [&](int rows) {
+        const int64_t n = (tiles(rows) + NCU - 1) / NCU;   // workgroups per CU
+        return (rows + 3) * ((double)(n / slots) * c(slots) + c(n % slots));
+    };
+    int best = cap;
+    double low = cost(cap);
+    for (int rows = std::min(cap, 64); rows >= 2; --rows) {
+        if (tiles(rows) > most) break;
+        const double t = cost(rows);
+        if (t < low) {
+            low = t;
+            best = rows;
+        }
+    }
+    return best;
 }
 
 int thread_error(int code, const char* fmt, ...) {
@@ -231,13 +276,18 @@ static Layout layout_of(const hweno_problem* probs, int32_t nprob, const hweno_c
         nd += (size_t)K * D * nc;
         maxst = std::max(maxst, (size_t)nvar * K * nc);
         if (D == 1) tiles += (probs[p].nx + TILE1D_OUT - 1) / TILE1D_OUT;
-        else tiles += tiles_2d(probs[p].nx, probs[p].ny, 8);  // smallest segment height
+        else tiles += tiles_2d(probs[p].nx, probs[p].ny, 8);  // smallest height a caller can ask for
         nch += (int)((nc + CHUNK_CELLS - 1) / CHUNK_CELLS);
     }
     L.u_bytes = align256(nu * su);
     L.d_bytes = align256(nd * sd);
     L.probs = align256(sizeof(ProbDev) * nprob);
     L.ctl = align256(sizeof(StepCtl));
+    if (D == 2) {   // shorter segments of small problems (split_rows)
+        int64_t two = 0;
+        for (int p = 0; p < nprob; ++p) two += tiles_2d(probs[p].nx, probs[p].ny, 2);
+        tiles = std::max(tiles, (size_t)std::min(two, SPLIT_TILES));
+    }
     L.tiles_cap = 2 * tiles;
     L.tiles = align256(L.tiles_cap * (D == 1 ? sizeof(Tile1D) : sizeof(Tile2D)));
     L.nchunks = nch;
@@ -256,7 +306,6 @@ static Layout layout_of(const hweno_problem* probs, int32_t nprob, const hweno_c
 // region: list position 8k + x holds the k-th tile of region x, and the
 // dispatcher hands workgroup b to XCD b mod 8), then the per-problem list.
 static int build_tiles(hweno_handle* h) {
-    const int rows = h->tun.tile_rows;
     std::vector<int> begin(h->nprob), count(h->nprob);
     if (h->dim == 1) {
         std::vector<Tile1D> per;
@@ -274,13 +323,19 @@ static int build_tiles(hweno_handle* h) {
         h->ntiles_step = (int)n;
         for (int& b : begin) b += (int)n;
     } else {
+        // a persistent grid is the caller's own balance: heights as given
+        const int rows = h->tun.grid_blocks > 0
+                             ? h->tun.tile_rows
+                             : split_rows(h->probs.data(), h->nprob, h->cfg, h->tun.tile_rows);
         std::vector<Tile2D> per;
         for (int p = 0; p < h->nprob; ++p) {
             begin[p] = (int)per.size();
             const int nx = h->probs[p].nx, ny = h->probs[p].ny;
-            for (int j0 = 0; j0 < ny; j0 += rows)
-                for (int i0 = 0; i0 < nx; i0 += STRIP_OUT)
-                    per.push_back({p, i0, j0, std::min(rows, ny - j0)});
+            const int nseg = (ny + rows - 1) / rows;
+            for (int s = 0; s < nseg; ++s) {
+                const int j0 = segment_row(s, nseg, ny), j1 = segment_row(s + 1, nseg, ny);
+                for (int i0 = 0; i0 < nx; i0 += STRIP_OUT) per.push_back({p, i0, j0, j1 - j0});
+            }
             count[p] = (int)per.size() - begin[p];
         }
         const size_t n = per.size();

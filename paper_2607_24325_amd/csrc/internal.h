@@ -146,6 +146,16 @@ int validate_problems(const hweno_problem* probs, int32_t nprob, const hweno_con
 // Sets the thread's last error (hweno_last_error(NULL)); returns code.
 int thread_error(int code, const char* fmt, ...);
 Scheme scheme_of(const hweno_problem& p0, const hweno_config& cfg);
+// Segment height of the 2D tiles of one launch over these problems: at most
+// `cap` rows, fewer where that would leave the GPU idle.
+int split_rows(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg, int cap);
+// Tiles of one problem at that height, and the first row of segment s.
+int tiles_2d(int nx, int ny, int rows);
+__host__ __device__ inline int segment_row(int s, int nseg, int ny) {
+    return (int)((int64_t)s * ny / nseg);
+}
+// Tile lists are sized for max(tiles at 8 rows, min(tiles at 2 rows, this)).
+constexpr int64_t SPLIT_TILES = 4096;
 // Per-problem table entry (static fields; time 0, speeds unknown).
 ProbDev probdev_of(const hweno_problem& pr, const hweno_config& cfg, int64_t off_u,
                    int64_t off_d);

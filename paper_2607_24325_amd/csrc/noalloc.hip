@@ -21,7 +21,7 @@ static __device__ __align__(256) unsigned char scratch[HWENO_NOALLOC_SCRATCH_BYT
 // chunks of one problem into the scratch (per-problem order; results do not
 // depend on the order of the tiles).
 __global__ void noalloc_setup_kernel(ProbDev pd, StepCtl ctl, ProbDev* probs, StepCtl* dctl,
-                                     int dim, int rows, void* tiles, int ntiles, Chunk* chunks,
+                                     int dim, int nseg, void* tiles, int ntiles, Chunk* chunks,
                                      int nchunks) {
     const int tid = blockIdx.x * blockDim.x + threadIdx.x;
     const int nth = gridDim.x * blockDim.x;
@@ -35,8 +35,8 @@ __global__ void noalloc_setup_kernel(ProbDev pd, StepCtl ctl, ProbDev* probs, St
             ((Tile1D*)tiles)[t] = Tile1D{0, t * TILE1D_OUT};
         } else {
             const int js = t / strips, is = t - js * strips;
-            const int j0 = js * rows;
-            ((Tile2D*)tiles)[t] = Tile2D{0, is * STRIP_OUT, j0, min(rows, pd.ny - j0)};
+            const int j0 = segment_row(js, nseg, pd.ny), j1 = segment_row(js + 1, nseg, pd.ny);
+            ((Tile2D*)tiles)[t] = Tile2D{0, is * STRIP_OUT, j0, j1 - j0};
         }
     }
     const int64_t nc = (int64_t)pd.nx * pd.ny;
@@ -105,15 +105,19 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
     const int D = dim, nvar = 1 + D;
     const size_t su = prec == HWENO_F32 ? 4 : 8, sd = prec == HWENO_F64 ? 8 : 4;
     const int64_t ncell = (int64_t)pr.nx * pr.ny;
-    const int rows = 32;
-    const int ntiles = dim == 1 ? (pr.nx + TILE1D_OUT - 1) / TILE1D_OUT
-                                : ((pr.nx + STRIP_OUT - 1) / STRIP_OUT) * ((pr.ny + rows - 1) / rows);
     const int nchunks = (int)((ncell + CHUNK_CELLS - 1) / CHUNK_CELLS);
     // regions: three state sets, the saved hats, table, control, tiles, chunks
     const size_t ub = up256((size_t)ncell * K * su), db = up256((size_t)ncell * K * D * sd);
-    const size_t tb = up256((size_t)ntiles * (dim == 1 ? sizeof(Tile1D) : sizeof(Tile2D)));
     const size_t cb = up256((size_t)nchunks * sizeof(Chunk));
-    const size_t need = 3 * (ub + db) + db + up256(sizeof(ProbDev)) + up256(sizeof(StepCtl)) + tb + cb;
+    // segments as hweno_step cuts them; 32 rows where only their shorter list fits
+    int rows = dim == 2 ? split_rows(prob, 1, *cfg, 32) : 0, ntiles = 0;
+    size_t tb = 0, need = 0;
+    for (;; rows = 32) {
+        ntiles = dim == 1 ? (pr.nx + TILE1D_OUT - 1) / TILE1D_OUT : tiles_2d(pr.nx, pr.ny, rows);
+        tb = up256((size_t)ntiles * (dim == 1 ? sizeof(Tile1D) : sizeof(Tile2D)));
+        need = 3 * (ub + db) + db + up256(sizeof(ProbDev)) + up256(sizeof(StepCtl)) + tb + cb;
+        if (need <= HWENO_NOALLOC_SCRATCH_BYTES || dim == 1 || rows == 32) break;
+    }
     if (need > HWENO_NOALLOC_SCRATCH_BYTES)
         return thread_error(HWENO_ERR_ARG,
                             "problem of %lld cells needs %zu bytes of scratch; the allocation-free "
@@ -147,7 +151,8 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
     const int use_dt_in = dt_in > 0.0;
     const Scheme sch = scheme_of(pr, *cfg);
     const int sgrid = std::max(1, std::min(1024, (std::max(ntiles, nchunks) + 255) / 256));
-    noalloc_setup_kernel<<<sgrid, 256, 0, s>>>(pd, sc, probs, ctl, dim, rows, tiles, ntiles,
+    const int nseg = dim == 2 ? (pr.ny + rows - 1) / rows : 0;
+    noalloc_setup_kernel<<<sgrid, 256, 0, s>>>(pd, sc, probs, ctl, dim, nseg, tiles, ntiles,
                                                chunks, nchunks);
     NA_TRY(hipGetLastError());
     NA_TRY(launch_pack(prec, 1, const_cast<double*>(state_in), U[0], 0, 0, K, nvar, ncell, s));
