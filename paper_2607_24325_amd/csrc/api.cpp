@@ -39,6 +39,7 @@ struct hweno_handle {
     void* d_tiles = nullptr;        // step list followed by the per-problem list
     size_t tiles_cap = 0;           // capacity in tiles
     int ntiles_step = 0;
+    int cells1d = 0;                // 1D: cells per lane of the step kernel; 0: stage by stage
     std::vector<int> tile_begin, tile_count;  // per problem, in the per-problem list
     Chunk* d_chunks = nullptr;
     int nchunks = 0;
@@ -268,14 +269,18 @@ static Layout layout_of(const hweno_problem* probs, int32_t nprob, const hweno_c
     const int nvar = 1 + D;
     size_t su, sd;
     prec_sizes(cfg->precision, &su, &sd);
-    size_t nu = 0, nd = 0, maxst = 0, tiles = 0;
+    size_t nu = 0, nd = 0, maxst = 0, tiles = 0, steps1d = 0;
     int nch = 0;
+    const int cells1d = D == 1 ? step1d_cells(probs, nprob, *cfg) : 0;
     for (int p = 0; p < nprob; ++p) {
         const size_t nc = (size_t)probs[p].nx * probs[p].ny;
         nu += (size_t)K * nc;
         nd += (size_t)K * D * nc;
         maxst = std::max(maxst, (size_t)nvar * K * nc);
-        if (D == 1) tiles += (probs[p].nx + TILE1D_OUT - 1) / TILE1D_OUT;
+        if (D == 1) {
+            tiles += (probs[p].nx + TILE1D_OUT - 1) / TILE1D_OUT;
+            steps1d += tiles_1d(probs[p].nx, cells1d);
+        }
         else tiles += tiles_2d(probs[p].nx, probs[p].ny, 8);  // smallest height a caller can ask for
         nch += (int)((nc + CHUNK_CELLS - 1) / CHUNK_CELLS);
     }
@@ -288,7 +293,7 @@ static Layout layout_of(const hweno_problem* probs, int32_t nprob, const hweno_c
         for (int p = 0; p < nprob; ++p) two += tiles_2d(probs[p].nx, probs[p].ny, 2);
         tiles = std::max(tiles, (size_t)std::min(two, SPLIT_TILES));
     }
-    L.tiles_cap = 2 * tiles;
+    L.tiles_cap = tiles + std::max(tiles, steps1d);
     L.tiles = align256(L.tiles_cap * (D == 1 ? sizeof(Tile1D) : sizeof(Tile2D)));
     L.nchunks = nch;
     L.chunks = align256(sizeof(Chunk) * nch);
@@ -308,17 +313,19 @@ static Layout layout_of(const hweno_problem* probs, int32_t nprob, const hweno_c
 static int build_tiles(hweno_handle* h) {
     std::vector<int> begin(h->nprob), count(h->nprob);
     if (h->dim == 1) {
-        std::vector<Tile1D> per;
+        std::vector<Tile1D> step, per;
         for (int p = 0; p < h->nprob; ++p) {
+            const int nx = h->probs[p].nx;
+            const int out = h->cells1d ? 64 * h->cells1d - STEP1D_HALO : TILE1D_OUT;
+            for (int c0 = 0; c0 < nx; c0 += out) step.push_back({p, c0});
             begin[p] = (int)per.size();
-            for (int c0 = 0; c0 < h->probs[p].nx; c0 += TILE1D_OUT) per.push_back({p, c0});
+            for (int c0 = 0; c0 < nx; c0 += TILE1D_OUT) per.push_back({p, c0});
             count[p] = (int)per.size() - begin[p];
         }
-        const size_t n = per.size();
-        if (2 * n > h->tiles_cap) return fail(h, HWENO_ERR_OOM, "tile list exceeds its buffer");
-        std::vector<Tile1D> all(per);
-        all.insert(all.end(), per.begin(), per.end());
-        HIP_TRY(h, hipMemcpy(h->d_tiles, all.data(), all.size() * sizeof(Tile1D),
+        const size_t n = step.size();
+        if (n + per.size() > h->tiles_cap) return fail(h, HWENO_ERR_OOM, "tile list exceeds its buffer");
+        step.insert(step.end(), per.begin(), per.end());
+        HIP_TRY(h, hipMemcpy(h->d_tiles, step.data(), step.size() * sizeof(Tile1D),
                              hipMemcpyHostToDevice));
         h->ntiles_step = (int)n;
         for (int& b : begin) b += (int)n;
@@ -472,6 +479,8 @@ static int setup(hweno_handle* h, const hweno_problem* probs, int32_t nprob,
     h->tun.use_graph = 1;
     h->tun.variant = 0;
     h->tun.source = HWENO_TUNED_DEFAULT;
+    // speeds of every stage need a reduction between the stages
+    if (h->dim == 1 && !cfg->alpha_stage) h->cells1d = step1d_cells(probs, nprob, *cfg);
     return build_tiles(h);
 }
 
@@ -548,13 +557,14 @@ extern "C" int hweno_set_state(hweno_handle* h, int32_t prob, const double* src,
     HIP_TRY(h, hipMemcpyAsync(h->d_stage, src, sizeof(double) * n,
                               src_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
                               h->stream));
-    HIP_TRY(h, launch_pack(h->prec, 1, h->d_stage, h->U[0], h->h_probs[prob].off_u,
+    HIP_TRY(h, launch_pack(h->prec, 1, h->d_stage, h->U[0], h->U[1], h->d_probs + prob, h->h_probs[prob].off_u,
                            h->h_probs[prob].off_d, h->K, h->nvar, h->ncell[prob], h->stream));
     ProbDev d;
     HIP_TRY(h, hipMemcpyAsync(&d, h->d_probs + prob, sizeof d, hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
     d.t = t;
     d.err = 0;
+    d.err_next = 0;
     d.bad_cell = INT64_MAX;
     d.active = 0;
     d.alpha_valid = 0;
@@ -576,7 +586,7 @@ extern "C" int hweno_get_state(hweno_handle* h, int32_t prob, double* dst,
                               h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
     if (dst) {
-        HIP_TRY(h, launch_pack(h->prec, 0, h->d_stage, h->U[0], h->h_probs[prob].off_u,
+        HIP_TRY(h, launch_pack(h->prec, 0, h->d_stage, h->U[0], h->U[1], h->d_probs + prob, h->h_probs[prob].off_u,
                                h->h_probs[prob].off_d, h->K, h->nvar, h->ncell[prob], h->stream));
         HIP_TRY(h, hipMemcpyAsync(dst, h->d_stage, sizeof(double) * n,
                                   dst_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
@@ -601,6 +611,7 @@ static StageArgs stage_args(hweno_handle* h, int mode) {
     StageArgs a{};
     const int k = mode == MODE_RHS ? 0 : mode - 1;  // input set of the stage
     a.in = h->U[k];
+    a.in1 = h->U[mode == MODE_RHS ? 1 : k];
     a.out = h->U[mode == MODE_S3 ? 0 : (k + 1) % 3];
     a.un = h->U[0].u;
     a.h = h->H;
@@ -620,7 +631,7 @@ static hipError_t launch_stage(hweno_handle* h, int mode, const StageArgs& a) {
 
 static int alpha_all(hweno_handle* h) {
     HIP_TRY(h, launch_reset(h->d_probs, h->d_ctl, h->nprob, SEL_ALL, h->stream));
-    HIP_TRY(h, launch_alpha(h->prec, h->flux, h->dim, h->U[0].u, h->d_probs, h->d_chunks,
+    HIP_TRY(h, launch_alpha(h->prec, h->flux, h->dim, h->U[0].u, h->U[1].u, h->d_probs, h->d_chunks,
                             h->nchunks, h->sch, SEL_ALL, 0, h->stream));
     return HWENO_OK;
 }
@@ -675,23 +686,43 @@ extern "C" int hweno_rhs(hweno_handle* h, int32_t prob, double* L_out, double* U
 // fused stage kernels, time update.
 // The launches of one step, in order; rec(kind, launch) issues each one
 // (and may bracket it with events).
-enum LaunchKind { LK_OTHER = 0, LK_ALPHA = 1, LK_STAGE = 2 };
+enum LaunchKind { LK_OTHER = 0, LK_ALPHA = 1, LK_STAGE = 2, LK_STEP = 3 };  // LK_STEP: three stages
 
 // One step.  fast: no problem that can advance has stale speeds, so the
 // reduction kernel is left out (and with at most 256 problems the dt kernel
 // clears the step counters itself, which leaves out the reset kernel too).
 template <class Rec>
 static int enqueue_step_with(hweno_handle* h, int use_dt_in, bool fast, Rec&& rec) {
-    const int own_ctl = fast && h->nprob <= 256;
+    const int own_ctl = fast && (h->cells1d || h->nprob <= 256);
     // speeds are gathered by stage 3 of the previous step; the reduction
     // kernel only fills them in after set_state
     if (!own_ctl)
         HIP_TRY(h, rec(LK_OTHER, [&] { return launch_reset(h->d_probs, h->d_ctl, h->nprob, SEL_STALE, h->stream); }));
     if (!fast)
         HIP_TRY(h, rec(LK_ALPHA, [&] {
-            return launch_alpha(h->prec, h->flux, h->dim, h->U[0].u, h->d_probs, h->d_chunks,
+            return launch_alpha(h->prec, h->flux, h->dim, h->U[0].u, h->U[1].u, h->d_probs, h->d_chunks,
                                 h->nchunks, h->sch, SEL_STALE, 0, h->stream);
         }));
+    if (h->cells1d) {
+        // one kernel takes the whole step; its last wave ends it where few
+        // tiles (arrivals at one counter) and few problems are to be ended
+        Step1Args a{};
+        a.s[0] = h->U[0];
+        a.s[1] = h->U[1];
+        a.probs = h->d_probs;
+        a.ctl = h->d_ctl;
+        a.tiles = (const Tile1D*)h->d_tiles;
+        a.ntiles = h->ntiles_step;
+        a.finish = ends_own_step(h->ntiles_step, h->nprob);
+        a.rule = StepRule{h->cfg.cfl, 1, use_dt_in, 1, 1};
+        a.sch = h->sch;
+        HIP_TRY(h, rec(LK_STEP, [&] {
+            return launch_step1d(h->prec, h->flux, h->cells1d, a, h->tun.grid_blocks, h->stream);
+        }));
+        if (!a.finish)
+            HIP_TRY(h, rec(LK_OTHER, [&] { return launch_finish(h->d_probs, h->d_ctl, h->nprob, a.rule, h->stream); }));
+        return HWENO_OK;
+    }
     HIP_TRY(h, rec(LK_OTHER, [&] { return launch_dt(h->d_probs, h->d_ctl, h->nprob, use_dt_in, own_ctl, h->stream); }));
     for (int mode = MODE_S1; mode <= MODE_S3; ++mode) {
         if (mode != MODE_S1 && h->cfg.alpha_stage) {
@@ -699,13 +730,13 @@ static int enqueue_step_with(hweno_handle* h, int use_dt_in, bool fast, Rec&& re
             const void* uin = h->U[mode - 1].u;
             HIP_TRY(h, rec(LK_OTHER, [&] { return launch_reset(h->d_probs, h->d_ctl, h->nprob, SEL_ACTIVE, h->stream); }));
             HIP_TRY(h, rec(LK_ALPHA, [&] {
-                return launch_alpha(h->prec, h->flux, h->dim, uin, h->d_probs, h->d_chunks,
+                return launch_alpha(h->prec, h->flux, h->dim, uin, uin, h->d_probs, h->d_chunks,
                                     h->nchunks, h->sch, SEL_ACTIVE, 0, h->stream);
             }));
         }
         HIP_TRY(h, rec(LK_STAGE, [&] { return launch_stage(h, mode, stage_args(h, mode)); }));
     }
-    HIP_TRY(h, rec(LK_OTHER, [&] { return launch_finish(h->d_probs, h->d_ctl, h->nprob, h->stream); }));
+    HIP_TRY(h, rec(LK_OTHER, [&] { return launch_finish(h->d_probs, h->d_ctl, h->nprob, StepRule{h->cfg.cfl, h->dim, use_dt_in, 0, 0}, h->stream); }));
     return HWENO_OK;
 }
 
@@ -1021,10 +1052,11 @@ extern "C" int hweno_autotune(hweno_handle* h, hweno_tuning* best) {
     const int saved_fresh = h->speeds_fresh;
     const size_t ub = (size_t)((char*)h->U[0].d - (char*)h->U[0].u);
     const size_t db = (size_t)((char*)h->U[1].u - (char*)h->U[0].d);
+    const size_t sb = h->cells1d ? 2 * (ub + db) : ub + db;   // the sets that can hold a state
     void* save = nullptr;
-    HIP_TRY(h, hipMalloc(&save, ub + db));
+    HIP_TRY(h, hipMalloc(&save, sb));
     auto restore = [&]() -> int {
-        HIP_TRY(h, hipMemcpyAsync(h->U[0].u, save, ub + db, hipMemcpyDeviceToDevice, h->stream));
+        HIP_TRY(h, hipMemcpyAsync(h->U[0].u, save, sb, hipMemcpyDeviceToDevice, h->stream));
         HIP_TRY(h, hipMemcpyAsync(h->d_probs, saved_probs.data(), sizeof(ProbDev) * h->nprob,
                                   hipMemcpyHostToDevice, h->stream));
         HIP_TRY(h, hipMemcpyAsync(h->d_ctl, &saved_ctl, sizeof saved_ctl, hipMemcpyHostToDevice,
@@ -1033,7 +1065,7 @@ extern "C" int hweno_autotune(hweno_handle* h, hweno_tuning* best) {
         h->speeds_fresh = saved_fresh;   // the restored table may hold stale speeds
         return HWENO_OK;
     };
-    HIP_TRY(h, hipMemcpyAsync(save, h->U[0].u, ub + db, hipMemcpyDeviceToDevice, h->stream));
+    HIP_TRY(h, hipMemcpyAsync(save, h->U[0].u, sb, hipMemcpyDeviceToDevice, h->stream));
     const std::vector<hweno_tuning> cands = tuning_candidates(h);
     const hweno_tuning keep = h->tun;
     hipEvent_t e0, e1;
@@ -1166,9 +1198,9 @@ extern "C" int hweno_timed_steps(hweno_handle* h, int32_t nsteps, hweno_timing* 
         out->total_ms = ms;
         for (size_t i = 0; i < kinds.size(); ++i) {
             HIP_TRY(h, hipEventElapsedTime(&ms, ev[1 + 2 * i], ev[2 + 2 * i]));
-            if (kinds[i] == LK_STAGE) {
+            if (kinds[i] == LK_STAGE || kinds[i] == LK_STEP) {
                 out->stage_ms += ms;
-                out->stage_launches += 1;
+                out->stage_launches += kinds[i] == LK_STEP ? 3 : 1;
             } else if (kinds[i] == LK_ALPHA) {
                 out->alpha_ms += ms;
             } else {

@@ -28,21 +28,20 @@ __global__ void reset_kernel(ProbDev* probs, StepCtl* ctl, int nprob, int sel) {
 // problem (Euler: |velocity| + sound speed), in double precision; cells that
 // are not finite or have rho <= 0 / p <= 0 flag the problem.
 template <int P, int FLUX, int DIM>
-__global__ void __launch_bounds__(256) alpha_kernel(const void* uptr, ProbDev* probs,
+__global__ void __launch_bounds__(256) alpha_kernel(const void* u0, const void* u1, ProbDev* probs,
                                                     const Chunk* chunks, int nchunks,
                                                     Scheme sch, int sel) {
     using TU = typename PrecT<P>::TU;
     constexpr int K = FLUX == F_EULER ? (DIM == 1 ? 3 : 4) : 1;
     __shared__ double smx[4], smy[4];
     __shared__ long long sbad[4];
-    const TU* U = (const TU*)uptr;
     for (int ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
         const Chunk chunk = chunks[ch];
         ProbDev& P_ = probs[chunk.prob];
         if (sel == SEL_STALE && (!(P_.t < P_.t_end) || P_.err || P_.alpha_valid)) continue;
         if (sel == SEL_ACTIVE && (!P_.active || (P_.err & ERR_STAGE_BAD))) continue;
         const int64_t plane = (int64_t)P_.nx * P_.ny;
-        const TU* base = U + P_.off_u;
+        const TU* base = (const TU*)(P_.cur ? u1 : u0) + P_.off_u;
         double mx = 0.0, my = 0.0;
         long long bad = LLONG_MAX;
         // every load of the thread's cells first (lanes past the chunk read
@@ -107,28 +106,14 @@ __global__ void __launch_bounds__(256) alpha_kernel(const void* uptr, ProbDev* p
     }
 }
 
-// dt = min(CFL rule, t_end - t); the CFL rule is cfl*dx^e/alpha_x in 1D and
-// cfl/(alpha_x/dx^e + alpha_y/dy^e) in 2D (or the caller's step).  Returns
+// Chooses a problem's step for kernels that read it from the table; returns
 // whether the problem takes this step.
 __device__ __forceinline__ int select_dt(ProbDev& P_, const StepCtl* ctl, int use_dt_in) {
-    P_.active = 0;
-    P_.last = 0;
-    P_.dt = 0.0;
-    if (!(P_.t < P_.t_end) || P_.err) return 0;
-    double dtc;
-    if (use_dt_in) {
-        dtc = P_.dt_in;
-        if (!(dtc > 0.0)) return 0;
-    } else {
-        const double ax = as_double(P_.ax_bits), ay = as_double(P_.ay_bits);
-        dtc = ctl->dim == 1 ? ctl->cfl * P_.dxe / ax : ctl->cfl / (ax / P_.dxe + ay / P_.dye);
-    }
-    const double rem = P_.t_end - P_.t;
-    const int last = !(dtc < rem);
-    P_.dt = last ? rem : dtc;
-    P_.last = last;
-    P_.active = 1;
-    return 1;
+    const StepChoice c = choose_step(P_, StepRule{ctl->cfl, ctl->dim, use_dt_in, 1, 0});
+    P_.active = c.act;
+    P_.last = c.last;
+    P_.dt = c.dt;
+    return c.act;
 }
 
 // own_ctl: the launch is one block that holds every problem and sets the
@@ -148,31 +133,49 @@ __global__ void dt_kernel(ProbDev* probs, StepCtl* ctl, int nprob, int use_dt_in
     }
 }
 
-// t += dt (exactly t_end on the clipped last step); counts problems still
-// running and the steps in which anything advanced.
-// The speeds stage 3 gathered from the new state become current.
-__global__ void finish_kernel(ProbDev* probs, StepCtl* ctl, int nprob) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < nprob) {
-        ProbDev& P_ = probs[p];
-        // a problem whose intermediate stage was not admissible skipped its
-        // stages 2 and 3: its state and time stay those of U^n
-        if (P_.active && !(P_.err & ERR_STAGE_BAD)) {
-            P_.t = P_.last ? P_.t_end : P_.t + P_.dt;
-            P_.ax_bits = P_.ax_next;
-            P_.ay_bits = P_.ay_next;
-            P_.alpha_valid = 1;
-        }
-        P_.ax_next = 0;
-        P_.ay_next = 0;
-        if (P_.t < P_.t_end && !P_.err) atomicAdd(&ctl->nactive, 1);
+// Ends the step of every problem and counts those still running and the
+// steps in which anything advanced.  A workgroup takes FINISH_PROBS problems,
+// so that batches of up to that many (four rounds of it) are counted by one
+// workgroup; beyond, the last workgroup to get here adds the counts up.
+constexpr int FINISH_PROBS = 4096;
+__global__ void __launch_bounds__(1024) finish_kernel(ProbDev* probs, StepCtl* ctl, int nprob,
+                                                      StepRule rule) {
+    int run = 0, any = 0;
+    const int p0 = blockIdx.x * FINISH_PROBS;
+    for (int p = p0 + threadIdx.x; p < nprob && p < p0 + FINISH_PROBS; p += blockDim.x) {
+        bool running;
+        any |= finish_problem(probs[p], rule, running);
+        run += running;
     }
-    if (p == 0 && ctl->step_active) ctl->steps += 1;
+    __shared__ int srun;
+    if (threadIdx.x == 0) srun = 0;
+    any = __syncthreads_or(any);
+    if (run) atomicAdd(&srun, run);
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    run = srun;
+    if (gridDim.x > 1) {
+        // counts of this and the workgroups before it; the additions of each
+        // have reached memory before it arrives
+        atomicAdd(&ctl->sum_run, run);
+        atomicOr(&ctl->sum_any, any);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (atomicAdd(&ctl->arrived, 1) != (int)gridDim.x - 1) return;
+        run = atomicExch(&ctl->sum_run, 0);
+        any = atomicExch(&ctl->sum_any, 0);
+        ctl->arrived = 0;
+    }
+    ctl->nactive = run;
+    ctl->step_active = any;
+    if (any) ctl->steps += 1;
 }
 
 template <class TU, class TD>
-__global__ void pack_kernel(int to_internal, double* ext, TU* u, TD* d, int K, int nvar,
-                            int64_t ncell) {
+__global__ void pack_kernel(int to_internal, double* ext, TU* u0, TD* d0, TU* u1, TD* d1,
+                            const ProbDev* prob, int K, int nvar, int64_t ncell) {
+    const int cur = prob->cur;
+    TU* u = cur ? u1 : u0;
+    TD* d = cur ? d1 : d0;
     const int64_t n = (int64_t)nvar * K * ncell;
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
          e += (int64_t)gridDim.x * blockDim.x) {
@@ -197,28 +200,28 @@ hipError_t launch_reset(ProbDev* probs, StepCtl* ctl, int nprob, int sel, hipStr
 }
 
 template <int P>
-static hipError_t alpha_dispatch(int flux, int dim, const void* u, ProbDev* probs,
+static hipError_t alpha_dispatch(int flux, int dim, const void* u0, const void* u1, ProbDev* probs,
                                  const Chunk* chunks, int nchunks, const Scheme& sch, int sel,
                                  int grid, hipStream_t s) {
     if (dim == 1) {
-        if (flux == F_ADV) alpha_kernel<P, F_ADV, 1><<<grid, 256, 0, s>>>(u, probs, chunks, nchunks, sch, sel);
-        else if (flux == F_BURGERS) alpha_kernel<P, F_BURGERS, 1><<<grid, 256, 0, s>>>(u, probs, chunks, nchunks, sch, sel);
-        else alpha_kernel<P, F_EULER, 1><<<grid, 256, 0, s>>>(u, probs, chunks, nchunks, sch, sel);
+        if (flux == F_ADV) alpha_kernel<P, F_ADV, 1><<<grid, 256, 0, s>>>(u0, u1, probs, chunks, nchunks, sch, sel);
+        else if (flux == F_BURGERS) alpha_kernel<P, F_BURGERS, 1><<<grid, 256, 0, s>>>(u0, u1, probs, chunks, nchunks, sch, sel);
+        else alpha_kernel<P, F_EULER, 1><<<grid, 256, 0, s>>>(u0, u1, probs, chunks, nchunks, sch, sel);
     } else {
-        if (flux == F_ADV) alpha_kernel<P, F_ADV, 2><<<grid, 256, 0, s>>>(u, probs, chunks, nchunks, sch, sel);
-        else if (flux == F_BURGERS) alpha_kernel<P, F_BURGERS, 2><<<grid, 256, 0, s>>>(u, probs, chunks, nchunks, sch, sel);
-        else alpha_kernel<P, F_EULER, 2><<<grid, 256, 0, s>>>(u, probs, chunks, nchunks, sch, sel);
+        if (flux == F_ADV) alpha_kernel<P, F_ADV, 2><<<grid, 256, 0, s>>>(u0, u1, probs, chunks, nchunks, sch, sel);
+        else if (flux == F_BURGERS) alpha_kernel<P, F_BURGERS, 2><<<grid, 256, 0, s>>>(u0, u1, probs, chunks, nchunks, sch, sel);
+        else alpha_kernel<P, F_EULER, 2><<<grid, 256, 0, s>>>(u0, u1, probs, chunks, nchunks, sch, sel);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_alpha(int prec, int flux, int dim, const void* u, ProbDev* probs,
+hipError_t launch_alpha(int prec, int flux, int dim, const void* u0, const void* u1, ProbDev* probs,
                         const Chunk* chunks, int nchunks, const Scheme& sch, int sel,
                         int grid, hipStream_t s) {
     if (grid <= 0 || grid > nchunks) grid = nchunks;
-    if (prec == P_F32) return alpha_dispatch<P_F32>(flux, dim, u, probs, chunks, nchunks, sch, sel, grid, s);
-    if (prec == P_KAHAN) return alpha_dispatch<P_KAHAN>(flux, dim, u, probs, chunks, nchunks, sch, sel, grid, s);
-    return alpha_dispatch<P_F64>(flux, dim, u, probs, chunks, nchunks, sch, sel, grid, s);
+    if (prec == P_F32) return alpha_dispatch<P_F32>(flux, dim, u0, u1, probs, chunks, nchunks, sch, sel, grid, s);
+    if (prec == P_KAHAN) return alpha_dispatch<P_KAHAN>(flux, dim, u0, u1, probs, chunks, nchunks, sch, sel, grid, s);
+    return alpha_dispatch<P_F64>(flux, dim, u0, u1, probs, chunks, nchunks, sch, sel, grid, s);
 }
 
 hipError_t launch_dt(ProbDev* probs, StepCtl* ctl, int nprob, int use_dt_in, int own_ctl,
@@ -228,28 +231,31 @@ hipError_t launch_dt(ProbDev* probs, StepCtl* ctl, int nprob, int use_dt_in, int
     return hipGetLastError();
 }
 
-hipError_t launch_finish(ProbDev* probs, StepCtl* ctl, int nprob, hipStream_t s) {
-    finish_kernel<<<(nprob + 255) / 256, 256, 0, s>>>(probs, ctl, nprob);
+hipError_t launch_finish(ProbDev* probs, StepCtl* ctl, int nprob, const StepRule& rule,
+                         hipStream_t s) {
+    const int threads = nprob >= 1024 ? 1024 : (nprob + 63) / 64 * 64;
+    finish_kernel<<<(nprob + FINISH_PROBS - 1) / FINISH_PROBS, threads, 0, s>>>(probs, ctl, nprob, rule);
     return hipGetLastError();
 }
 
-hipError_t launch_pack(int prec, int to_internal, double* ext, StateBuf buf, int64_t off_u,
-                       int64_t off_d, int K, int nvar, int64_t ncell, hipStream_t s) {
+template <class TU, class TD>
+static void pack_launch(int to_internal, double* ext, StateBuf b0, StateBuf b1, const ProbDev* prob,
+                        int64_t off_u, int64_t off_d, int K, int nvar, int64_t ncell,
+                        hipStream_t s) {
     const int64_t n = (int64_t)nvar * K * ncell;
     const int grid = (int)((n + 255) / 256 < 65536 ? (n + 255) / 256 : 65536);
-    if (prec == P_F64) {
-        pack_kernel<double, double><<<grid, 256, 0, s>>>(to_internal, ext, (double*)buf.u + off_u,
-                                                         (double*)buf.d + off_d, K, nvar, ncell);
-    } else if (prec == P_F32) {
-        pack_kernel<float, float><<<grid, 256, 0, s>>>(to_internal, ext, (float*)buf.u + off_u,
-                                                       (float*)buf.d + off_d, K, nvar, ncell);
-    } else if (prec == P_ACC64) {
-        pack_kernel<double, float><<<grid, 256, 0, s>>>(to_internal, ext, (double*)buf.u + off_u,
-                                                        (float*)buf.d + off_d, K, nvar, ncell);
-    } else {
-        pack_kernel<ffs, float><<<grid, 256, 0, s>>>(to_internal, ext, (ffs*)buf.u + off_u,
-                                                     (float*)buf.d + off_d, K, nvar, ncell);
-    }
+    pack_kernel<TU, TD><<<grid, 256, 0, s>>>(to_internal, ext, (TU*)b0.u + off_u, (TD*)b0.d + off_d,
+                                             (TU*)b1.u + off_u, (TD*)b1.d + off_d, prob, K, nvar,
+                                             ncell);
+}
+
+hipError_t launch_pack(int prec, int to_internal, double* ext, StateBuf b0, StateBuf b1,
+                       const ProbDev* prob, int64_t off_u, int64_t off_d, int K, int nvar,
+                       int64_t ncell, hipStream_t s) {
+    auto* f = prec == P_F64 ? pack_launch<double, double>
+              : prec == P_F32 ? pack_launch<float, float>
+              : prec == P_ACC64 ? pack_launch<double, float> : pack_launch<ffs, float>;
+    f(to_internal, ext, b0, b1, prob, off_u, off_d, K, nvar, ncell, s);
     return hipGetLastError();
 }
 

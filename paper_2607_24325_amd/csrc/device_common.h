@@ -105,6 +105,13 @@ __device__ __forceinline__ double rcp(double x) {
     return fma(r, e, r);
 }
 
+// Products that go into a sum are fused explicitly where the compiler's own
+// choice would depend on the code around them and results have to be the same
+// bits in several kernels.
+__device__ __forceinline__ float fused(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fused(double a, double b, double c) { return fma(a, b, c); }
+__device__ __forceinline__ ff fused(ff a, ff b, ff c) { return c + a * b; }
+
 // ------------------------------------------------------- physical fluxes ---
 //
 // For a state U and a derivative direction V of one side of an interface,
@@ -145,20 +152,21 @@ template <class T> struct Flux<T, F_EULER, 3, 0> {
         const T ir = rcp(rho);
         const T u = m * ir;
         const T half_u2 = (T)0.5 * u * u;
-        const T p = gm1 * (E - rho * half_u2);
-        const T Ep = E + p;
+        const T e = fused(-rho, half_u2, E);   // internal energy; p = gm1 e
+        const T Ep = fused(gm1, e, E);
         const T H = Ep * ir;
         f[0] = m;
-        f[1] = m * u + p;
+        f[1] = fused(m, u, gm1 * e);
         f[2] = u * Ep;
         const T dr = V[0], dm = V[1], dE = V[2];
-        const T dp = gm1 * (dE - u * dm + half_u2 * dr);
+        const T de = fused(half_u2, dr, fused(-u, dm, dE));
         // the rows of A V with the common factor a = dm - u dr taken out:
         // 2u dm - u^2 dr = u (dm + a), H dm - u H dr = H a
-        const T a = dm - u * dr;
+        const T a = fused(-u, dr, dm);
+        const T dEp = fused(gm1, de, dE);
         fv[0] = dm;
-        fv[1] = u * (dm + a) + dp;
-        fv[2] = H * a + u * (dE + dp);
+        fv[1] = fused(u, dm + a, gm1 * de);
+        fv[2] = sizeof(T) == 4 ? fused(a, H, u * dEp) : fused(u, dEp, H * a);
     }
 };
 
@@ -314,7 +322,7 @@ __device__ __forceinline__ void publish_reduced(ProbDev& P, double mx, double my
     if (my > 0.0) publish_max(&P.ay_next, my, seen_y);
     if (bad != LLONG_MAX) {
         atomicMin((long long*)&P.bad_cell, bad);
-        atomicOr(&P.err, ERR_STATE_BAD);
+        atomicOr(&P.err_next, ERR_STATE_BAD);   // err itself stays as this step began
     }
 }
 
@@ -423,6 +431,85 @@ __device__ __attribute__((noinline)) void gather_tile_speeds(const TU* out_u, ui
         }
     }
     publish_tile_speeds(P, mx, my, bad, seen_x, seen_y, s_mx, s_my, s_bad);
+}
+
+// ------------------------------------------------------------ step control --
+//
+// dt = min(CFL rule, t_end - t); the CFL rule is cfl*dx^e/alpha_x in 1D and
+// cfl/(alpha_x/dx^e + alpha_y/dy^e) in 2D (or the caller's step).  Nothing it
+// reads changes before the step's end, so every workgroup of a step can form
+// the same choice itself.
+struct StepChoice {
+    bool act;     // the problem takes this step
+    bool last;    // it lands on t_end
+    double dt;
+};
+__device__ __forceinline__ StepChoice choose_step(const ProbDev& P, const StepRule& r) {
+    const double rem = P.t_end - P.t;
+    double dtc = P.dt_in;
+    if (!r.use_dt_in) {
+        const double ax = as_double(P.ax_bits), ay = as_double(P.ay_bits);
+        dtc = r.dim == 1 ? r.cfl * P.dxe / ax : r.cfl / (ax / P.dxe + ay / P.dye);
+    }
+    StepChoice c;
+    c.act = P.t < P.t_end && !P.err && (!r.use_dt_in || dtc > 0.0);
+    c.last = c.act && !(dtc < rem);
+    c.dt = c.act ? (c.last ? rem : dtc) : 0.0;
+    return c;
+}
+
+// Ends a problem's step: t += dt (exactly t_end on the clipped last one), the
+// speeds and errors gathered from the new state become current.  Returns
+// whether it was to take the step; running: it is still short of t_end.
+// The gathered values are read past this XCD's L2 (other XCDs' atomics).
+__device__ __forceinline__ bool finish_problem(ProbDev& P, const StepRule& r, bool& running) {
+    if (r.choose) {
+        const StepChoice c = choose_step(P, r);
+        P.active = c.act;
+        P.last = c.last;
+        P.dt = c.dt;
+    }
+    const bool act = P.active;
+    // a problem whose intermediate stage was not admissible skipped its
+    // stages 2 and 3: its state and time stay those of U^n
+    if (act && !(P.err & ERR_STAGE_BAD)) {
+        P.t = P.last ? P.t_end : P.t + P.dt;
+        P.ax_bits = peek_slot(&P.ax_next);
+        P.ay_bits = peek_slot(&P.ay_next);
+        P.alpha_valid = 1;
+        P.err |= __hip_atomic_load(&P.err_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (r.flip) P.cur ^= 1;
+    }
+    P.ax_next = 0;
+    P.ay_next = 0;
+    P.err_next = 0;
+    running = P.t < P.t_end && !P.err;
+    return act;
+}
+
+// Ends the step of every problem of a launch in one wave or workgroup of n
+// threads (tid < n <= 64, or called by one wave): used by the last wave of a
+// launch over few problems.
+__device__ __forceinline__ void finish_step(ProbDev* probs, StepCtl* ctl, const StepRule& r,
+                                            int tid, int n) {
+    const int nprob = ctl->nprob;
+    int run = 0, any = 0;
+    for (int p = tid; p < nprob; p += n) {
+        bool running;
+        any |= finish_problem(probs[p], r, running);
+        run += running;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        run += __shfl_xor(run, o, 64);
+        any |= __shfl_xor(any, o, 64);
+    }
+    if (tid == 0) {
+        ctl->nactive = run;
+        ctl->step_active = any;
+        ctl->arrived = 0;
+        if (any) ctl->steps += 1;
+    }
 }
 
 // --------------------------------------- classical smoothness indicator ---

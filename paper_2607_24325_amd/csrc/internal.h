@@ -43,6 +43,8 @@ struct ProbDev {
                        // ERR_STAGE_BAD (an intermediate stage input)
     int32_t alpha_valid;  // ax_bits/ay_bits hold the speeds of the current state
     int64_t bad_cell;  // smallest flat index of a non-admissible cell
+    int32_t err_next;  // err of the state being written, current at the step's end
+    int32_t cur;       // state set (0 or 1) that holds the problem's state
 };
 
 // Global step control, resident in device memory.
@@ -53,8 +55,19 @@ struct StepCtl {
     int32_t dim;
     int32_t nactive;   // problems still short of t_end after the last step
     int32_t step_active;  // some problem advanced in the current step
-    int32_t pad;
+    int32_t arrived;   // tiles or workgroups of the current launch that are done
+    int32_t sum_run;   // counts in the making (finish_kernel)
+    int32_t sum_any;
     int64_t steps;     // steps in which some problem advanced
+};
+
+// How a launch takes and ends a step of its problems.
+struct StepRule {
+    double cfl;
+    int32_t dim;
+    int32_t use_dt_in;  // the caller's step lengths (ProbDev::dt_in)
+    int32_t choose;     // the kernels choose dt themselves; else a dt kernel ran
+    int32_t flip;       // the new state is in the other state set
 };
 
 // 2D tile: a strip of 64 loaded columns (60 output columns starting at i0)
@@ -75,6 +88,7 @@ struct Chunk {
 
 constexpr int STRIP_OUT = 60;      // output columns per 2D strip (64 lanes - 4 halo)
 constexpr int TILE1D_OUT = 254;    // output cells per 1D tile (256 threads - 2)
+constexpr int STEP1D_HALO = 12;    // halo cells of a wave of the 1D step kernel
 constexpr int CHUNK_CELLS = 2048;  // cells per reduction chunk
 
 // Scheme constants of one handle.
@@ -97,6 +111,7 @@ struct StateBuf {
 
 struct StageArgs {
     StateBuf in;        // U^(k): stencil input
+    StateBuf in1;       // 1D right-hand sides: input of problems whose state set is 1
     StateBuf out;       // U^(k+1)
     const void* un;     // u-bar of U^n (stages 2, 3)
     void* h;            // saved hats of U^n
@@ -106,6 +121,17 @@ struct StageArgs {
     const void* tiles;
     int32_t ntiles;
     int32_t tile_offset;
+    Scheme sch;
+};
+
+struct Step1Args {
+    StateBuf s[2];      // the state sets a step reads and writes, by ProbDev::cur
+    ProbDev* probs;
+    StepCtl* ctl;
+    const Tile1D* tiles;  // of step1d_cells * 64 - STEP1D_HALO cells
+    int32_t ntiles;
+    int32_t finish;     // the launch's last wave ends the step
+    StepRule rule;
     Scheme sch;
 };
 
@@ -128,15 +154,27 @@ hipError_t launch_reset(ProbDev* probs, StepCtl* ctl, int nprob, int sel, hipStr
 // all_problems: 1 = every problem (rhs / alpha queries); 0 = only problems
 // still short of t_end, without a pending error and whose speeds are not
 // current (time stepping: stage 3 computes them for the next step).
-hipError_t launch_alpha(int prec, int flux, int dim, const void* u, ProbDev* probs,
+// u0, u1: the averages of problems whose state set is 0 and 1.
+hipError_t launch_alpha(int prec, int flux, int dim, const void* u0, const void* u1, ProbDev* probs,
                         const Chunk* chunks, int nchunks, const Scheme& sch, int sel,
                         int grid, hipStream_t s);
 hipError_t launch_dt(ProbDev* probs, StepCtl* ctl, int nprob, int use_dt_in, int own_ctl,
                      hipStream_t s);
-hipError_t launch_finish(ProbDev* probs, StepCtl* ctl, int nprob, hipStream_t s);
+hipError_t launch_finish(ProbDev* probs, StepCtl* ctl, int nprob, const StepRule& rule,
+                         hipStream_t s);
+// One whole 1D step; cells: cells per lane (step1d_cells).
+hipError_t launch_step1d(int prec, int flux, int cells, const Step1Args& a, int grid, hipStream_t s);
+// Cells per lane of the 1D step kernel for these problems.
+int step1d_cells(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg);
+// Whether the last wave of a step kernel ends the step (finish_step) instead
+// of a kernel of its own (5 us with the gap before it): every wave then
+// arrives at one counter, and one wave ends all problems, 64 at a time.
+inline int ends_own_step(int ntiles, int nprob) { return ntiles <= 1024 && nprob <= 64; }
 // Converts one problem's state between the boundary layout (double,
-// ext[((var*K + c)*ny + j)*nx + i]) and the internal planes of buf.
-hipError_t launch_pack(int prec, int to_internal, double* ext, StateBuf buf, int64_t off_u,
+// ext[((var*K + c)*ny + j)*nx + i]) and the internal planes of b0 or b1, the
+// one prob->cur names.
+hipError_t launch_pack(int prec, int to_internal, double* ext, StateBuf b0, StateBuf b1,
+                       const ProbDev* prob, int64_t off_u,
                        int64_t off_d, int K, int nvar, int64_t ncell, hipStream_t s);
 
 // --- host helpers of the C ABI (api.cpp) --------------------------------
@@ -151,6 +189,11 @@ Scheme scheme_of(const hweno_problem& p0, const hweno_config& cfg);
 int split_rows(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg, int cap);
 // Tiles of one problem at that height, and the first row of segment s.
 int tiles_2d(int nx, int ny, int rows);
+// Tiles of a 1D problem in the step kernel with that many cells per lane.
+inline int tiles_1d(int nx, int cells) {
+    const int out = 64 * cells - STEP1D_HALO;
+    return (nx + out - 1) / out;
+}
 __host__ __device__ inline int segment_row(int s, int nseg, int ny) {
     return (int)((int64_t)s * ny / nseg);
 }

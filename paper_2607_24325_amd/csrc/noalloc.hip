@@ -21,7 +21,7 @@ static __device__ __align__(256) unsigned char scratch[HWENO_NOALLOC_SCRATCH_BYT
 // chunks of one problem into the scratch (per-problem order; results do not
 // depend on the order of the tiles).
 __global__ void noalloc_setup_kernel(ProbDev pd, StepCtl ctl, ProbDev* probs, StepCtl* dctl,
-                                     int dim, int nseg, void* tiles, int ntiles, Chunk* chunks,
+                                     int dim, int nseg, int out1d, void* tiles, int ntiles, Chunk* chunks,
                                      int nchunks) {
     const int tid = blockIdx.x * blockDim.x + threadIdx.x;
     const int nth = gridDim.x * blockDim.x;
@@ -32,7 +32,7 @@ __global__ void noalloc_setup_kernel(ProbDev pd, StepCtl ctl, ProbDev* probs, St
     const int strips = (pd.nx + STRIP_OUT - 1) / STRIP_OUT;
     for (int t = tid; t < ntiles; t += nth) {
         if (dim == 1) {
-            ((Tile1D*)tiles)[t] = Tile1D{0, t * TILE1D_OUT};
+            ((Tile1D*)tiles)[t] = Tile1D{0, t * out1d};
         } else {
             const int js = t / strips, is = t - js * strips;
             const int j0 = segment_row(js, nseg, pd.ny), j1 = segment_row(js + 1, nseg, pd.ny);
@@ -109,6 +109,9 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
     // regions: three state sets, the saved hats, table, control, tiles, chunks
     const size_t ub = up256((size_t)ncell * K * su), db = up256((size_t)ncell * K * D * sd);
     const size_t cb = up256((size_t)nchunks * sizeof(Chunk));
+    // 1D: the step kernel, or stage by stage with the speeds of every stage
+    const int cells1d = dim == 1 && !cfg->alpha_stage ? step1d_cells(prob, 1, *cfg) : 0;
+    const int out1d = cells1d ? 64 * cells1d - STEP1D_HALO : TILE1D_OUT;
     // segments as hweno_step cuts them; 32 rows where only their shorter list fits
     int rows = dim == 2 ? split_rows(prob, 1, *cfg, 32) : 0, ntiles = 0;
     size_t tb = 0, need = 0;
@@ -137,6 +140,10 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
     StepCtl* ctl = (StepCtl*)p; p += up256(sizeof(StepCtl));
     void* tiles = p; p += tb;
     Chunk* chunks = (Chunk*)p;
+    if (cells1d) {   // two sets only: the longer tile list goes where the third would
+        tiles = U[2].u;
+        ntiles = tiles_1d(pr.nx, cells1d);
+    }
 
     // Every value a launch reads is written here first: the table entry and
     // step control come from the arguments (speeds zero, no error, the
@@ -152,34 +159,53 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
     const Scheme sch = scheme_of(pr, *cfg);
     const int sgrid = std::max(1, std::min(1024, (std::max(ntiles, nchunks) + 255) / 256));
     const int nseg = dim == 2 ? (pr.ny + rows - 1) / rows : 0;
-    noalloc_setup_kernel<<<sgrid, 256, 0, s>>>(pd, sc, probs, ctl, dim, nseg, tiles, ntiles,
+    noalloc_setup_kernel<<<sgrid, 256, 0, s>>>(pd, sc, probs, ctl, dim, nseg, out1d, tiles,
+                                               ntiles,
                                                chunks, nchunks);
     NA_TRY(hipGetLastError());
-    NA_TRY(launch_pack(prec, 1, const_cast<double*>(state_in), U[0], 0, 0, K, nvar, ncell, s));
-    NA_TRY(launch_alpha(prec, flux, dim, U[0].u, probs, chunks, nchunks, sch, SEL_STALE, 0, s));
-    NA_TRY(launch_dt(probs, ctl, 1, use_dt_in, 1, s));
-    for (int mode = MODE_S1; mode <= MODE_S3; ++mode) {
-        if (mode != MODE_S1 && cfg->alpha_stage) {
-            NA_TRY(launch_reset(probs, ctl, 1, SEL_ACTIVE, s));
-            NA_TRY(launch_alpha(prec, flux, dim, U[mode - 1].u, probs, chunks, nchunks, sch,
-                                SEL_ACTIVE, 0, s));
-        }
-        StageArgs a{};
-        const int k = mode - 1;
-        a.in = U[k];
-        a.out = U[mode == MODE_S3 ? 0 : k + 1];
-        a.un = U[0].u;
-        a.h = H;
+    NA_TRY(launch_pack(prec, 1, const_cast<double*>(state_in), U[0], U[1], probs, 0, 0, K, nvar, ncell, s));
+    NA_TRY(launch_alpha(prec, flux, dim, U[0].u, U[1].u, probs, chunks, nchunks, sch,
+                        SEL_STALE, 0, s));
+    StepRule rule{cfg->cfl, dim, use_dt_in, 0, 0};
+    if (cells1d) {
+        rule.choose = rule.flip = 1;
+        Step1Args a{};
+        a.s[0] = U[0];
+        a.s[1] = U[1];
         a.probs = probs;
-        a.tiles = tiles;
+        a.ctl = ctl;
+        a.tiles = (const Tile1D*)tiles;
         a.ntiles = ntiles;
-        a.tile_offset = 0;
+        a.finish = ends_own_step(ntiles, 1);
+        a.rule = rule;
         a.sch = sch;
-        if (dim == 1) NA_TRY(launch_stage1d(prec, flux, mode, a, 0, s));
-        else NA_TRY(launch_stage2d(prec, flux, cfg->gauss_q, mode, 0, a, 0, s));
+        NA_TRY(launch_step1d(prec, flux, cells1d, a, 0, s));
+        if (!a.finish) NA_TRY(launch_finish(probs, ctl, 1, rule, s));
+    } else {
+        NA_TRY(launch_dt(probs, ctl, 1, use_dt_in, 1, s));
+        for (int mode = MODE_S1; mode <= MODE_S3; ++mode) {
+            if (mode != MODE_S1 && cfg->alpha_stage) {
+                NA_TRY(launch_reset(probs, ctl, 1, SEL_ACTIVE, s));
+                NA_TRY(launch_alpha(prec, flux, dim, U[mode - 1].u, U[mode - 1].u, probs, chunks, nchunks, sch,
+                                    SEL_ACTIVE, 0, s));
+            }
+            StageArgs a{};
+            const int k = mode - 1;
+            a.in = U[k];
+            a.out = U[mode == MODE_S3 ? 0 : k + 1];
+            a.un = U[0].u;
+            a.h = H;
+            a.probs = probs;
+            a.tiles = tiles;
+            a.ntiles = ntiles;
+            a.tile_offset = 0;
+            a.sch = sch;
+            if (dim == 1) NA_TRY(launch_stage1d(prec, flux, mode, a, 0, s));
+            else NA_TRY(launch_stage2d(prec, flux, cfg->gauss_q, mode, 0, a, 0, s));
+        }
+        NA_TRY(launch_finish(probs, ctl, 1, rule, s));
     }
-    NA_TRY(launch_finish(probs, ctl, 1, s));
-    NA_TRY(launch_pack(prec, 0, state_out, U[0], 0, 0, K, nvar, ncell, s));
+    NA_TRY(launch_pack(prec, 0, state_out, U[0], U[1], probs, 0, 0, K, nvar, ncell, s));
     if (dt_out || bad_out) {
         noalloc_report_kernel<<<1, 64, 0, s>>>(probs, dt_out, bad_out);
         NA_TRY(hipGetLastError());
