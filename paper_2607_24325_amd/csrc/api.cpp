@@ -33,6 +33,8 @@ struct hweno_handle {
     void* H = nullptr;
     ProbDev* d_probs = nullptr;
     StepCtl* d_ctl = nullptr;
+    ProbEnd* d_ends = nullptr;      // how steps end
+    size_t slots_cap = 0;           // speed slots
     std::vector<ProbDev> h_probs;   // static fields (offsets, sizes, spacing)
     std::vector<int64_t> ncell;
     // work lists
@@ -97,8 +99,8 @@ static void prec_sizes(int prec, size_t* su, size_t* sd) {
 
 // Sizes of every region of a handle's workspace.
 struct Layout {
-    size_t u_bytes, d_bytes, probs, ctl, tiles, chunks, stage, total;
-    size_t tiles_cap;
+    size_t u_bytes, d_bytes, probs, ctl, ends, groups, slots, tiles, chunks, stage, total;
+    size_t tiles_cap, slots_cap;
     int nchunks;
     size_t stage_elems;
 };
@@ -269,7 +271,7 @@ static Layout layout_of(const hweno_problem* probs, int32_t nprob, const hweno_c
     const int nvar = 1 + D;
     size_t su, sd;
     prec_sizes(cfg->precision, &su, &sd);
-    size_t nu = 0, nd = 0, maxst = 0, tiles = 0, steps1d = 0;
+    size_t nu = 0, nd = 0, maxst = 0, tiles = 0, steps1d = 0, slots = 0;
     int nch = 0;
     const int cells1d = D == 1 ? step1d_cells(probs, nprob, *cfg) : 0;
     for (int p = 0; p < nprob; ++p) {
@@ -282,12 +284,19 @@ static Layout layout_of(const hweno_problem* probs, int32_t nprob, const hweno_c
             steps1d += tiles_1d(probs[p].nx, cells1d);
         }
         else tiles += tiles_2d(probs[p].nx, probs[p].ny, 8);  // smallest height a caller can ask for
+        // lines for the problems that can be cut into more than SLOTS tiles
+        if ((D == 1 ? tiles_1d(probs[p].nx, 1) : tiles_2d(probs[p].nx, probs[p].ny, 2)) > SLOTS)
+            slots += SLOTS;
         nch += (int)((nc + CHUNK_CELLS - 1) / CHUNK_CELLS);
     }
     L.u_bytes = align256(nu * su);
     L.d_bytes = align256(nd * sd);
     L.probs = align256(sizeof(ProbDev) * nprob);
     L.ctl = align256(sizeof(StepCtl));
+    L.ends = align256(sizeof(ProbEnd) * nprob);
+    L.groups = align256(sizeof(Slot) * (SLOTS + 1));
+    L.slots_cap = slots;
+    L.slots = align256(sizeof(Slot) * slots);
     if (D == 2) {   // shorter segments of small problems (split_rows)
         int64_t two = 0;
         for (int p = 0; p < nprob; ++p) two += tiles_2d(probs[p].nx, probs[p].ny, 2);
@@ -299,8 +308,8 @@ static Layout layout_of(const hweno_problem* probs, int32_t nprob, const hweno_c
     L.chunks = align256(sizeof(Chunk) * nch);
     L.stage_elems = 2 * maxst;
     L.stage = align256(sizeof(double) * L.stage_elems);
-    L.total = 3 * (L.u_bytes + L.d_bytes) + L.d_bytes + L.probs + L.ctl + L.tiles + L.chunks +
-              L.stage;
+    L.total = 3 * (L.u_bytes + L.d_bytes) + L.d_bytes + L.probs + L.ctl + L.ends + L.groups + L.slots +
+              L.tiles + L.chunks + L.stage;
     return L;
 }
 
@@ -312,12 +321,14 @@ static Layout layout_of(const hweno_problem* probs, int32_t nprob, const hweno_c
 // dispatcher hands workgroup b to XCD b mod 8), then the per-problem list.
 static int build_tiles(hweno_handle* h) {
     std::vector<int> begin(h->nprob), count(h->nprob);
+    std::vector<ProbEnd> ends(h->nprob);
     if (h->dim == 1) {
         std::vector<Tile1D> step, per;
         for (int p = 0; p < h->nprob; ++p) {
             const int nx = h->probs[p].nx;
             const int out = h->cells1d ? 64 * h->cells1d - STEP1D_HALO : TILE1D_OUT;
             for (int c0 = 0; c0 < nx; c0 += out) step.push_back({p, c0});
+            ends[p].ntiles = (nx + out - 1) / out;
             begin[p] = (int)per.size();
             for (int c0 = 0; c0 < nx; c0 += TILE1D_OUT) per.push_back({p, c0});
             count[p] = (int)per.size() - begin[p];
@@ -341,9 +352,12 @@ static int build_tiles(hweno_handle* h) {
             const int nseg = (ny + rows - 1) / rows;
             for (int s = 0; s < nseg; ++s) {
                 const int j0 = segment_row(s, nseg, ny), j1 = segment_row(s + 1, nseg, ny);
-                for (int i0 = 0; i0 < nx; i0 += STRIP_OUT) per.push_back({p, i0, j0, j1 - j0});
+                for (int i0 = 0; i0 < nx; i0 += STRIP_OUT)
+                    per.push_back({p, i0, j0, (int16_t)(j1 - j0),
+                                   (int16_t)(((int)per.size() - begin[p]) % SLOTS)});
             }
             count[p] = (int)per.size() - begin[p];
+            ends[p].ntiles = count[p];
         }
         const size_t n = per.size();
         if (2 * n > h->tiles_cap) return fail(h, HWENO_ERR_OOM, "tile list exceeds its buffer");
@@ -363,6 +377,15 @@ static int build_tiles(hweno_handle* h) {
         h->ntiles_step = (int)n;
         for (int& b : begin) b += (int)n;
     }
+    size_t slots = 0;
+    for (ProbEnd& e : ends) {
+        e.arrived = e.pad = 0;
+        e.slot0 = e.ntiles > SLOTS ? (int)slots : -1;
+        if (e.slot0 >= 0) slots += SLOTS;
+    }
+    if (slots > h->slots_cap) return fail(h, HWENO_ERR_OOM, "speed slots exceed their buffer");
+    HIP_TRY(h, hipMemcpy(h->d_ends, ends.data(), sizeof(ProbEnd) * h->nprob,
+                         hipMemcpyHostToDevice));
     h->tile_begin = begin;
     h->tile_count = count;
     return HWENO_OK;
@@ -440,6 +463,12 @@ static int setup(hweno_handle* h, const hweno_problem* probs, int32_t nprob,
     h->H = p; p += L.d_bytes;
     h->d_probs = (ProbDev*)p; p += L.probs;
     h->d_ctl = (StepCtl*)p; p += L.ctl;
+    h->d_ends = (ProbEnd*)p; p += L.ends;
+    Slot* groups = (Slot*)p; p += L.groups;
+    Slot* slots = (Slot*)p; p += L.slots;
+    h->slots_cap = L.slots_cap;
+    // every step leaves them clear for the next
+    HIP_TRY(h, hipMemset(groups, 0, L.groups + L.slots));
     h->d_tiles = p; p += L.tiles;
     h->tiles_cap = L.tiles_cap;
     h->d_chunks = (Chunk*)p; p += L.chunks;
@@ -472,6 +501,9 @@ static int setup(hweno_handle* h, const hweno_problem* probs, int32_t nprob,
     ctl.cfl = cfg->cfl;
     ctl.nprob = nprob;
     ctl.dim = h->dim;
+    ctl.ends = h->d_ends;
+    ctl.groups = groups;
+    ctl.slots = slots;
     HIP_TRY(h, hipMemcpy(h->d_ctl, &ctl, sizeof ctl, hipMemcpyHostToDevice));
     h->state_set.assign(nprob, 0);
     h->tun.tile_rows = 32;
@@ -620,6 +652,7 @@ static StageArgs stage_args(hweno_handle* h, int mode) {
     a.ntiles = h->ntiles_step;
     a.tile_offset = 0;
     a.sch = h->sch;
+    a.ctl = h->d_ctl;
     return a;
 }
 
@@ -693,7 +726,11 @@ enum LaunchKind { LK_OTHER = 0, LK_ALPHA = 1, LK_STAGE = 2, LK_STEP = 3 };  // L
 // clears the step counters itself, which leaves out the reset kernel too).
 template <class Rec>
 static int enqueue_step_with(hweno_handle* h, int use_dt_in, bool fast, Rec&& rec) {
-    const int own_ctl = fast && (h->cells1d || h->nprob <= 256);
+    // with the speeds of every stage, dt comes from a kernel of its own, and
+    // the stages take it from the table; else each launch chooses it itself
+    const bool choose = !h->cfg.alpha_stage;
+    const int flags = (use_dt_in ? STEP_DT_IN : 0) | (choose ? STEP_CHOOSE : 0);
+    const int own_ctl = fast && (choose || h->nprob <= 256);
     // speeds are gathered by stage 3 of the previous step; the reduction
     // kernel only fills them in after set_state
     if (!own_ctl)
@@ -704,26 +741,22 @@ static int enqueue_step_with(hweno_handle* h, int use_dt_in, bool fast, Rec&& re
                                 h->nchunks, h->sch, SEL_STALE, 0, h->stream);
         }));
     if (h->cells1d) {
-        // one kernel takes the whole step; its last wave ends it where few
-        // tiles (arrivals at one counter) and few problems are to be ended
         Step1Args a{};
         a.s[0] = h->U[0];
         a.s[1] = h->U[1];
         a.probs = h->d_probs;
-        a.ctl = h->d_ctl;
         a.tiles = (const Tile1D*)h->d_tiles;
         a.ntiles = h->ntiles_step;
-        a.finish = ends_own_step(h->ntiles_step, h->nprob);
-        a.rule = StepRule{h->cfg.cfl, 1, use_dt_in, 1, 1};
+        a.flags = flags | STEP_FLIP;
+        a.ctl = h->d_ctl;
         a.sch = h->sch;
         HIP_TRY(h, rec(LK_STEP, [&] {
             return launch_step1d(h->prec, h->flux, h->cells1d, a, h->tun.grid_blocks, h->stream);
         }));
-        if (!a.finish)
-            HIP_TRY(h, rec(LK_OTHER, [&] { return launch_finish(h->d_probs, h->d_ctl, h->nprob, a.rule, h->stream); }));
         return HWENO_OK;
     }
-    HIP_TRY(h, rec(LK_OTHER, [&] { return launch_dt(h->d_probs, h->d_ctl, h->nprob, use_dt_in, own_ctl, h->stream); }));
+    if (!choose)
+        HIP_TRY(h, rec(LK_OTHER, [&] { return launch_dt(h->d_probs, h->d_ctl, h->nprob, use_dt_in, own_ctl, h->stream); }));
     for (int mode = MODE_S1; mode <= MODE_S3; ++mode) {
         if (mode != MODE_S1 && h->cfg.alpha_stage) {
             // speeds of this stage's input (per-stage option)
@@ -734,9 +767,12 @@ static int enqueue_step_with(hweno_handle* h, int use_dt_in, bool fast, Rec&& re
                                     h->nchunks, h->sch, SEL_ACTIVE, 0, h->stream);
             }));
         }
-        HIP_TRY(h, rec(LK_STAGE, [&] { return launch_stage(h, mode, stage_args(h, mode)); }));
+        HIP_TRY(h, rec(LK_STAGE, [&] {
+            StageArgs a = stage_args(h, mode);
+            a.flags = flags;
+            return launch_stage(h, mode, a);
+        }));
     }
-    HIP_TRY(h, rec(LK_OTHER, [&] { return launch_finish(h->d_probs, h->d_ctl, h->nprob, StepRule{h->cfg.cfl, h->dim, use_dt_in, 0, 0}, h->stream); }));
     return HWENO_OK;
 }
 

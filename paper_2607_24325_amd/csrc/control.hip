@@ -109,7 +109,7 @@ __global__ void __launch_bounds__(256) alpha_kernel(const void* u0, const void* 
 // Chooses a problem's step for kernels that read it from the table; returns
 // whether the problem takes this step.
 __device__ __forceinline__ int select_dt(ProbDev& P_, const StepCtl* ctl, int use_dt_in) {
-    const StepChoice c = choose_step(P_, StepRule{ctl->cfl, ctl->dim, use_dt_in, 1, 0});
+    const StepChoice c = choose_step(P_, ctl, STEP_CHOOSE | (use_dt_in ? STEP_DT_IN : 0));
     P_.active = c.act;
     P_.last = c.last;
     P_.dt = c.dt;
@@ -131,43 +131,6 @@ __global__ void dt_kernel(ProbDev* probs, StepCtl* ctl, int nprob, int use_dt_in
     } else if (act) {
         atomicOr(&ctl->step_active, 1);
     }
-}
-
-// Ends the step of every problem and counts those still running and the
-// steps in which anything advanced.  A workgroup takes FINISH_PROBS problems,
-// so that batches of up to that many (four rounds of it) are counted by one
-// workgroup; beyond, the last workgroup to get here adds the counts up.
-constexpr int FINISH_PROBS = 4096;
-__global__ void __launch_bounds__(1024) finish_kernel(ProbDev* probs, StepCtl* ctl, int nprob,
-                                                      StepRule rule) {
-    int run = 0, any = 0;
-    const int p0 = blockIdx.x * FINISH_PROBS;
-    for (int p = p0 + threadIdx.x; p < nprob && p < p0 + FINISH_PROBS; p += blockDim.x) {
-        bool running;
-        any |= finish_problem(probs[p], rule, running);
-        run += running;
-    }
-    __shared__ int srun;
-    if (threadIdx.x == 0) srun = 0;
-    any = __syncthreads_or(any);
-    if (run) atomicAdd(&srun, run);
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    run = srun;
-    if (gridDim.x > 1) {
-        // counts of this and the workgroups before it; the additions of each
-        // have reached memory before it arrives
-        atomicAdd(&ctl->sum_run, run);
-        atomicOr(&ctl->sum_any, any);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (atomicAdd(&ctl->arrived, 1) != (int)gridDim.x - 1) return;
-        run = atomicExch(&ctl->sum_run, 0);
-        any = atomicExch(&ctl->sum_any, 0);
-        ctl->arrived = 0;
-    }
-    ctl->nactive = run;
-    ctl->step_active = any;
-    if (any) ctl->steps += 1;
 }
 
 template <class TU, class TD>
@@ -228,13 +191,6 @@ hipError_t launch_dt(ProbDev* probs, StepCtl* ctl, int nprob, int use_dt_in, int
                      hipStream_t s) {
     if (own_ctl && nprob > 256) return hipErrorInvalidValue;
     dt_kernel<<<(nprob + 255) / 256, 256, 0, s>>>(probs, ctl, nprob, use_dt_in, own_ctl);
-    return hipGetLastError();
-}
-
-hipError_t launch_finish(ProbDev* probs, StepCtl* ctl, int nprob, const StepRule& rule,
-                         hipStream_t s) {
-    const int threads = nprob >= 1024 ? 1024 : (nprob + 63) / 64 * 64;
-    finish_kernel<<<(nprob + FINISH_PROBS - 1) / FINISH_PROBS, threads, 0, s>>>(probs, ctl, nprob, rule);
     return hipGetLastError();
 }
 

@@ -312,59 +312,171 @@ __device__ __forceinline__ void publish_max(uint64_t* slot, double v, uint64_t s
     if (b > seen) atomicMax((unsigned long long*)slot, b);
 }
 
-// Folds reduced speeds and a first bad cell into the problem's slots for the
-// state being written (one lane calls this; seen_x, seen_y: earlier reads of
-// the two slots).  Speeds are non-negative, so their bit patterns order as
-// unsigned integers.
-__device__ __forceinline__ void publish_reduced(ProbDev& P, double mx, double my, long long bad,
-                                                uint64_t seen_x, uint64_t seen_y) {
-    publish_max(&P.ax_next, mx, seen_x);
-    if (my > 0.0) publish_max(&P.ay_next, my, seen_y);
+// Where a tile of the group `slot` leaves its speed maxima.
+__device__ __forceinline__ uint64_t* speed_slot(ProbDev& P, int p, const StepCtl* ctl, int slot) {
+    const int slot0 = ctl->ends[p].slot0;
+    return slot0 < 0 ? &P.ax_next : &ctl->slots[slot0 + slot].ax;
+}
+
+// Folds a tile's reduced speeds and first bad cell into the problem's maxima
+// for the state being written (one lane calls this).  Speeds are non-negative,
+// so their bit patterns order as unsigned integers; err itself stays as the
+// step began with.
+__device__ __forceinline__ void publish_speeds(ProbDev& P, int p, const StepCtl* ctl, int slot,
+                                               double mx, double my, long long bad) {
+    uint64_t* s = speed_slot(P, p, ctl, slot);
+    atomicMax((unsigned long long*)&s[0], (unsigned long long)__double_as_longlong(mx));
+    if (my > 0.0)
+        atomicMax((unsigned long long*)&s[1], (unsigned long long)__double_as_longlong(my));
     if (bad != LLONG_MAX) {
         atomicMin((long long*)&P.bad_cell, bad);
-        atomicOr(&P.err_next, ERR_STATE_BAD);   // err itself stays as this step began
+        atomicOr(&P.err_next, ERR_STATE_BAD);
     }
 }
 
-// Wave-level version: every lane brings its values, lane 0 publishes.  The
-// bad-cell minimum is only formed when some lane has one.
-__device__ __forceinline__ void publish_next_speeds(ProbDev& P, double mx, double my,
-                                                    long long bad, uint64_t seen_x,
-                                                    uint64_t seen_y) {
-    mx = wave_max_d(mx);
-    my = wave_max_d(my);
-    if (__any(bad != LLONG_MAX)) bad = wave_min_ll(bad);
-    if ((threadIdx.x & 63) == 0) publish_reduced(P, mx, my, bad, seen_x, seen_y);
+// ------------------------------------------------------------ step control --
+//
+// dt = min(CFL rule, t_end - t); the CFL rule is cfl*dx^e/alpha_x in 1D and
+// cfl/(alpha_x/dx^e + alpha_y/dy^e) in 2D (or the caller's step).  Nothing it
+// reads changes before the step's end, so every workgroup of a step can form
+// the same choice itself.
+struct StepChoice {
+    bool act;     // the problem takes this step
+    bool last;    // it lands on t_end
+    double dt;
+};
+__device__ __forceinline__ StepChoice choose_step(const ProbDev& P, const StepCtl* ctl, int flags) {
+    const double rem = P.t_end - P.t;
+    double dtc = P.dt_in;
+    if (!(flags & STEP_DT_IN)) {
+        const double ax = as_double(P.ax_bits), ay = as_double(P.ay_bits);
+        dtc = ctl->dim == 1 ? ctl->cfl * P.dxe / ax : ctl->cfl / (ax / P.dxe + ay / P.dye);
+    }
+    StepChoice c;
+    c.act = P.t < P.t_end && !P.err && (!(flags & STEP_DT_IN) || dtc > 0.0);
+    c.last = c.act && !(dtc < rem);
+    c.dt = c.act ? (c.last ? rem : dtc) : 0.0;
+    return c;
 }
 
-// Folds lane maxima of the wave speeds, and first non-admissible cells, of a
-// workgroup into the problem's slots: reduced over each wave, then over the
-// waves through LDS (s_mx, s_my, s_bad: one entry per wave) by thread 0,
-// which read the slots (seen_x, seen_y) before the values were formed.
-// Every thread of the workgroup calls it (it holds a barrier).
-__device__ __forceinline__ void publish_tile_speeds(ProbDev& P, double mx, double my,
-                                                    long long bad, uint64_t seen_x,
-                                                    uint64_t seen_y, double* s_mx, double* s_my,
-                                                    long long* s_bad) {
+// The same for a stage kernel, which takes the choice of a dt kernel where one
+// ran, and where stages 2 and 3 skip a problem whose stage input was not
+// admissible (per-stage speeds): its U^n stays as it is.
+__device__ __forceinline__ StepChoice stage_step(const ProbDev& P, const StepCtl* ctl, int flags,
+                                                 int mode) {
+    if (flags & STEP_CHOOSE) {
+        StepChoice c = choose_step(P, ctl, flags);   // the same in every lane: kept in scalar registers
+        c.act = __builtin_amdgcn_readfirstlane(c.act);
+        c.dt = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(c.dt)),
+                                __builtin_amdgcn_readfirstlane(__double2loint(c.dt)));
+        return c;
+    }
+    StepChoice c;
+    c.act = P.active && (mode == MODE_S1 || !(P.err & ERR_STAGE_BAD));
+    c.last = P.last;
+    c.dt = P.dt;
+    return c;
+}
+
+// Ends a problem's step: t += dt (exactly t_end on the clipped last one), the
+// speeds (ax, ay) and errors gathered from the new state become current.
+// Returns whether it was to take the step; running: it is still short of
+// t_end.  What other workgroups gathered is read past this XCD's L2.
+__device__ __forceinline__ bool finish_problem(ProbDev& P, const StepCtl* ctl, int flags,
+                                               uint64_t ax, uint64_t ay, bool& running) {
+    if (flags & STEP_CHOOSE) {
+        const StepChoice c = choose_step(P, ctl, flags);
+        P.active = c.act;
+        P.last = c.last;
+        P.dt = c.dt;
+    }
+    const bool act = P.active;
+    // a problem whose intermediate stage was not admissible skipped its
+    // stages 2 and 3: its state and time stay those of U^n
+    if (act && !(P.err & ERR_STAGE_BAD)) {
+        P.t = P.last ? P.t_end : P.t + P.dt;
+        P.ax_bits = ax;
+        P.ay_bits = ay;
+        P.alpha_valid = 1;
+        P.err |= __hip_atomic_load(&P.err_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (flags & STEP_FLIP) P.cur ^= 1;
+    }
+    P.ax_next = 0;
+    P.ay_next = 0;
+    P.err_next = 0;
+    running = P.t < P.t_end && !P.err;
+    return act;
+}
+
+// Waits until this wave's atomics have been performed.
+__device__ __forceinline__ void wait_atomics() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Arrival of a finished tile (group `slot`) of problem p, by the wave that
+// published its speeds: every lane calls it.  The problem's last tile ends its
+// step, the launch's last problem writes the step counters.
+__device__ __forceinline__ void end_tile(ProbDev& P, int p, int slot, StepCtl* ctl, int flags) {
     const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    mx = wave_max_d(mx);
-    my = wave_max_d(my);
-    if (__any(bad != LLONG_MAX)) bad = wave_min_ll(bad);
+    ProbEnd& pe = ctl->ends[p];
+    const int ntiles = pe.ntiles, slot0 = pe.slot0;
+    int last = 0;
     if (lane == 0) {
-        s_mx[w] = mx;
-        s_my[w] = my;
-        s_bad[w] = bad;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int v = 1; v < nw; ++v) {
-            mx = fmax(mx, s_mx[v]);
-            my = fmax(my, s_my[v]);
-            bad = s_bad[v] < bad ? s_bad[v] : bad;
+        wait_atomics();
+        if (slot0 < 0) {
+            last = atomicAdd(&pe.arrived, 1) == ntiles - 1;
+        } else if (atomicAdd(&ctl->slots[slot0 + slot].arrived, 1) == (ntiles - slot - 1) / SLOTS) {
+            last = atomicAdd(&pe.arrived, 1) == SLOTS - 1;
         }
-        publish_reduced(P, mx, my, bad, seen_x, seen_y);
     }
+    if (!__builtin_amdgcn_readfirstlane(last)) return;
+    uint64_t ax, ay;
+    if (slot0 < 0) {
+        ax = peek_slot(&P.ax_next);
+        ay = peek_slot(&P.ay_next);
+    } else {
+        Slot& s = ctl->slots[slot0 + lane];
+        ax = (uint64_t)__double_as_longlong(wave_max_d(as_double(peek_slot(&s.ax))));
+        ay = (uint64_t)__double_as_longlong(wave_max_d(as_double(peek_slot(&s.ay))));
+        s.ax = s.ay = 0;
+        s.arrived = 0;
+    }
+    if (lane != 0) return;
+    pe.arrived = 0;
+    bool running;
+    int any = finish_problem(P, ctl, flags, ax, ay, running), run = running;
+    const int nprob = ctl->nprob;
+    if (nprob > 1) {
+        // the group's counts reach memory before the group arrives
+        Slot& g = ctl->groups[p & (SLOTS - 1)];
+        if (run) atomicAdd(&g.run, run);
+        if (any) atomicOr(&g.any, any);
+        wait_atomics();
+        if (atomicAdd(&g.arrived, 1) != (nprob - (p & (SLOTS - 1)) - 1) / SLOTS) return;
+        Slot& all = ctl->groups[SLOTS];
+        run = __hip_atomic_load(&g.run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        any = __hip_atomic_load(&g.any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        g.run = g.any = g.arrived = 0;
+        if (run) atomicAdd(&all.run, run);
+        if (any) atomicOr(&all.any, any);
+        wait_atomics();
+        if (atomicAdd(&all.arrived, 1) != (nprob < SLOTS ? nprob : SLOTS) - 1) return;
+        run = __hip_atomic_load(&all.run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        any = __hip_atomic_load(&all.any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        all.run = all.any = all.arrived = 0;
+    }
+    ctl->nactive = run;
+    ctl->step_active = any;
+    if (any) ctl->steps += 1;
+}
+
+// publish_speeds by the wave's first lane (when a tile stepped), then
+// end_tile, in a call of its own: inlined into a stage kernel it would raise
+// the register allocation of the march or the stage.
+__device__ __attribute__((noinline)) inline void publish_and_end(ProbDev* P, int p, int slot,
+                                                                 StepCtl* ctl, int flags, int stepped,
+                                                                 double mx, double my,
+                                                                 long long bad) {
+    if (stepped && (threadIdx.x & 63) == 0) publish_speeds(*P, p, ctl, slot, mx, my, bad);
+    end_tile(*P, p, slot, ctl, flags);
 }
 
 // Wave speeds of the cell averages a stage-3 launch has just written for one
@@ -373,15 +485,15 @@ __device__ __forceinline__ void publish_tile_speeds(ProbDev& P, double mx, doubl
 // wave w reads a contiguous share of the rows (they come from the L2 the
 // march's stores went through, or from HBM), lane l column i0 + l, and
 // evaluates wave_speed exactly for each cell; the workgroup's maxima and
-// first non-admissible cell are folded into the problem's slots for the next
-// step.  out_u: the problem's u-bar planes of the state written; the march's
+// first non-admissible cell are left in LDS for the wave that ends the tile.
+// out_u: the problem's u-bar planes of the state written; the march's
 // stores must be visible (a barrier after them); s_mx, s_my, s_bad: LDS of
 // one entry per wave.  Not inlined: its FP64 division chains would otherwise
 // raise the register allocation of the whole march (and it stays within the
 // registers a call may use without saving any: no scratch).
 template <class TU, int FLUX, int K>
 __device__ __attribute__((noinline)) void gather_tile_speeds(const TU* out_u, uint32_t plane, int nx,
-                                                   int i0, int j0, int jend, ProbDev& P,
+                                                   int i0, int j0, int jend,
                                                    const Scheme& sch, double* s_mx, double* s_my,
                                                    long long* s_bad) {
     // the planes are global memory (global rather than flat loads) at
@@ -396,11 +508,6 @@ __device__ __attribute__((noinline)) void gather_tile_speeds(const TU* out_u, ui
     for (int k = 0; k < K; ++k) gp[k] = (GC*)uniform((uint64_t)out_u + (uint64_t)k * plane * sizeof(TU));
     const int lane = threadIdx.x & 63;
     const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    uint64_t seen_x = 0, seen_y = 0;
-    if (threadIdx.x == 0) {   // read early: the gather covers the latency
-        seen_x = peek_slot(&P.ax_next);
-        seen_y = peek_slot(&P.ay_next);
-    }
     const bool col = lane < STRIP_OUT && i0 + lane < nx;
     const int per = (jend - j0 + nw - 1) / nw;
     const int ra = j0 + w * per, rb = min(jend, ra + per);
@@ -430,85 +537,13 @@ __device__ __attribute__((noinline)) void gather_tile_speeds(const TU* out_u, ui
             }
         }
     }
-    publish_tile_speeds(P, mx, my, bad, seen_x, seen_y, s_mx, s_my, s_bad);
-}
-
-// ------------------------------------------------------------ step control --
-//
-// dt = min(CFL rule, t_end - t); the CFL rule is cfl*dx^e/alpha_x in 1D and
-// cfl/(alpha_x/dx^e + alpha_y/dy^e) in 2D (or the caller's step).  Nothing it
-// reads changes before the step's end, so every workgroup of a step can form
-// the same choice itself.
-struct StepChoice {
-    bool act;     // the problem takes this step
-    bool last;    // it lands on t_end
-    double dt;
-};
-__device__ __forceinline__ StepChoice choose_step(const ProbDev& P, const StepRule& r) {
-    const double rem = P.t_end - P.t;
-    double dtc = P.dt_in;
-    if (!r.use_dt_in) {
-        const double ax = as_double(P.ax_bits), ay = as_double(P.ay_bits);
-        dtc = r.dim == 1 ? r.cfl * P.dxe / ax : r.cfl / (ax / P.dxe + ay / P.dye);
-    }
-    StepChoice c;
-    c.act = P.t < P.t_end && !P.err && (!r.use_dt_in || dtc > 0.0);
-    c.last = c.act && !(dtc < rem);
-    c.dt = c.act ? (c.last ? rem : dtc) : 0.0;
-    return c;
-}
-
-// Ends a problem's step: t += dt (exactly t_end on the clipped last one), the
-// speeds and errors gathered from the new state become current.  Returns
-// whether it was to take the step; running: it is still short of t_end.
-// The gathered values are read past this XCD's L2 (other XCDs' atomics).
-__device__ __forceinline__ bool finish_problem(ProbDev& P, const StepRule& r, bool& running) {
-    if (r.choose) {
-        const StepChoice c = choose_step(P, r);
-        P.active = c.act;
-        P.last = c.last;
-        P.dt = c.dt;
-    }
-    const bool act = P.active;
-    // a problem whose intermediate stage was not admissible skipped its
-    // stages 2 and 3: its state and time stay those of U^n
-    if (act && !(P.err & ERR_STAGE_BAD)) {
-        P.t = P.last ? P.t_end : P.t + P.dt;
-        P.ax_bits = peek_slot(&P.ax_next);
-        P.ay_bits = peek_slot(&P.ay_next);
-        P.alpha_valid = 1;
-        P.err |= __hip_atomic_load(&P.err_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (r.flip) P.cur ^= 1;
-    }
-    P.ax_next = 0;
-    P.ay_next = 0;
-    P.err_next = 0;
-    running = P.t < P.t_end && !P.err;
-    return act;
-}
-
-// Ends the step of every problem of a launch in one wave or workgroup of n
-// threads (tid < n <= 64, or called by one wave): used by the last wave of a
-// launch over few problems.
-__device__ __forceinline__ void finish_step(ProbDev* probs, StepCtl* ctl, const StepRule& r,
-                                            int tid, int n) {
-    const int nprob = ctl->nprob;
-    int run = 0, any = 0;
-    for (int p = tid; p < nprob; p += n) {
-        bool running;
-        any |= finish_problem(probs[p], r, running);
-        run += running;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        run += __shfl_xor(run, o, 64);
-        any |= __shfl_xor(any, o, 64);
-    }
-    if (tid == 0) {
-        ctl->nactive = run;
-        ctl->step_active = any;
-        ctl->arrived = 0;
-        if (any) ctl->steps += 1;
+    mx = wave_max_d(mx);
+    my = wave_max_d(my);
+    if (__any(bad != LLONG_MAX)) bad = wave_min_ll(bad);
+    if (lane == 0) {
+        s_mx[w] = mx;
+        s_my[w] = my;
+        s_bad[w] = bad;
     }
 }
 

@@ -47,33 +47,51 @@ struct ProbDev {
     int32_t cur;       // state set (0 or 1) that holds the problem's state
 };
 
-// Global step control, resident in device memory.
+// How the last launch of a step ends it.  Its tiles bring their speed maxima
+// and then arrive; the last one of a problem ends the problem's step, the last
+// problem writes the step counters.  Atomics on one address take 11 ns each,
+// one after the other, so problems of more than SLOTS tiles spread maxima and
+// arrivals over SLOTS lines (8620 tiles, 1 million cells in 1D: 100 us a step
+// with one address, 57 us with 64), and batches their ends likewise.
+constexpr int SLOTS = 64;
+struct alignas(128) Slot {
+    uint64_t ax, ay;   // speed maxima (of a tile group)
+    int32_t arrived;   // tiles of the group, or problems of a group
+    int32_t run, any;  // problems of the group: still short of t_end; advanced
+};
+// Per problem: its tiles in the step list, its first slot (-1: the problem's
+// own ax_next, ay_next), tiles or full slots that have arrived.
+struct ProbEnd {
+    int32_t ntiles, slot0, arrived, pad;
+};
+// Global step control, resident in device memory.  Kernels get its address
+// alone: what they need only at a tile's end is then loaded there instead of
+// being held in scalar registers through the tile.
 struct StepCtl {
     double cfl;
-    int32_t use_dt_in;
     int32_t nprob;
     int32_t dim;
     int32_t nactive;   // problems still short of t_end after the last step
     int32_t step_active;  // some problem advanced in the current step
-    int32_t arrived;   // tiles or workgroups of the current launch that are done
-    int32_t sum_run;   // counts in the making (finish_kernel)
-    int32_t sum_any;
     int64_t steps;     // steps in which some problem advanced
+    ProbEnd* ends;     // per problem
+    Slot* slots;       // of the problems with more than SLOTS tiles
+    Slot* groups;      // SLOTS groups of problems and their total (batches)
 };
 
-// How a launch takes and ends a step of its problems.
-struct StepRule {
-    double cfl;
-    int32_t dim;
-    int32_t use_dt_in;  // the caller's step lengths (ProbDev::dt_in)
-    int32_t choose;     // the kernels choose dt themselves; else a dt kernel ran
-    int32_t flip;       // the new state is in the other state set
+// How a launch takes and ends a step of its problems (flags).
+enum StepFlags : int {
+    STEP_DT_IN = 1,    // the caller's step lengths (ProbDev::dt_in)
+    STEP_CHOOSE = 2,   // the kernels choose dt themselves; else a dt kernel ran
+    STEP_FLIP = 4      // the new state is in the other state set
 };
 
 // 2D tile: a strip of 64 loaded columns (60 output columns starting at i0)
-// marching through rows j0 .. j0+nrows-1.
+// marching through rows j0 .. j0+nrows-1; slot: its group of the problem's
+// tiles (number of the tile within the problem mod SLOTS).
 struct Tile2D {
-    int32_t prob, i0, j0, nrows;
+    int32_t prob, i0, j0;
+    int16_t nrows, slot;
 };
 
 // 1D tile: 254 output cells starting at c0.
@@ -121,17 +139,18 @@ struct StageArgs {
     const void* tiles;
     int32_t ntiles;
     int32_t tile_offset;
+    StepCtl* ctl;
+    int32_t flags;      // StepFlags
     Scheme sch;
 };
 
 struct Step1Args {
     StateBuf s[2];      // the state sets a step reads and writes, by ProbDev::cur
     ProbDev* probs;
-    StepCtl* ctl;
     const Tile1D* tiles;  // of step1d_cells * 64 - STEP1D_HALO cells
     int32_t ntiles;
-    int32_t finish;     // the launch's last wave ends the step
-    StepRule rule;
+    int32_t flags;      // StepFlags
+    StepCtl* ctl;
     Scheme sch;
 };
 
@@ -160,16 +179,10 @@ hipError_t launch_alpha(int prec, int flux, int dim, const void* u0, const void*
                         int grid, hipStream_t s);
 hipError_t launch_dt(ProbDev* probs, StepCtl* ctl, int nprob, int use_dt_in, int own_ctl,
                      hipStream_t s);
-hipError_t launch_finish(ProbDev* probs, StepCtl* ctl, int nprob, const StepRule& rule,
-                         hipStream_t s);
 // One whole 1D step; cells: cells per lane (step1d_cells).
 hipError_t launch_step1d(int prec, int flux, int cells, const Step1Args& a, int grid, hipStream_t s);
 // Cells per lane of the 1D step kernel for these problems.
 int step1d_cells(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg);
-// Whether the last wave of a step kernel ends the step (finish_step) instead
-// of a kernel of its own (5 us with the gap before it): every wave then
-// arrives at one counter, and one wave ends all problems, 64 at a time.
-inline int ends_own_step(int ntiles, int nprob) { return ntiles <= 1024 && nprob <= 64; }
 // Converts one problem's state between the boundary layout (double,
 // ext[((var*K + c)*ny + j)*nx + i]) and the internal planes of b0 or b1, the
 // one prob->cur names.

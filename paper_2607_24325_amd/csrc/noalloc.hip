@@ -21,6 +21,7 @@ static __device__ __align__(256) unsigned char scratch[HWENO_NOALLOC_SCRATCH_BYT
 // chunks of one problem into the scratch (per-problem order; results do not
 // depend on the order of the tiles).
 __global__ void noalloc_setup_kernel(ProbDev pd, StepCtl ctl, ProbDev* probs, StepCtl* dctl,
+                                     ProbEnd pe,
                                      int dim, int nseg, int out1d, void* tiles, int ntiles, Chunk* chunks,
                                      int nchunks) {
     const int tid = blockIdx.x * blockDim.x + threadIdx.x;
@@ -28,7 +29,10 @@ __global__ void noalloc_setup_kernel(ProbDev pd, StepCtl ctl, ProbDev* probs, St
     if (tid == 0) {
         *probs = pd;
         *dctl = ctl;
+        *ctl.ends = pe;
     }
+    if (pe.slot0 >= 0)
+        for (int k = tid; k < SLOTS; k += nth) ctl.slots[k] = Slot{};
     const int strips = (pd.nx + STRIP_OUT - 1) / STRIP_OUT;
     for (int t = tid; t < ntiles; t += nth) {
         if (dim == 1) {
@@ -36,7 +40,7 @@ __global__ void noalloc_setup_kernel(ProbDev pd, StepCtl ctl, ProbDev* probs, St
         } else {
             const int js = t / strips, is = t - js * strips;
             const int j0 = segment_row(js, nseg, pd.ny), j1 = segment_row(js + 1, nseg, pd.ny);
-            ((Tile2D*)tiles)[t] = Tile2D{0, is * STRIP_OUT, j0, j1 - j0};
+            ((Tile2D*)tiles)[t] = Tile2D{0, is * STRIP_OUT, j0, (int16_t)(j1 - j0), (int16_t)(t % SLOTS)};
         }
     }
     const int64_t nc = (int64_t)pd.nx * pd.ny;
@@ -137,12 +141,25 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
     }
     void* H = p; p += db;
     ProbDev* probs = (ProbDev*)p; p += up256(sizeof(ProbDev));
-    StepCtl* ctl = (StepCtl*)p; p += up256(sizeof(StepCtl));
+    StepCtl* ctl = (StepCtl*)p;
+    StepCtl sc{};
+    sc.ends = (ProbEnd*)(p + sizeof(StepCtl));
+    static_assert(sizeof(StepCtl) + sizeof(ProbEnd) <= 256, "one region holds both");
+    p += up256(sizeof(StepCtl));
     void* tiles = p; p += tb;
     Chunk* chunks = (Chunk*)p;
     if (cells1d) {   // two sets only: the longer tile list goes where the third would
         tiles = U[2].u;
         ntiles = tiles_1d(pr.nx, cells1d);
+    }
+    // slots for the speeds of many tiles: in the unused third set, or behind
+    // the lists where there is room (else every tile uses the table's own)
+    ProbEnd pe{ntiles, -1, 0, 0};
+    if (ntiles > SLOTS) {
+        if (cells1d) sc.slots = (Slot*)U[2].d;
+        else if (need + SLOTS * sizeof(Slot) <= HWENO_NOALLOC_SCRATCH_BYTES)
+            sc.slots = (Slot*)((char*)chunks + cb);
+        if (sc.slots) pe.slot0 = 0;
     }
 
     // Every value a launch reads is written here first: the table entry and
@@ -151,7 +168,6 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
     ProbDev pd = probdev_of(pr, *cfg, 0, 0);
     pd.t = t;
     pd.dt_in = dt_in;
-    StepCtl sc{};
     sc.cfl = cfg->cfl;
     sc.nprob = 1;
     sc.dim = dim;
@@ -159,30 +175,27 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
     const Scheme sch = scheme_of(pr, *cfg);
     const int sgrid = std::max(1, std::min(1024, (std::max(ntiles, nchunks) + 255) / 256));
     const int nseg = dim == 2 ? (pr.ny + rows - 1) / rows : 0;
-    noalloc_setup_kernel<<<sgrid, 256, 0, s>>>(pd, sc, probs, ctl, dim, nseg, out1d, tiles,
+    noalloc_setup_kernel<<<sgrid, 256, 0, s>>>(pd, sc, probs, ctl, pe, dim, nseg, out1d, tiles,
                                                ntiles,
                                                chunks, nchunks);
     NA_TRY(hipGetLastError());
     NA_TRY(launch_pack(prec, 1, const_cast<double*>(state_in), U[0], U[1], probs, 0, 0, K, nvar, ncell, s));
     NA_TRY(launch_alpha(prec, flux, dim, U[0].u, U[1].u, probs, chunks, nchunks, sch,
                         SEL_STALE, 0, s));
-    StepRule rule{cfg->cfl, dim, use_dt_in, 0, 0};
+    const int flags = (use_dt_in ? STEP_DT_IN : 0) | (cfg->alpha_stage ? 0 : STEP_CHOOSE);
     if (cells1d) {
-        rule.choose = rule.flip = 1;
         Step1Args a{};
         a.s[0] = U[0];
         a.s[1] = U[1];
         a.probs = probs;
-        a.ctl = ctl;
         a.tiles = (const Tile1D*)tiles;
         a.ntiles = ntiles;
-        a.finish = ends_own_step(ntiles, 1);
-        a.rule = rule;
+        a.flags = flags | STEP_FLIP;
+        a.ctl = ctl;
         a.sch = sch;
         NA_TRY(launch_step1d(prec, flux, cells1d, a, 0, s));
-        if (!a.finish) NA_TRY(launch_finish(probs, ctl, 1, rule, s));
     } else {
-        NA_TRY(launch_dt(probs, ctl, 1, use_dt_in, 1, s));
+        if (cfg->alpha_stage) NA_TRY(launch_dt(probs, ctl, 1, use_dt_in, 1, s));
         for (int mode = MODE_S1; mode <= MODE_S3; ++mode) {
             if (mode != MODE_S1 && cfg->alpha_stage) {
                 NA_TRY(launch_reset(probs, ctl, 1, SEL_ACTIVE, s));
@@ -199,11 +212,12 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
             a.tiles = tiles;
             a.ntiles = ntiles;
             a.tile_offset = 0;
+            a.flags = flags;
+            a.ctl = ctl;
             a.sch = sch;
             if (dim == 1) NA_TRY(launch_stage1d(prec, flux, mode, a, 0, s));
             else NA_TRY(launch_stage2d(prec, flux, cfg->gauss_q, mode, 0, a, 0, s));
         }
-        NA_TRY(launch_finish(probs, ctl, 1, rule, s));
     }
     NA_TRY(launch_pack(prec, 0, state_out, U[0], U[1], probs, 0, 0, K, nvar, ncell, s));
     if (dt_out || bad_out) {

@@ -156,6 +156,9 @@ template <int P, int K, int mode, bool CH> constexpr bool stage1d_late_rk() {
     return mode == MODE_S3 && P != P_F64 && !CH && K > 1;
 }
 
+// Group of a tile among its problem's tiles.
+__device__ __forceinline__ int c0_slot(int c0) { return (c0 / TILE1D_OUT) & (SLOTS - 1); }
+
 template <int P, int K, int FLUX, int mode, bool CH>
 __global__ void __launch_bounds__(256, (stage1d_min_blocks<P, mode, CH>())) stage1d_kernel(StageArgs a) {
     using TU = typename PrecT<P>::TU;
@@ -182,26 +185,27 @@ __global__ void __launch_bounds__(256, (stage1d_min_blocks<P, mode, CH>())) stag
 
     for (int tix = blockIdx.x; tix < a.ntiles; tix += gridDim.x) {
         const Tile1D tile = tiles[tix];
-        const ProbDev& P_ = a.probs[tile.prob];
-        // stages 2 and 3 skip a problem whose stage input was not admissible
-        // (per-stage speeds): its U^n stays as it is
-        if (mode != MODE_RHS &&
-            (!P_.active || (mode != MODE_S1 && (P_.err & ERR_STAGE_BAD))))
-            continue;
+        ProbDev& P_ = a.probs[tile.prob];
+        const int slot = c0_slot(tile.c0);
+        StepChoice step{};
+        if (mode != MODE_RHS) {
+            step = stage_step(P_, a.ctl, a.flags, mode);
+            if (!step.act) {
+                if (mode == MODE_S3 && tid < 64)
+                    publish_and_end(&P_, tile.prob, slot, a.ctl, a.flags, 0, 0.0, 0.0, LLONG_MAX);
+                continue;
+            }
+        }
         const int nx = P_.nx, bcx = P_.bc_x;
         const T dx = (T)P_.dx, inv_dx = (T)P_.inv_dx;
         const TA inv_dx_a = (TA)P_.inv_dx;
         const T alpha = (T)as_double(P_.ax_bits);
-        const double dt = P_.dt;
+        const double dt = step.dt;
         const int c0 = tile.c0;
         // problem-table fields are copied before any store: read after one,
         // they would be reloaded (possible aliasing) and waited for
         const int64_t off_u = P_.off_u, off_d = P_.off_d;
         const StateBuf in = mode == MODE_RHS && P_.cur ? a.in1 : a.in;
-        // stage 3: thread 0, which publishes the tile's speed maximum, reads
-        // the slot now (a lower bound of its final value; see publish_max)
-        uint64_t seen_x = 0;
-        if (mode == MODE_S3 && tid == 0) seen_x = peek_slot(&a.probs[tile.prob].ax_next);
 
         for (int k = tid; k < NL; k += 256) {
             const int src = bc_map(c0 - 2 + k, nx, bcx);
@@ -325,7 +329,7 @@ __global__ void __launch_bounds__(256, (stage1d_min_blocks<P, mode, CH>())) stag
             }
         }
         __syncthreads();   // LDS reuse by the next tile
-        if (mode == MODE_S3 && tid == 0) {
+        if (mode == MODE_S3 && tid < 64) {
             double mx = s_mx[0];
             long long bad = s_bad[0];
 #pragma unroll
@@ -333,7 +337,7 @@ __global__ void __launch_bounds__(256, (stage1d_min_blocks<P, mode, CH>())) stag
                 mx = fmax(mx, s_mx[w]);
                 bad = s_bad[w] < bad ? s_bad[w] : bad;
             }
-            publish_reduced(a.probs[tile.prob], mx, 0.0, bad, seen_x, 0);
+            publish_and_end(&P_, tile.prob, slot, a.ctl, a.flags, 1, mx, 0.0, bad);
         }
     }
 }

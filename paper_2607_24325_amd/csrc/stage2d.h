@@ -240,18 +240,23 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, Q, mode, V>()))
     for (int tix = blockIdx.x; tix < a.ntiles; tix += gridDim.x) {
         const Tile2D tile = tiles[tix];
         const ProbDev& P_ = a.probs[tile.prob];
-        // stages 2 and 3 skip a problem whose stage input was not admissible
-        // (per-stage speeds): its U^n stays as it is
-        if (mode != MODE_RHS &&
-            (!P_.active || (mode != MODE_S1 && (P_.err & ERR_STAGE_BAD))))
-            continue;
+        StepChoice step{};
+        if (mode != MODE_RHS) {
+            step = stage_step(P_, a.ctl, a.flags, mode);
+            if (!step.act) {
+                if (mode == MODE_S3 && threadIdx.x < 64)
+                    publish_and_end(&a.probs[tile.prob], tile.prob, tile.slot, a.ctl, a.flags, 0,
+                                    0.0, 0.0, LLONG_MAX);
+                continue;
+            }
+        }
         const int nx = P_.nx, ny = P_.ny, bcx = P_.bc_x, bcy = P_.bc_y;
         const int64_t plane = (int64_t)nx * ny;
         const T inv_dx = (T)P_.inv_dx, inv_dy = (T)P_.inv_dy;
         const TA inv_dx_a = (TA)P_.inv_dx, inv_dy_a = (TA)P_.inv_dy;
         const T rx = (T)(P_.dx * P_.inv_dy), ry = (T)(P_.dy * P_.inv_dx);
         const T ax = (T)as_double(P_.ax_bits), ay = (T)as_double(P_.ay_bits);
-        const double dt = P_.dt;
+        const double dt = step.dt;
         const int gi = tile.i0 - 2 + lane;          // this lane's column
         const int li = bc_map(gi, nx, bcx);         // column it reads
         const bool out_col = lane >= 2 && lane < 62 && gi < nx;
@@ -596,9 +601,25 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, Q, mode, V>()))
             wm = w0; w0 = wp; wp = wn_;
         }
         __syncthreads();  // LDS reuse by the next tile; the tile's stores are visible
-        if (fuse_alpha)
+        if (fuse_alpha) {
             gather_tile_speeds<TU, FLUX, K>((const TU*)a.out.u + off_u, (uint32_t)plane, nx, tile.i0,
-                                            j0, jend, a.probs[tile.prob], sch, smx, smy, sbad);
+                                            j0, jend, sch, smx, smy, sbad);
+            __syncthreads();
+            if (threadIdx.x < 64) {
+                // the tile is read again rather than held through the march
+                const volatile Tile2D* t = &tiles[tix];
+                const int prob = t->prob, slot = t->slot;
+                double mx = smx[0], my = smy[0];
+                long long bad = sbad[0];
+#pragma unroll
+                for (int v = 1; v < K; ++v) {
+                    mx = fmax(mx, smx[v]);
+                    my = fmax(my, smy[v]);
+                    bad = sbad[v] < bad ? sbad[v] : bad;
+                }
+                publish_and_end(&a.probs[prob], prob, slot, a.ctl, a.flags, 1, mx, my, bad);
+            }
+        }
     }
 }
 

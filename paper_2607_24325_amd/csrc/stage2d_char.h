@@ -68,18 +68,23 @@ __global__ void __launch_bounds__(256, (P == P_F64 ? 1 : 2)) stage2d_char_kernel
     for (int tix = blockIdx.x; tix < a.ntiles; tix += gridDim.x) {
         const Tile2D tile = tiles[tix];
         const ProbDev& P_ = a.probs[tile.prob];
-        // stages 2 and 3 skip a problem whose stage input was not admissible
-        // (per-stage speeds): its U^n stays as it is
-        if (mode != MODE_RHS &&
-            (!P_.active || (mode != MODE_S1 && (P_.err & ERR_STAGE_BAD))))
-            continue;
+        StepChoice step{};
+        if (mode != MODE_RHS) {
+            step = stage_step(P_, a.ctl, a.flags, mode);
+            if (!step.act) {
+                if (mode == MODE_S3 && c == 0)
+                    publish_and_end(&a.probs[tile.prob], tile.prob, tile.slot, a.ctl, a.flags, 0,
+                                    0.0, 0.0, LLONG_MAX);
+                continue;
+            }
+        }
         const int nx = P_.nx, ny = P_.ny, bcx = P_.bc_x, bcy = P_.bc_y;
         const int64_t plane = (int64_t)nx * ny;
         const T inv_dx = (T)P_.inv_dx, inv_dy = (T)P_.inv_dy;
         const TA inv_dx_a = (TA)P_.inv_dx, inv_dy_a = (TA)P_.inv_dy;
         const T rx = (T)(P_.dx * P_.inv_dy), ry = (T)(P_.dy * P_.inv_dx);
         const T ax = (T)as_double(P_.ax_bits), ay = (T)as_double(P_.ay_bits);
-        const double dt = P_.dt;
+        const double dt = step.dt;
         const int gi = tile.i0 - 2 + lane;
         const int li = bc_map(gi, nx, bcx);
         const bool out_col = lane >= 2 && lane < 62 && gi < nx;
@@ -430,13 +435,13 @@ __global__ void __launch_bounds__(256, (P == P_F64 ? 1 : 2)) stage2d_char_kernel
             gather_speeds(jend - 1, pw);
             if (c == pw) {
                 ProbDev& Pw = a.probs[tile.prob];
-                const uint64_t seen_x = peek_slot(&Pw.ax_next), seen_y = peek_slot(&Pw.ay_next);
-                const double mxl = smx[lane], myl = smy[lane];
-                const long long badl = sbad[lane];
+                const double mxl = wave_max_d(smx[lane]), myl = wave_max_d(smy[lane]);
+                long long badl = sbad[lane];
+                if (__any(badl != LLONG_MAX)) badl = wave_min_ll(badl);
                 smx[lane] = 0.0;
                 smy[lane] = 0.0;
                 sbad[lane] = LLONG_MAX;
-                publish_next_speeds(Pw, mxl, myl, badl, seen_x, seen_y);
+                publish_and_end(&Pw, tile.prob, tile.slot, a.ctl, a.flags, 1, mxl, myl, badl);
             }
         }
     }

@@ -46,7 +46,8 @@ __global__ void __launch_bounds__(64) step1d_kernel(Step1Args a) {
     for (int tix = blockIdx.x; tix < a.ntiles; tix += gridDim.x) {
         const Tile1D tile = a.tiles[tix];
         ProbDev& P_ = a.probs[tile.prob];
-        const StepChoice step = choose_step(P_, a.rule);
+        const int slot = (tile.c0 / OUT) & (SLOTS - 1);
+        const StepChoice step = choose_step(P_, a.ctl, a.flags);
         if (step.act) {
             const int nx = P_.nx, bcx = P_.bc_x, cur = P_.cur;
             const T dx = (T)P_.dx, inv_dx = (T)P_.inv_dx;
@@ -59,8 +60,6 @@ __global__ void __launch_bounds__(64) step1d_kernel(Step1Args a) {
             const TD* Iv = (const TD*)(cur ? a.s[1].d : a.s[0].d) + off_d;
             TU* Ou = (TU*)(cur ? a.s[0].u : a.s[1].u) + off_u;
             TD* Ov = (TD*)(cur ? a.s[0].d : a.s[1].d) + off_d;
-            uint64_t seen_x = 0;
-            if (lane == 0) seen_x = peek_slot(&P_.ax_next);
             const int g0 = tile.c0 - 6;              // first cell of the wave
             // images of a periodic domain evolve as the cells they repeat;
             // other ghost cells are set anew from the interior in every stage
@@ -228,18 +227,11 @@ __global__ void __launch_bounds__(64) step1d_kernel(Step1Args a) {
                     else bad = g < bad ? g : bad;
                 }
             }
-            publish_next_speeds(P_, mx, 0.0, bad, seen_x, 0);
+            mx = wave_max_d(mx);
+            if (__any(bad != LLONG_MAX)) bad = wave_min_ll(bad);
+            if (lane == 0) publish_speeds(P_, tile.prob, a.ctl, slot, mx, 0.0, bad);
         }
-        if (a.finish) {
-            // the last wave to get here ends the step: its own and, before
-            // their arrivals, all others' speeds have reached memory
-            int last = 0;
-            if (lane == 0) {
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                last = atomicAdd(&a.ctl->arrived, 1) == a.ntiles - 1;
-            }
-            if (__builtin_amdgcn_readfirstlane(last)) finish_step(a.probs, a.ctl, a.rule, lane, 64);
-        }
+        end_tile(P_, tile.prob, slot, a.ctl, a.flags);
     }
 }
 
