@@ -42,6 +42,7 @@ struct hweno_handle {
     size_t tiles_cap = 0;           // capacity in tiles
     int ntiles_step = 0;
     int cells1d = 0;                // 1D: cells per lane of the step kernel; 0: stage by stage
+    int waves1d = 0;                // 1D: waves of the run kernel's workgroups; 0: not used
     std::vector<int> tile_begin, tile_count;  // per problem, in the per-problem list
     Chunk* d_chunks = nullptr;
     int nchunks = 0;
@@ -513,6 +514,7 @@ static int setup(hweno_handle* h, const hweno_problem* probs, int32_t nprob,
     h->tun.source = HWENO_TUNED_DEFAULT;
     // speeds of every stage need a reduction between the stages
     if (h->dim == 1 && !cfg->alpha_stage) h->cells1d = step1d_cells(probs, nprob, *cfg);
+    if (h->dim == 1) h->waves1d = run1d_waves(probs, nprob, *cfg);
     return build_tiles(h);
 }
 
@@ -721,6 +723,20 @@ extern "C" int hweno_rhs(hweno_handle* h, int32_t prob, double* L_out, double* U
 // (and may bracket it with events).
 enum LaunchKind { LK_OTHER = 0, LK_ALPHA = 1, LK_STAGE = 2, LK_STEP = 3 };  // LK_STEP: three stages
 
+// n steps of problems that fit one workgroup each, in one launch.
+static hipError_t launch_run(hweno_handle* h, int n, int flags) {
+    Run1Args a{};
+    a.s[0] = h->U[0];
+    a.s[1] = h->U[1];
+    a.probs = h->d_probs;
+    a.ctl = h->d_ctl;
+    a.cfl = h->cfg.cfl;
+    a.nsteps = n;
+    a.flags = flags;
+    a.sch = h->sch;
+    return launch_run1d(h->prec, h->flux, h->waves1d, h->nprob, a, h->stream);
+}
+
 // One step.  fast: no problem that can advance has stale speeds, so the
 // reduction kernel is left out (and with at most 256 problems the dt kernel
 // clears the step counters itself, which leaves out the reset kernel too).
@@ -730,6 +746,10 @@ static int enqueue_step_with(hweno_handle* h, int use_dt_in, bool fast, Rec&& re
     // the stages take it from the table; else each launch chooses it itself
     const bool choose = !h->cfg.alpha_stage;
     const int flags = (use_dt_in ? STEP_DT_IN : 0) | (choose ? STEP_CHOOSE : 0);
+    if (h->waves1d) {
+        HIP_TRY(h, rec(LK_STEP, [&] { return launch_run(h, 1, flags); }));
+        return HWENO_OK;
+    }
     const int own_ctl = fast && (choose || h->nprob <= 256);
     // speeds are gathered by stage 3 of the previous step; the reduction
     // kernel only fills them in after set_state
@@ -784,7 +804,7 @@ static int enqueue_step(hweno_handle* h, int use_dt_in, bool fast) {
 
 static int launch_step(hweno_handle* h) {
     const bool fast = h->speeds_fresh != 0;
-    if (!h->tun.use_graph) return enqueue_step(h, 0, fast);
+    if (!h->tun.use_graph || h->waves1d) return enqueue_step(h, 0, fast);
     hipGraphExec_t& exec = fast ? h->graph_fast : h->graph;
     hipGraph_t& def = fast ? h->graph_fast_def : h->graph_def;
     if (!exec) {
@@ -833,6 +853,13 @@ static int capture_multi(hweno_handle* h) {
 static int launch_steps(hweno_handle* h, int64_t n) {
     int64_t done = 0;
     int rc = HWENO_OK;
+    if (h->waves1d) {   // at most this many steps a launch (some 20 ms)
+        constexpr int64_t MOST = 4096;
+        for (; done < n; done += MOST)
+            HIP_TRY(h, launch_run(h, (int)std::min(MOST, n - done), STEP_CHOOSE));
+        if (n > 0) h->speeds_fresh = 1;
+        return rc;
+    }
     if (!h->tun.use_graph) {
         for (; done < n && rc == HWENO_OK; ++done) rc = launch_step(h);
         return rc;
@@ -901,14 +928,14 @@ extern "C" int hweno_run_to_time(hweno_handle* h, int64_t* steps_out) {
     HIP_TRY(h, hipMemcpyAsync(&ctl, h->d_ctl, sizeof ctl, hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
     const int64_t steps0 = ctl.steps;
-    int batch = 4;
+    int batch = h->waves1d ? 1024 : 4;
     for (;;) {
         rc = launch_steps(h, batch);
         if (rc) return rc;
         HIP_TRY(h, hipMemcpyAsync(&ctl, h->d_ctl, sizeof ctl, hipMemcpyDeviceToHost, h->stream));
         HIP_TRY(h, hipStreamSynchronize(h->stream));
         if (ctl.nactive == 0) break;
-        batch = std::min(batch * 2, 64);
+        batch = std::min(batch * 2, h->waves1d ? 4096 : 64);
     }
     if (steps_out) *steps_out = ctl.steps - steps0;
     return hweno_sync(h);

@@ -345,18 +345,22 @@ struct StepChoice {
     bool last;    // it lands on t_end
     double dt;
 };
-__device__ __forceinline__ StepChoice choose_step(const ProbDev& P, const StepCtl* ctl, int flags) {
+__device__ __forceinline__ StepChoice choose_step(const ProbDev& P, double cfl, int dim, int flags) {
     const double rem = P.t_end - P.t;
     double dtc = P.dt_in;
     if (!(flags & STEP_DT_IN)) {
         const double ax = as_double(P.ax_bits), ay = as_double(P.ay_bits);
-        dtc = ctl->dim == 1 ? ctl->cfl * P.dxe / ax : ctl->cfl / (ax / P.dxe + ay / P.dye);
+        dtc = dim == 1 ? cfl * P.dxe / ax : cfl / (ax / P.dxe + ay / P.dye);
     }
     StepChoice c;
     c.act = P.t < P.t_end && !P.err && (!(flags & STEP_DT_IN) || dtc > 0.0);
     c.last = c.act && !(dtc < rem);
     c.dt = c.act ? (c.last ? rem : dtc) : 0.0;
     return c;
+}
+
+__device__ __forceinline__ StepChoice choose_step(const ProbDev& P, const StepCtl* ctl, int flags) {
+    return choose_step(P, ctl->cfl, ctl->dim, flags);
 }
 
 // The same for a stage kernel, which takes the choice of a dt kernel where one
@@ -411,6 +415,34 @@ __device__ __forceinline__ bool finish_problem(ProbDev& P, const StepCtl* ctl, i
 // Waits until this wave's atomics have been performed.
 __device__ __forceinline__ void wait_atomics() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// Counts a problem whose step (or steps, for a launch that takes several)
+// ended; the launch's last problem writes the step counters.  One lane.
+__device__ __forceinline__ void end_problem(int p, int run, int steps, StepCtl* ctl) {
+    const int nprob = ctl->nprob;
+    if (nprob > 1) {
+        // the group's counts reach memory before the group arrives
+        Slot& g = ctl->groups[p & (SLOTS - 1)];
+        if (run) atomicAdd(&g.run, run);
+        if (steps) atomicMax(&g.steps, steps);
+        wait_atomics();
+        if (atomicAdd(&g.arrived, 1) != (nprob - (p & (SLOTS - 1)) - 1) / SLOTS) return;
+        Slot& all = ctl->groups[SLOTS];
+        run = __hip_atomic_load(&g.run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        steps = __hip_atomic_load(&g.steps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        g.run = g.steps = g.arrived = 0;
+        if (run) atomicAdd(&all.run, run);
+        if (steps) atomicMax(&all.steps, steps);
+        wait_atomics();
+        if (atomicAdd(&all.arrived, 1) != (nprob < SLOTS ? nprob : SLOTS) - 1) return;
+        run = __hip_atomic_load(&all.run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        steps = __hip_atomic_load(&all.steps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        all.run = all.steps = all.arrived = 0;
+    }
+    ctl->nactive = run;
+    ctl->step_active = steps != 0;
+    ctl->steps += steps;
+}
+
 // Arrival of a finished tile (group `slot`) of problem p, by the wave that
 // published its speeds: every lane calls it.  The problem's last tile ends its
 // step, the launch's last problem writes the step counters.
@@ -442,30 +474,8 @@ __device__ __forceinline__ void end_tile(ProbDev& P, int p, int slot, StepCtl* c
     if (lane != 0) return;
     pe.arrived = 0;
     bool running;
-    int any = finish_problem(P, ctl, flags, ax, ay, running), run = running;
-    const int nprob = ctl->nprob;
-    if (nprob > 1) {
-        // the group's counts reach memory before the group arrives
-        Slot& g = ctl->groups[p & (SLOTS - 1)];
-        if (run) atomicAdd(&g.run, run);
-        if (any) atomicOr(&g.any, any);
-        wait_atomics();
-        if (atomicAdd(&g.arrived, 1) != (nprob - (p & (SLOTS - 1)) - 1) / SLOTS) return;
-        Slot& all = ctl->groups[SLOTS];
-        run = __hip_atomic_load(&g.run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        any = __hip_atomic_load(&g.any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        g.run = g.any = g.arrived = 0;
-        if (run) atomicAdd(&all.run, run);
-        if (any) atomicOr(&all.any, any);
-        wait_atomics();
-        if (atomicAdd(&all.arrived, 1) != (nprob < SLOTS ? nprob : SLOTS) - 1) return;
-        run = __hip_atomic_load(&all.run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        any = __hip_atomic_load(&all.any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        all.run = all.any = all.arrived = 0;
-    }
-    ctl->nactive = run;
-    ctl->step_active = any;
-    if (any) ctl->steps += 1;
+    const int steps = finish_problem(P, ctl, flags, ax, ay, running);
+    end_problem(p, running, steps, ctl);
 }
 
 // publish_speeds by the wave's first lane (when a tile stepped), then

@@ -57,7 +57,7 @@ constexpr int SLOTS = 64;
 struct alignas(128) Slot {
     uint64_t ax, ay;   // speed maxima (of a tile group)
     int32_t arrived;   // tiles of the group, or problems of a group
-    int32_t run, any;  // problems of the group: still short of t_end; advanced
+    int32_t run, steps;  // problems of the group still short of t_end; most steps taken
 };
 // Per problem: its tiles in the step list, its first slot (-1: the problem's
 // own ax_next, ay_next), tiles or full slots that have arrived.
@@ -154,6 +154,24 @@ struct Step1Args {
     Scheme sch;
 };
 
+// Steps of problems that fit one workgroup each (run1d.h).
+constexpr int RUN1D_WAVES = 8;
+struct Run1Args {
+    StateBuf s[2];
+    ProbDev* probs;
+    StepCtl* ctl;
+    double cfl;
+    int32_t nsteps;
+    int32_t flags;      // StepFlags
+    // one problem on the caller's arrays in the boundary layout instead
+    const double* ext_in;
+    double* ext_out;
+    double* dt_out;
+    int64_t* bad_out;
+    ProbDev prob;
+    Scheme sch;
+};
+
 // --- launchers (defined in the .hip files) ------------------------------
 hipError_t launch_stage1d(int prec, int flux, int mode, const StageArgs& a, int grid,
                           hipStream_t s);
@@ -181,6 +199,11 @@ hipError_t launch_dt(ProbDev* probs, StepCtl* ctl, int nprob, int use_dt_in, int
                      hipStream_t s);
 // One whole 1D step; cells: cells per lane (step1d_cells).
 hipError_t launch_step1d(int prec, int flux, int cells, const Step1Args& a, int grid, hipStream_t s);
+// Steps of nprob problems of at most `waves` waves each.
+hipError_t launch_run1d(int prec, int flux, int waves, int nprob, const Run1Args& a, hipStream_t s);
+// Waves that hold the largest of these 1D problems in one workgroup; 0 where
+// it does not fit.
+int run1d_waves(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg);
 // Cells per lane of the 1D step kernel for these problems.
 int step1d_cells(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg);
 // Converts one problem's state between the boundary layout (double,

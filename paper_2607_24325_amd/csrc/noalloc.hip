@@ -130,10 +130,29 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
                             "problem of %lld cells needs %zu bytes of scratch; the allocation-free "
                             "step has %zu (use a handle for larger problems)",
                             (long long)ncell, need, (size_t)HWENO_NOALLOC_SCRATCH_BYTES);
+    hipStream_t s = (hipStream_t)hip_stream;
+    const int use_dt_in = dt_in > 0.0;
+    const int flags = (use_dt_in ? STEP_DT_IN : 0) | (cfg->alpha_stage ? 0 : STEP_CHOOSE);
+    if (const int waves = dim == 1 ? run1d_waves(prob, 1, *cfg) : 0) {
+        // one launch, straight on the caller's arrays (the scratch is not used)
+        Run1Args a{};
+        a.cfl = cfg->cfl;
+        a.nsteps = 1;
+        a.flags = flags;
+        a.ext_in = state_in;
+        a.ext_out = state_out;
+        a.dt_out = dt_out;
+        a.bad_out = bad_out;
+        a.prob = probdev_of(pr, *cfg, 0, 0);
+        a.prob.t = t;
+        a.prob.dt_in = dt_in;
+        a.sch = scheme_of(pr, *cfg);
+        NA_TRY(launch_run1d(prec, flux, waves, 1, a, s));
+        return HWENO_OK;
+    }
     char* p = nullptr;
     rc = scratch_address(&p);
     if (rc) return rc;
-    hipStream_t s = (hipStream_t)hip_stream;
     StateBuf U[3];
     for (int k = 0; k < 3; ++k) {
         U[k].u = p; p += ub;
@@ -171,18 +190,15 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
     sc.cfl = cfg->cfl;
     sc.nprob = 1;
     sc.dim = dim;
-    const int use_dt_in = dt_in > 0.0;
     const Scheme sch = scheme_of(pr, *cfg);
     const int sgrid = std::max(1, std::min(1024, (std::max(ntiles, nchunks) + 255) / 256));
     const int nseg = dim == 2 ? (pr.ny + rows - 1) / rows : 0;
     noalloc_setup_kernel<<<sgrid, 256, 0, s>>>(pd, sc, probs, ctl, pe, dim, nseg, out1d, tiles,
-                                               ntiles,
-                                               chunks, nchunks);
+                                               ntiles, chunks, nchunks);
     NA_TRY(hipGetLastError());
     NA_TRY(launch_pack(prec, 1, const_cast<double*>(state_in), U[0], U[1], probs, 0, 0, K, nvar, ncell, s));
     NA_TRY(launch_alpha(prec, flux, dim, U[0].u, U[1].u, probs, chunks, nchunks, sch,
                         SEL_STALE, 0, s));
-    const int flags = (use_dt_in ? STEP_DT_IN : 0) | (cfg->alpha_stage ? 0 : STEP_CHOOSE);
     if (cells1d) {
         Step1Args a{};
         a.s[0] = U[0];

@@ -1,4 +1,5 @@
-// Launcher of the 1D step kernel (instantiations live in step1d_<mode>.hip).
+// Launchers of the 1D step and run kernels (instantiations live in
+// step1d_<mode>.hip) and the rules that choose between them.
 #include "internal.h"
 
 namespace hweno {
@@ -8,15 +9,40 @@ hipError_t launch_step1d_f32(int flux, int cells, const Step1Args& a, int grid, 
 hipError_t launch_step1d_acc64(int flux, int cells, const Step1Args& a, int grid, hipStream_t s);
 hipError_t launch_step1d_kahan(int flux, int cells, const Step1Args& a, int grid, hipStream_t s);
 
+hipError_t launch_run1d_f64(int flux, int waves, int nprob, const Run1Args& a, hipStream_t s);
+hipError_t launch_run1d_f32(int flux, int waves, int nprob, const Run1Args& a, hipStream_t s);
+hipError_t launch_run1d_acc64(int flux, int waves, int nprob, const Run1Args& a, hipStream_t s);
+hipError_t launch_run1d_kahan(int flux, int waves, int nprob, const Run1Args& a, hipStream_t s);
+
 // One cell per lane while the waves leave most of the GPU idle: the three
 // stages are one serial chain, 3.5 us for one cell of a lane and 3 us more for
-// a second (a step of 4000 cells, F64: 10.9 us with one, 13.9 with two); from
-// some 30 000 cells the halo of 12 in 64 costs more than it (50 000 cells:
-// 21.5 against 18.7 us, 4 million: 302 against 265).
+// a second (a step of 4000 cells, F64: 10.9 us with one, 14.3 with two); from
+// some 130 000 cells the halo of 12 in 64 costs more than it (100 000 cells:
+// 16.4 against 16.5 us, 200 000: 24.4 against 23.3, 4 million: 300 against 252).
 int step1d_cells(const hweno_problem* probs, int32_t nprob, const hweno_config&) {
     int64_t waves = 0;
     for (int p = 0; p < nprob; ++p) waves += tiles_1d(probs[p].nx, 1);
-    return waves <= 600 ? 1 : 2;
+    return waves <= 2500 ? 1 : 2;
+}
+
+int run1d_waves(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg) {
+    if (cfg.alpha_stage) return 0;
+    int most = 0;
+    for (int p = 0; p < nprob; ++p) {
+        const int w = tiles_1d(probs[p].nx, 1);
+        most = w > most ? w : most;
+    }
+    return most <= RUN1D_WAVES ? most : 0;
+}
+
+hipError_t launch_run1d(int prec, int flux, int waves, int nprob, const Run1Args& a,
+                        hipStream_t s) {
+    if (waves < 1 || waves > RUN1D_WAVES || nprob < 1) return hipErrorInvalidValue;
+    if (prec == P_F64) return launch_run1d_f64(flux, waves, nprob, a, s);
+    if (prec == P_F32) return launch_run1d_f32(flux, waves, nprob, a, s);
+    if (prec == P_ACC64) return launch_run1d_acc64(flux, waves, nprob, a, s);
+    if (prec == P_KAHAN) return launch_run1d_kahan(flux, waves, nprob, a, s);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_step1d(int prec, int flux, int cells, const Step1Args& a, int grid,

@@ -1,10 +1,14 @@
-// Instantiations of the 1D step kernel for the P_ACC64 arithmetic mode.
-#include "step1d.h"
+// Instantiations of the 1D step and run kernels for the P_ACC64 arithmetic mode.
+#include "run1d.h"
 
 namespace hweno {
 
 hipError_t launch_step1d_acc64(int flux, int cells, const Step1Args& a, int grid, hipStream_t s) {
     return step1d_launch_prec<P_ACC64>(flux, cells, a, grid, s);
+}
+
+hipError_t launch_run1d_acc64(int flux, int waves, int nprob, const Run1Args& a, hipStream_t s) {
+    return run1d_launch_prec<P_ACC64>(flux, waves, nprob, a, s);
 }
 
 }  // namespace hweno
