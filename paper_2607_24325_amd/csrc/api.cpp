@@ -24,6 +24,7 @@ struct hweno_handle {
     std::vector<hweno_problem> probs;
     int nprob = 0, dim = 1, flux = 0, K = 1, D = 1, nvar = 2, prec = 0;
     size_t su = 8, sd = 8;  // bytes per stored average / derivative value
+    int device = 0;
     hipStream_t stream = nullptr;
     bool own_stream = false;
     char* ws = nullptr;
@@ -48,6 +49,7 @@ struct hweno_handle {
     int nchunks = 0;
     double* d_stage = nullptr;      // staging for set/get_state and rhs (double)
     size_t stage_elems = 0;
+    ProbStatus* status = nullptr;   // pinned host memory the device writes
     std::vector<char> state_set;
     // Step graphs: the full step, and the step without the reduction of
     // stale wave speeds.  Speeds go stale only through set_state; after one
@@ -438,6 +440,7 @@ static int setup(hweno_handle* h, const hweno_problem* probs, int32_t nprob,
     h->prec = cfg->precision;
     prec_sizes(h->prec, &h->su, &h->sd);
     const Layout L = layout_of(probs, nprob, cfg);
+    HIP_TRY(h, hipGetDevice(&h->device));
     if (stream) {
         h->stream = (hipStream_t)stream;
     } else {
@@ -456,6 +459,7 @@ static int setup(hweno_handle* h, const hweno_problem* probs, int32_t nprob,
         h->own_ws = true;
     }
     h->ws_bytes = L.total;
+    HIP_TRY(h, hipHostMalloc((void**)&h->status, sizeof(ProbStatus), hipHostMallocDefault));
     char* p = h->ws;
     for (int s = 0; s < 3; ++s) {
         h->U[s].u = p; p += L.u_bytes;
@@ -541,6 +545,7 @@ extern "C" int hweno_destroy(hweno_handle* h) {
     if (h->stream) (void)hipStreamSynchronize(h->stream);
     drop_graph(h);
     if (h->own_ws && h->ws) (void)hipFree(h->ws);
+    if (h->status) (void)hipHostFree(h->status);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
     delete h;
     return HWENO_OK;
@@ -560,19 +565,43 @@ static int read_probs(hweno_handle* h, std::vector<ProbDev>& v) {
     return HWENO_OK;
 }
 
-static int report_errors(hweno_handle* h, const std::vector<ProbDev>& v, int only = -1) {
-    for (int p = 0; p < h->nprob; ++p) {
-        if (only >= 0 && p != only) continue;
-        if (v[p].err) {
-            const int64_t c = v[p].bad_cell;
-            const int nx = v[p].nx;
-            return fail(h, HWENO_ERR_NONFINITE,
-                        "problem %d: non-admissible state (non-finite, or rho <= 0 / p <= 0) "
-                        "at cell i=%lld j=%lld, t=%.17g",
-                        p, (long long)(c % nx), (long long)(c / nx), v[p].t);
-        }
-    }
+static int bad_state(hweno_handle* h, int p, int64_t c, int nx, double t) {
+    return fail(h, HWENO_ERR_NONFINITE,
+                "problem %d: non-admissible state (non-finite, or rho <= 0 / p <= 0) "
+                "at cell i=%lld j=%lld, t=%.17g",
+                p, (long long)(c % nx), (long long)(c / nx), t);
+}
+
+static int report_errors(hweno_handle* h, const std::vector<ProbDev>& v) {
+    for (int p = 0; p < h->nprob; ++p)
+        if (v[p].err) return bad_state(h, p, v[p].bad_cell, v[p].nx, v[p].t);
     return HWENO_OK;
+}
+
+// The same of the one problem whose status the device has written.
+static int report_status(hweno_handle* h, int prob) {
+    const ProbStatus& s = *h->status;
+    return s.err ? bad_state(h, prob, s.bad_cell, s.nx, s.t) : HWENO_OK;
+}
+
+// Whether kernels of the handle can use a caller's "device" array as it is:
+// memory of this GPU, aligned to its elements (a copy also takes another GPU's
+// memory, mapped host memory and odd addresses).
+static bool kernel_can_use(const hweno_handle* h, const void* p) {
+    if ((uintptr_t)p % sizeof(double)) return false;
+    hipPointerAttribute_t at{};
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();   // the copy that follows reports it
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == h->device;
+}
+
+static hipError_t pack_state(hweno_handle* h, int prob, const double* src, double* dst,
+                             const PackOp& op) {
+    return launch_pack(h->prec, src, dst, h->U[0], h->U[1], h->d_probs + prob,
+                       h->h_probs[prob].off_u, h->h_probs[prob].off_d, h->K, h->nvar,
+                       h->ncell[prob], op, h->stream);
 }
 
 static int check_prob(hweno_handle* h, int32_t prob) {
@@ -587,22 +616,17 @@ extern "C" int hweno_set_state(hweno_handle* h, int32_t prob, const double* src,
     int rc = check_prob(h, prob);
     if (rc) return rc;
     if (!src) return fail(h, HWENO_ERR_ARG, "src is NULL");
-    const int64_t n = (int64_t)h->nvar * h->K * h->ncell[prob];
-    HIP_TRY(h, hipMemcpyAsync(h->d_stage, src, sizeof(double) * n,
-                              src_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
-                              h->stream));
-    HIP_TRY(h, launch_pack(h->prec, 1, h->d_stage, h->U[0], h->U[1], h->d_probs + prob, h->h_probs[prob].off_u,
-                           h->h_probs[prob].off_d, h->K, h->nvar, h->ncell[prob], h->stream));
-    ProbDev d;
-    HIP_TRY(h, hipMemcpyAsync(&d, h->d_probs + prob, sizeof d, hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(h, hipStreamSynchronize(h->stream));
-    d.t = t;
-    d.err = 0;
-    d.err_next = 0;
-    d.bad_cell = INT64_MAX;
-    d.active = 0;
-    d.alpha_valid = 0;
-    HIP_TRY(h, hipMemcpyAsync(h->d_probs + prob, &d, sizeof d, hipMemcpyHostToDevice, h->stream));
+    // this GPU's data are converted where they lie, others through the staging
+    // area; the same launch makes the table entry that of a new state
+    const double* dsrc = src;
+    if (!src_on_device || !kernel_can_use(h, src)) {
+        const int64_t n = (int64_t)h->nvar * h->K * h->ncell[prob];
+        HIP_TRY(h, hipMemcpyAsync(h->d_stage, src, sizeof(double) * n,
+                                  src_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
+                                  h->stream));
+        dsrc = h->d_stage;
+    }
+    HIP_TRY(h, pack_state(h, prob, dsrc, nullptr, PackOp{t, 1, 0, nullptr}));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
     h->state_set[prob] = 1;
     h->speeds_fresh = 0;
@@ -614,21 +638,22 @@ extern "C" int hweno_get_state(hweno_handle* h, int32_t prob, double* dst,
     int rc = check_prob(h, prob);
     if (rc) return rc;
     if (!h->state_set[prob]) return fail(h, HWENO_ERR_STATE, "problem %d has no state yet", prob);
-    const int64_t n = (int64_t)h->nvar * h->K * h->ncell[prob];
-    std::vector<ProbDev> v(h->nprob);
-    HIP_TRY(h, hipMemcpyAsync(&v[prob], h->d_probs + prob, sizeof(ProbDev), hipMemcpyDeviceToHost,
-                              h->stream));
-    HIP_TRY(h, hipStreamSynchronize(h->stream));
     if (dst) {
-        HIP_TRY(h, launch_pack(h->prec, 0, h->d_stage, h->U[0], h->U[1], h->d_probs + prob, h->h_probs[prob].off_u,
-                               h->h_probs[prob].off_d, h->K, h->nvar, h->ncell[prob], h->stream));
-        HIP_TRY(h, hipMemcpyAsync(dst, h->d_stage, sizeof(double) * n,
-                                  dst_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
-                                  h->stream));
-        HIP_TRY(h, hipStreamSynchronize(h->stream));
+        const bool direct = dst_on_device && kernel_can_use(h, dst);
+        HIP_TRY(h, pack_state(h, prob, nullptr, direct ? dst : h->d_stage,
+                              PackOp{0.0, 0, 0, h->status}));
+        if (!direct) {
+            const int64_t n = (int64_t)h->nvar * h->K * h->ncell[prob];
+            HIP_TRY(h, hipMemcpyAsync(dst, h->d_stage, sizeof(double) * n,
+                                      dst_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
+                                      h->stream));
+        }
+    } else {
+        HIP_TRY(h, launch_status(h->d_probs + prob, h->status, h->stream));
     }
-    if (t) *t = v[prob].t;
-    return report_errors(h, v, prob);
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    if (t) *t = h->status->t;
+    return report_status(h, prob);
 }
 
 extern "C" int hweno_sync(hweno_handle* h) {
@@ -677,15 +702,11 @@ extern "C" int hweno_alpha(hweno_handle* h, int32_t prob, double* ax, double* ay
     if (!h->state_set[prob]) return fail(h, HWENO_ERR_STATE, "problem %d has no state yet", prob);
     rc = alpha_all(h);
     if (rc) return rc;
-    std::vector<ProbDev> v;
-    rc = read_probs(h, v);
-    if (rc) return rc;
-    double x, y;
-    std::memcpy(&x, &v[prob].ax_bits, 8);
-    std::memcpy(&y, &v[prob].ay_bits, 8);
-    if (ax) *ax = x;
-    if (ay) *ay = y;
-    return report_errors(h, v, prob);
+    HIP_TRY(h, launch_status(h->d_probs + prob, h->status, h->stream));
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    if (ax) *ax = h->status->ax;
+    if (ay) *ay = h->status->ay;
+    return report_status(h, prob);
 }
 
 extern "C" int hweno_rhs(hweno_handle* h, int32_t prob, double* L_out, double* Uhat_out,
@@ -711,10 +732,9 @@ extern "C" int hweno_rhs(hweno_handle* h, int32_t prob, double* L_out, double* U
             HIP_TRY(h, hipMemcpyAsync(Uhat_out, a.Uh_out, sizeof(double) * n,
                                       hipMemcpyDeviceToHost, h->stream));
     }
-    std::vector<ProbDev> v;
-    rc = read_probs(h, v);
-    if (rc) return rc;
-    return report_errors(h, v, prob);
+    HIP_TRY(h, launch_status(h->d_probs + prob, h->status, h->stream));
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    return report_status(h, prob);
 }
 
 // One SSP-RK3 step of every unfinished problem: wave speeds and dt, three

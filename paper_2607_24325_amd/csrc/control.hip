@@ -133,27 +133,45 @@ __global__ void dt_kernel(ProbDev* probs, StepCtl* ctl, int nprob, int use_dt_in
     }
 }
 
-template <class TU, class TD>
-__global__ void pack_kernel(int to_internal, double* ext, TU* u0, TD* d0, TU* u1, TD* d1,
-                            const ProbDev* prob, int K, int nvar, int64_t ncell) {
-    const int cur = prob->cur;
-    TU* u = cur ? u1 : u0;
-    TD* d = cur ? d1 : d0;
-    const int64_t n = (int64_t)nvar * K * ncell;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t plane = e / ncell;   // var*K + comp
-        const int64_t cell = e - plane * ncell;
-        if (plane < K) {
-            if (to_internal) u[e] = (TU)ext[e];
-            else ext[e] = (double)u[e];
+__device__ __forceinline__ void write_status(const ProbDev& P, ProbStatus* out) {
+    *out = ProbStatus{P.t, as_double(P.ax_bits), as_double(P.ay_bits), P.bad_cell, P.err, P.nx};
+}
+
+// Converts between the boundary layout and the internal planes: blockIdx.y is
+// the plane (var*K + comp), so that no element divides by the cell count.
+// First thread of the launch: op.set_t, the problem's table entry for a new
+// state; op.status, what the host asks of the table, into pinned host memory
+// (the host waits for the launch before it reads it).
+template <class TU, class TD, bool IN>
+__global__ void __launch_bounds__(256) pack_kernel(const double* src, double* dst, TU* u0, TD* d0,
+                                                   TU* u1, TD* d1, ProbDev* prob, int K,
+                                                   int64_t ncell, PackOp op) {
+    const int cur = prob->cur, plane = blockIdx.y;
+    TU* u = (cur ? u1 : u0) + (int64_t)plane * ncell;
+    TD* d = (cur ? d1 : d0) + (int64_t)(plane - K) * ncell;
+    const int64_t e0 = (int64_t)plane * ncell;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < ncell;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        if (IN) {
+            if (plane < K) u[i] = (TU)src[e0 + i];
+            else d[i] = (TD)src[e0 + i];
         } else {
-            const int64_t de = (plane - K) * ncell + cell;
-            if (to_internal) d[de] = (TD)ext[e];
-            else ext[e] = (double)d[de];
+            dst[e0 + i] = plane < K ? (double)u[i] : (double)d[i];
         }
     }
+    if (blockIdx.x != 0 || plane != 0 || threadIdx.x != 0) return;
+    if (op.set_t) {
+        prob->t = op.t;
+        prob->err = 0;
+        prob->err_next = 0;
+        prob->bad_cell = INT64_MAX;
+        prob->active = 0;
+        prob->alpha_valid = 0;
+    }
+    if (op.status) write_status(*prob, op.status);
 }
+
+__global__ void status_kernel(const ProbDev* prob, ProbStatus* out) { write_status(*prob, out); }
 
 // --------------------------------------------------------------- launchers
 
@@ -194,24 +212,30 @@ hipError_t launch_dt(ProbDev* probs, StepCtl* ctl, int nprob, int use_dt_in, int
     return hipGetLastError();
 }
 
-template <class TU, class TD>
-static void pack_launch(int to_internal, double* ext, StateBuf b0, StateBuf b1, const ProbDev* prob,
-                        int64_t off_u, int64_t off_d, int K, int nvar, int64_t ncell,
-                        hipStream_t s) {
-    const int64_t n = (int64_t)nvar * K * ncell;
-    const int grid = (int)((n + 255) / 256 < 65536 ? (n + 255) / 256 : 65536);
-    pack_kernel<TU, TD><<<grid, 256, 0, s>>>(to_internal, ext, (TU*)b0.u + off_u, (TD*)b0.d + off_d,
-                                             (TU*)b1.u + off_u, (TD*)b1.d + off_d, prob, K, nvar,
-                                             ncell);
+hipError_t launch_status(const ProbDev* prob, ProbStatus* out, hipStream_t s) {
+    status_kernel<<<1, 1, 0, s>>>(prob, out);
+    return hipGetLastError();
 }
 
-hipError_t launch_pack(int prec, int to_internal, double* ext, StateBuf b0, StateBuf b1,
-                       const ProbDev* prob, int64_t off_u, int64_t off_d, int K, int nvar,
-                       int64_t ncell, hipStream_t s) {
+template <class TU, class TD>
+static void pack_launch(const double* src, double* dst, StateBuf b0, StateBuf b1, ProbDev* prob,
+                        int64_t off_u, int64_t off_d, int K, int nvar, int64_t ncell,
+                        const PackOp& op, hipStream_t s) {
+    const int64_t nb = (ncell + 255) / 256;
+    const dim3 grid((unsigned)(nb < 8192 ? nb : 8192), (unsigned)(nvar * K));
+    TU *u0 = (TU*)b0.u + off_u, *u1 = (TU*)b1.u + off_u;
+    TD *d0 = (TD*)b0.d + off_d, *d1 = (TD*)b1.d + off_d;
+    if (src) pack_kernel<TU, TD, true><<<grid, 256, 0, s>>>(src, dst, u0, d0, u1, d1, prob, K, ncell, op);
+    else pack_kernel<TU, TD, false><<<grid, 256, 0, s>>>(src, dst, u0, d0, u1, d1, prob, K, ncell, op);
+}
+
+hipError_t launch_pack(int prec, const double* src, double* dst, StateBuf b0, StateBuf b1,
+                       ProbDev* prob, int64_t off_u, int64_t off_d, int K, int nvar, int64_t ncell,
+                       const PackOp& op, hipStream_t s) {
     auto* f = prec == P_F64 ? pack_launch<double, double>
               : prec == P_F32 ? pack_launch<float, float>
               : prec == P_ACC64 ? pack_launch<double, float> : pack_launch<ffs, float>;
-    f(to_internal, ext, b0, b1, prob, off_u, off_d, K, nvar, ncell, s);
+    f(src, dst, b0, b1, prob, off_u, off_d, K, nvar, ncell, op, s);
     return hipGetLastError();
 }
 

@@ -206,12 +206,26 @@ hipError_t launch_run1d(int prec, int flux, int waves, int nprob, const Run1Args
 int run1d_waves(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg);
 // Cells per lane of the 1D step kernel for these problems.
 int step1d_cells(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg);
+// What the host asks of a problem's table entry.
+struct ProbStatus {
+    double t, ax, ay;
+    int64_t bad_cell;
+    int32_t err, nx;
+};
+// What a conversion does besides: make the entry that of a new state at time
+// t; leave the status in pinned host memory.
+struct PackOp {
+    double t;
+    int32_t set_t, pad;
+    ProbStatus* status;
+};
 // Converts one problem's state between the boundary layout (double,
 // ext[((var*K + c)*ny + j)*nx + i]) and the internal planes of b0 or b1, the
-// one prob->cur names.
-hipError_t launch_pack(int prec, int to_internal, double* ext, StateBuf b0, StateBuf b1,
-                       const ProbDev* prob, int64_t off_u,
-                       int64_t off_d, int K, int nvar, int64_t ncell, hipStream_t s);
+// one prob->cur names: from src if given, else to dst.
+hipError_t launch_pack(int prec, const double* src, double* dst, StateBuf b0, StateBuf b1,
+                       ProbDev* prob, int64_t off_u, int64_t off_d, int K, int nvar, int64_t ncell,
+                       const PackOp& op, hipStream_t s);
+hipError_t launch_status(const ProbDev* prob, ProbStatus* out, hipStream_t s);
 
 // --- host helpers of the C ABI (api.cpp) --------------------------------
 // Checks problems and configuration (ERR_ARG with the reason as the

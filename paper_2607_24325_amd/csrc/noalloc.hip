@@ -196,7 +196,7 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
     noalloc_setup_kernel<<<sgrid, 256, 0, s>>>(pd, sc, probs, ctl, pe, dim, nseg, out1d, tiles,
                                                ntiles, chunks, nchunks);
     NA_TRY(hipGetLastError());
-    NA_TRY(launch_pack(prec, 1, const_cast<double*>(state_in), U[0], U[1], probs, 0, 0, K, nvar, ncell, s));
+    NA_TRY(launch_pack(prec, state_in, nullptr, U[0], U[1], probs, 0, 0, K, nvar, ncell, PackOp{}, s));
     NA_TRY(launch_alpha(prec, flux, dim, U[0].u, U[1].u, probs, chunks, nchunks, sch,
                         SEL_STALE, 0, s));
     if (cells1d) {
@@ -235,7 +235,7 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
             else NA_TRY(launch_stage2d(prec, flux, cfg->gauss_q, mode, 0, a, 0, s));
         }
     }
-    NA_TRY(launch_pack(prec, 0, state_out, U[0], U[1], probs, 0, 0, K, nvar, ncell, s));
+    NA_TRY(launch_pack(prec, nullptr, state_out, U[0], U[1], probs, 0, 0, K, nvar, ncell, PackOp{}, s));
     if (dt_out || bad_out) {
         noalloc_report_kernel<<<1, 64, 0, s>>>(probs, dt_out, bad_out);
         NA_TRY(hipGetLastError());
