@@ -287,9 +287,8 @@ static Layout layout_of(const hweno_problem* probs, int32_t nprob, const hweno_c
             steps1d += tiles_1d(probs[p].nx, cells1d);
         }
         else tiles += tiles_2d(probs[p].nx, probs[p].ny, 8);  // smallest height a caller can ask for
-        // lines for the problems that can be cut into more than SLOTS tiles
-        if ((D == 1 ? tiles_1d(probs[p].nx, 1) : tiles_2d(probs[p].nx, probs[p].ny, 2)) > SLOTS)
-            slots += SLOTS;
+        slots += lines_of(groups_of(D == 1 ? tiles_1d(probs[p].nx, 1)
+                                           : tiles_2d(probs[p].nx, probs[p].ny, 2)));
         nch += (int)((nc + CHUNK_CELLS - 1) / CHUNK_CELLS);
     }
     L.u_bytes = align256(nu * su);
@@ -382,9 +381,10 @@ static int build_tiles(hweno_handle* h) {
     }
     size_t slots = 0;
     for (ProbEnd& e : ends) {
-        e.arrived = e.pad = 0;
-        e.slot0 = e.ntiles > SLOTS ? (int)slots : -1;
-        if (e.slot0 >= 0) slots += SLOTS;
+        e.slot0 = (int)slots;
+        e.groups = groups_of(e.ntiles);
+        e.pad = 0;
+        slots += lines_of(e.groups);
     }
     if (slots > h->slots_cap) return fail(h, HWENO_ERR_OOM, "speed slots exceed their buffer");
     HIP_TRY(h, hipMemcpy(h->d_ends, ends.data(), sizeof(ProbEnd) * h->nprob,

@@ -312,22 +312,17 @@ __device__ __forceinline__ void publish_max(uint64_t* slot, double v, uint64_t s
     if (b > seen) atomicMax((unsigned long long*)slot, b);
 }
 
-// Where a tile of the group `slot` leaves its speed maxima.
-__device__ __forceinline__ uint64_t* speed_slot(ProbDev& P, int p, const StepCtl* ctl, int slot) {
-    const int slot0 = ctl->ends[p].slot0;
-    return slot0 < 0 ? &P.ax_next : &ctl->slots[slot0 + slot].ax;
-}
-
 // Folds a tile's reduced speeds and first bad cell into the problem's maxima
 // for the state being written (one lane calls this).  Speeds are non-negative,
 // so their bit patterns order as unsigned integers; err itself stays as the
 // step began with.
 __device__ __forceinline__ void publish_speeds(ProbDev& P, int p, const StepCtl* ctl, int slot,
                                                double mx, double my, long long bad) {
-    uint64_t* s = speed_slot(P, p, ctl, slot);
-    atomicMax((unsigned long long*)&s[0], (unsigned long long)__double_as_longlong(mx));
+    const ProbEnd pe = ctl->ends[p];
+    Slot& s = ctl->slots[pe.slot0 + (pe.groups > 1 ? slot : 0)];
+    atomicMax((unsigned long long*)&s.ax, (unsigned long long)__double_as_longlong(mx));
     if (my > 0.0)
-        atomicMax((unsigned long long*)&s[1], (unsigned long long)__double_as_longlong(my));
+        atomicMax((unsigned long long*)&s.ay, (unsigned long long)__double_as_longlong(my));
     if (bad != LLONG_MAX) {
         atomicMin((long long*)&P.bad_cell, bad);
         atomicOr(&P.err_next, ERR_STATE_BAD);
@@ -405,8 +400,6 @@ __device__ __forceinline__ bool finish_problem(ProbDev& P, const StepCtl* ctl, i
         P.err |= __hip_atomic_load(&P.err_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (flags & STEP_FLIP) P.cur ^= 1;
     }
-    P.ax_next = 0;
-    P.ay_next = 0;
     P.err_next = 0;
     running = P.t < P.t_end && !P.err;
     return act;
@@ -448,31 +441,31 @@ __device__ __forceinline__ void end_problem(int p, int run, int steps, StepCtl* 
 // step, the launch's last problem writes the step counters.
 __device__ __forceinline__ void end_tile(ProbDev& P, int p, int slot, StepCtl* ctl, int flags) {
     const int lane = threadIdx.x & 63;
-    ProbEnd& pe = ctl->ends[p];
-    const int ntiles = pe.ntiles, slot0 = pe.slot0;
+    const ProbEnd pe = ctl->ends[p];
+    const bool many = pe.groups > 1;
+    Slot* line = &ctl->slots[pe.slot0];   // the groups', or the problem's one
     int last = 0;
     if (lane == 0) {
         wait_atomics();
-        if (slot0 < 0) {
-            last = atomicAdd(&pe.arrived, 1) == ntiles - 1;
-        } else if (atomicAdd(&ctl->slots[slot0 + slot].arrived, 1) == (ntiles - slot - 1) / SLOTS) {
-            last = atomicAdd(&pe.arrived, 1) == SLOTS - 1;
-        }
+        if (!many)
+            last = atomicAdd(&line->arrived, 1) == pe.ntiles - 1;
+        else if (atomicAdd(&line[slot].arrived, 1) == (pe.ntiles - slot - 1) / SLOTS)
+            last = atomicAdd(&line[SLOTS].arrived, 1) == SLOTS - 1;
     }
     if (!__builtin_amdgcn_readfirstlane(last)) return;
-    uint64_t ax, ay;
-    if (slot0 < 0) {
-        ax = peek_slot(&P.ax_next);
-        ay = peek_slot(&P.ay_next);
-    } else {
-        Slot& s = ctl->slots[slot0 + lane];
-        ax = (uint64_t)__double_as_longlong(wave_max_d(as_double(peek_slot(&s.ax))));
-        ay = (uint64_t)__double_as_longlong(wave_max_d(as_double(peek_slot(&s.ay))));
+    Slot& s = line[many ? lane : 0];
+    double mx = as_double(peek_slot(&s.ax)), my = as_double(peek_slot(&s.ay));
+    if (many) {
+        mx = wave_max_d(mx);
+        my = wave_max_d(my);
+    }
+    if (many || lane == 0) {
         s.ax = s.ay = 0;
         s.arrived = 0;
     }
     if (lane != 0) return;
-    pe.arrived = 0;
+    if (many) line[SLOTS].arrived = 0;
+    const uint64_t ax = (uint64_t)__double_as_longlong(mx), ay = (uint64_t)__double_as_longlong(my);
     bool running;
     const int steps = finish_problem(P, ctl, flags, ax, ay, running);
     end_problem(p, running, steps, ctl);

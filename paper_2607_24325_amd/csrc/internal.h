@@ -35,8 +35,6 @@ struct ProbDev {
     double dt_in;      // requested step when the caller supplies one
     uint64_t ax_bits;  // max wave speeds of the current state, as the bits of
     uint64_t ay_bits;  // non-negative doubles
-    uint64_t ax_next;  // the same for the state stage 3 is writing
-    uint64_t ay_next;
     int32_t active;    // 1 while the current step advances this problem
     int32_t last;      // the current step lands exactly on t_end
     int32_t err;       // non-admissible state seen: ERR_STATE_BAD (a stored state),
@@ -52,18 +50,24 @@ struct ProbDev {
 // problem writes the step counters.  Atomics on one address take 11 ns each,
 // one after the other, so problems of more than SLOTS tiles spread maxima and
 // arrivals over SLOTS lines (8620 tiles, 1 million cells in 1D: 100 us a step
-// with one address, 57 us with 64), and batches their ends likewise.
+// with one address, 57 us with 64), and batches their ends likewise.  The
+// lines are apart from the problem table, which every tile reads when it
+// starts: an atomic takes its line out of the L2s of all XCDs (512 problems of
+// 1D, 2.1 million cells: 142 us a step with the maxima in the table, XXX apart).
 constexpr int SLOTS = 64;
 struct alignas(128) Slot {
     uint64_t ax, ay;   // speed maxima (of a tile group)
-    int32_t arrived;   // tiles of the group, or problems of a group
+    int32_t arrived;   // tiles of the group, groups of a problem, problems of a group
     int32_t run, steps;  // problems of the group still short of t_end; most steps taken
 };
-// Per problem: its tiles in the step list, its first slot (-1: the problem's
-// own ax_next, ay_next), tiles or full slots that have arrived.
+// Per problem: its tiles in the step list, the groups they arrive in (1 or
+// SLOTS) and its first line: the groups', followed by the problem's if there
+// are several.
 struct ProbEnd {
-    int32_t ntiles, slot0, arrived, pad;
+    int32_t ntiles, groups, slot0, pad;
 };
+inline int groups_of(int ntiles) { return ntiles > SLOTS ? SLOTS : 1; }
+__host__ __device__ inline int lines_of(int groups) { return groups > 1 ? groups + 1 : 1; }
 // Global step control, resident in device memory.  Kernels get its address
 // alone: what they need only at a tile's end is then loaded there instead of
 // being held in scalar registers through the tile.
@@ -75,7 +79,7 @@ struct StepCtl {
     int32_t step_active;  // some problem advanced in the current step
     int64_t steps;     // steps in which some problem advanced
     ProbEnd* ends;     // per problem
-    Slot* slots;       // of the problems with more than SLOTS tiles
+    Slot* slots;
     Slot* groups;      // SLOTS groups of problems and their total (batches)
 };
 

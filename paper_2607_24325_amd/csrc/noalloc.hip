@@ -31,8 +31,7 @@ __global__ void noalloc_setup_kernel(ProbDev pd, StepCtl ctl, ProbDev* probs, St
         *dctl = ctl;
         *ctl.ends = pe;
     }
-    if (pe.slot0 >= 0)
-        for (int k = tid; k < SLOTS; k += nth) ctl.slots[k] = Slot{};
+    for (int k = tid; k < lines_of(pe.groups); k += nth) ctl.slots[k] = Slot{};
     const int strips = (pd.nx + STRIP_OUT - 1) / STRIP_OUT;
     for (int t = tid; t < ntiles; t += nth) {
         if (dim == 1) {
@@ -122,7 +121,7 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
     for (;; rows = 32) {
         ntiles = dim == 1 ? (pr.nx + TILE1D_OUT - 1) / TILE1D_OUT : tiles_2d(pr.nx, pr.ny, rows);
         tb = up256((size_t)ntiles * (dim == 1 ? sizeof(Tile1D) : sizeof(Tile2D)));
-        need = 3 * (ub + db) + db + up256(sizeof(ProbDev)) + up256(sizeof(StepCtl)) + tb + cb;
+        need = 3 * (ub + db) + db + up256(sizeof(ProbDev)) + 256 + tb + cb;
         if (need <= HWENO_NOALLOC_SCRATCH_BYTES || dim == 1 || rows == 32) break;
     }
     if (need > HWENO_NOALLOC_SCRATCH_BYTES)
@@ -163,22 +162,23 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
     StepCtl* ctl = (StepCtl*)p;
     StepCtl sc{};
     sc.ends = (ProbEnd*)(p + sizeof(StepCtl));
-    static_assert(sizeof(StepCtl) + sizeof(ProbEnd) <= 256, "one region holds both");
-    p += up256(sizeof(StepCtl));
+    sc.slots = (Slot*)(p + 128);
+    static_assert(sizeof(StepCtl) + sizeof(ProbEnd) <= 128 && sizeof(Slot) == 128,
+                  "one region of 256 bytes holds the three");
+    p += 256;
     void* tiles = p; p += tb;
     Chunk* chunks = (Chunk*)p;
     if (cells1d) {   // two sets only: the longer tile list goes where the third would
         tiles = U[2].u;
         ntiles = tiles_1d(pr.nx, cells1d);
     }
-    // slots for the speeds of many tiles: in the unused third set, or behind
-    // the lists where there is room (else every tile uses the table's own)
-    ProbEnd pe{ntiles, -1, 0, 0};
-    if (ntiles > SLOTS) {
-        if (cells1d) sc.slots = (Slot*)U[2].d;
-        else if (need + SLOTS * sizeof(Slot) <= HWENO_NOALLOC_SCRATCH_BYTES)
-            sc.slots = (Slot*)((char*)chunks + cb);
-        if (sc.slots) pe.slot0 = 0;
+    // lines for the groups of many tiles: in the unused third set, or behind
+    // the lists where there is room (else every tile uses the one line)
+    ProbEnd pe{ntiles, 1, 0, 0};
+    const size_t gb = lines_of(SLOTS) * sizeof(Slot);
+    if (groups_of(ntiles) > 1 && (cells1d || need + gb <= HWENO_NOALLOC_SCRATCH_BYTES)) {
+        pe.groups = SLOTS;
+        sc.slots = (Slot*)(cells1d ? (char*)U[2].d : (char*)chunks + cb);
     }
 
     // Every value a launch reads is written here first: the table entry and
