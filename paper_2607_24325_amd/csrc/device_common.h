@@ -170,57 +170,52 @@ template <class T> struct Flux<T, F_EULER, 3, 0> {
     }
 };
 
-// 2D Euler, U = (rho, rho*mu, rho*nu, E); DIR selects F (x) or G (y).
+// 2D Euler, U = (rho, rho*mu, rho*nu, E); DIR selects F (x) or G (y).  What an
+// edge point needs of one side is the flux plus al times its argument (al =
+// alpha on the left, -alpha on the right): with s = (normal velocity) + al the
+// transported terms of both become one product, and the second side's terms
+// are accumulated onto the first's (FIRST: out starts with this side).  Per
+// edge point this takes 24 instructions fewer than fluxes and Lax-Friedrichs
+// terms apart.
 template <class T, int DIR> struct Flux<T, F_EULER, 4, DIR> {
     T gm1;
     __device__ Flux(const Scheme& s) : gm1((T)(s.gas_gamma - 1.0)) {}
-    // (dF/dU) D or (dG/dU) D, with the common factor of three of its rows
-    // taken out: for F, a = dm - u dr gives 2u dm - u^2 dr = u (dm + a),
-    // v dm + u dn - uv dr = v a + u dn and H dm - uH dr = H a (for G
-    // likewise with b = dn - v dr)
-    __device__ __forceinline__ void jvp(T u, T v, T q2h, T H, const T* D, T* out) const {
-        const T dr = D[0], dm = D[1], dn = D[2], dE = D[3];
-        const T dp = gm1 * (dE - u * dm - v * dn + q2h * dr);
-        if (DIR == 0) {
-            const T a = dm - u * dr;
-            out[0] = dm;
-            out[1] = u * (dm + a) + dp;
-            out[2] = v * a + u * dn;
-            out[3] = H * a + u * (dE + dp);
-        } else {
-            const T b = dn - v * dr;
-            out[0] = dn;
-            out[1] = u * b + v * dm;
-            out[2] = v * (dn + b) + dp;
-            out[3] = H * b + v * (dE + dp);
-        }
-    }
-    // velocity, half its square, pressure and total enthalpy of U
+    // velocity, half its square, pressure, total enthalpy, s
     struct Prim {
-        T u, v, q2h, p, H;
+        T u, v, q2h, p, H, s;
     };
-    __device__ __forceinline__ Prim prim(const T* U) const {
+    __device__ __forceinline__ Prim prim(const T* U, T al) const {
         const T rho = U[0], m = U[1], n = U[2], E = U[3];
         const T ir = rcp(rho);
         const T u = m * ir, v = n * ir;
-        const T q2h = (T)0.5 * (u * u + v * v);
-        const T p = gm1 * (E - rho * q2h);
-        return {u, v, q2h, p, (E + p) * ir};
+        const T q2h = (T)0.5 * fused(u, u, v * v);
+        const T p = gm1 * fused(-rho, q2h, E);
+        return {u, v, q2h, p, (E + p) * ir, (DIR == 0 ? u : v) + al};
     }
-    __device__ __forceinline__ void flux(const T* U, const Prim& w, T* f) const {
-        const T m = U[1], n = U[2], Ep = U[3] + w.p;
-        if (DIR == 0) {
-            f[0] = m; f[1] = m * w.u + w.p; f[2] = m * w.v; f[3] = w.u * Ep;
-        } else {
-            f[0] = n; f[1] = n * w.u; f[2] = n * w.v + w.p; f[3] = w.v * Ep;
-        }
+    // F: m, m u + p, n u, u (E + p); G: n, m v, n v + p, v (E + p)
+    template <bool FIRST>
+    __device__ __forceinline__ void flux(const T* U, const Prim& w, T al, T* out) const {
+        constexpr int N = DIR == 0 ? 1 : 2, A = 3 - N;   // normal and other momentum
+        const T vn = DIR == 0 ? w.u : w.v;
+        out[0] = fused(al, U[0], FIRST ? U[N] : out[0] + U[N]);
+        out[N] = fused(w.s, U[N], FIRST ? w.p : out[N] + w.p);
+        out[A] = FIRST ? w.s * U[A] : fused(w.s, U[A], out[A]);
+        out[3] = fused(w.s, U[3], FIRST ? vn * w.p : fused(vn, w.p, out[3]));
     }
-    __device__ __forceinline__ void side(const T* U, const T* V, const T* W, T* f, T* fv,
-                                         T* fw) const {
-        const Prim w = prim(U);
-        flux(U, w, f);
-        jvp(w.u, w.v, w.q2h, w.H, V, fv);
-        jvp(w.u, w.v, w.q2h, w.H, W, fw);
+    // (dF/dU) D or (dG/dU) D, with the common factor of three of its rows
+    // taken out: for F, a = dm - u dr gives 2u dm - u^2 dr = u (dm + a),
+    // v dm + u dn - uv dr = v a + u dn and H dm - uH dr = H a (for G
+    // likewise with the y momentum)
+    template <bool FIRST>
+    __device__ __forceinline__ void jvp(const T* D, const Prim& w, T al, T* out) const {
+        constexpr int N = DIR == 0 ? 1 : 2, A = 3 - N;
+        const T vn = DIR == 0 ? w.u : w.v, va = DIR == 0 ? w.v : w.u;
+        const T dp = gm1 * fused(w.q2h, D[0], fused(-w.v, D[2], fused(-w.u, D[1], D[3])));
+        const T a = fused(-vn, D[0], D[N]);
+        out[0] = fused(al, D[0], FIRST ? D[N] : out[0] + D[N]);
+        out[N] = fused(vn, a, fused(w.s, D[N], FIRST ? dp : out[N] + dp));
+        out[A] = fused(w.s, D[A], FIRST ? va * a : fused(va, a, out[A]));
+        out[3] = fused(w.s, D[3], fused(vn, dp, FIRST ? w.H * a : fused(w.H, a, out[3])));
     }
 };
 
@@ -718,10 +713,9 @@ template <class T, int K> struct Eigen {
 // ----------------------------------------------------- nonlinear weights ---
 //
 // omega~_m = gamma_m (1 + tau^2 / D_m), omega = omega~ / sum (eq.
-// nonlinear-weights, eq. nonlinear-weights-2D), with D_m = beta_m + eps or
-// beta_m^2 + eps (SQ = 1) or chosen per value (SQ = -1, from `squared`),
+// nonlinear-weights), with D_m = beta_m + eps or, `squared`, beta_m^2 + eps,
 // tau = mean_m |beta_0 - beta_m|.
-template <class T, int M, int SQ>
+template <class T, int M>
 __device__ __forceinline__ void nonlinear_weights_form(const T* beta, const Scheme& s, int squared,
                                                        T* omega) {
     T tau = 0;
@@ -730,7 +724,7 @@ __device__ __forceinline__ void nonlinear_weights_form(const T* beta, const Sche
     tau *= (T)(1.0 / M);
     const T tau2 = tau * tau;
     const T eps = (T)s.eps;
-    const bool sq = SQ < 0 ? squared != 0 : SQ != 0;
+    const bool sq = squared != 0;
     T wt[M + 1], sum = 0;
 #pragma unroll
     for (int m = 0; m <= M; ++m) {
@@ -743,22 +737,17 @@ __device__ __forceinline__ void nonlinear_weights_form(const T* beta, const Sche
     for (int m = 0; m <= M; ++m) omega[m] = wt[m] * inv;
 }
 
-// The form is chosen per launch.  BRANCH: a branch on the wave-uniform flag,
-// each side with the form fixed at compile time (fewer instructions, more
-// code); else one copy selecting the denominator per value (fewer registers,
-// which bound the occupancy of the 1D kernel).
-template <class T, int M, bool BRANCH>
+// The form is chosen per launch by a wave-uniform flag: one copy selecting the
+// denominator per value (fewer registers, which bound the occupancy of the 1D
+// kernels).
+template <class T, int M>
 __device__ __forceinline__ void nonlinear_weights(const T* beta, const Scheme& s, int squared,
                                                   T* omega) {
     if (s.weights == W_LINEAR) {
 #pragma unroll
         for (int m = 0; m <= M; ++m) omega[m] = (T)s.gam[m];
-    } else if (!BRANCH) {
-        nonlinear_weights_form<T, M, -1>(beta, s, squared, omega);
-    } else if (squared) {
-        nonlinear_weights_form<T, M, 1>(beta, s, squared, omega);
     } else {
-        nonlinear_weights_form<T, M, 0>(beta, s, squared, omega);
+        nonlinear_weights_form<T, M>(beta, s, squared, omega);
     }
 }
 

@@ -53,7 +53,7 @@ struct ProbDev {
 // with one address, 57 us with 64), and batches their ends likewise.  The
 // lines are apart from the problem table, which every tile reads when it
 // starts: an atomic takes its line out of the L2s of all XCDs (512 problems of
-// 1D, 2.1 million cells: 142 us a step with the maxima in the table, XXX apart).
+// 1D, 2.1 million cells: 142 us a step with the maxima in the table, 105 apart).
 constexpr int SLOTS = 64;
 struct alignas(128) Slot {
     uint64_t ax, ay;   // speed maxima (of a tile group)

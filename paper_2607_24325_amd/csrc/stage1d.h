@@ -59,7 +59,7 @@ __device__ __forceinline__ void recon1d_field(T dm, T dp, T sv, T dv, const Sche
     beta[1] = dm * dm;
     beta[2] = dp * dp;
     T w[3];
-    nonlinear_weights<T, 2, false>(beta, sch, squared, w);
+    nonlinear_weights<T, 2>(beta, sch, squared, w);
     const T a0 = w[0] * g0inv;
     const T b1 = w[1] - a0 * (T)sch.gam[1], b2 = w[2] - a0 * (T)sch.gam[2];
     T C[5];

@@ -36,119 +36,190 @@ template <> struct Gauss<3> {
     __device__ static constexpr double w(int mu) { return mu == 1 ? 8.0 / 18.0 : 5.0 / 18.0; }
 };
 
-// Appendix A coefficients c_{0,1..15} (stored 0..14) of the quartic p0 in
-// terms of q_1..q_17, written with the centre average subtracted from the
-// nine averages (q_5 = 0): every coefficient but the constant is invariant
-// under that shift, and the constant becomes relative to the centre.
+// The same weights for doubled edge fluxes and up to the factor WSUM, which
+// goes into 1/dx and 1/dy: the sum over an edge's points costs no product
+// (Q = 2) or one.
+template <int Q> constexpr double WSUM = Q == 2 ? 0.25 : 5.0 / 36.0;
+template <class T, int Q, class F> __device__ __forceinline__ T edge_sum(F f) {
+    if constexpr (Q == 2) return f(0) + f(1);
+    else return fused((T)1.6, f(1), f(0) + f(2));
+}
+
+// Appendix A coefficients c_{0,1..15} (0..14 here) of the quartic p0 in terms
+// of q_1..q_17, written with the centre average subtracted from the nine
+// averages (q_5 = 0): every coefficient but the constant is invariant under
+// that shift, and the constant becomes relative to the centre.  The march is
+// bound by vector instructions (98% of the issue slots in single precision),
+// so they come as the numerators n[l] = AN[l] c[l], whose scales go into the
+// one product per coefficient that weights p0 below, and the cubic and quartic
+// numerators, which are differences of the lower ones, are formed first and
+// taken back out of those: 51 instructions instead of 74 for the c themselves.
+// (With the blend, face values and edge flux below, 436 instructions a row and
+// wave instead of 511; a stage of 2048^2 cells 249 -> 236 us in F32_ACC64,
+// 449 -> 412 us in F64.)
+constexpr double AN[15] = {2880, 24, 24, 48, 16, 48, 20, 4, 4, 20, 4, 4, 4, 4, 4};
 template <class T>
-__device__ __forceinline__ void appendix_a(const T* q, T* c) {
+__device__ __forceinline__ void appendix_a(const T* q, T* n) {
     // q[0..16] hold q_1..q_17
-    const T q1 = q[0], q2 = q[1], q3 = q[2], q4 = q[3], q6 = q[5], q7 = q[6], q8 = q[7],
-            q9 = q[8];
-    const T corner = (q1 + q3) + (q7 + q9);
-    const T xdc = (q3 + q9) - (q1 + q7);
-    const T ydc = (q7 + q9) - (q1 + q3);
-    const T xyc = (q1 - q3) - (q7 - q9);
-    const T sx = q4 + q6, dxs = q6 - q4;
-    const T sy = q2 + q8, dys = q8 - q2;
+    const T S = q[0] + q[2], N = q[6] + q[8], dS = q[2] - q[0], dN = q[8] - q[6];
+    const T corner = S + N, ydc = N - S, xdc = dS + dN, xyc = dN - dS;
+    const T sx = q[3] + q[5], dxs = q[5] - q[3];
+    const T sy = q[1] + q[7], dys = q[7] - q[1];
     const T vWEs = q[9] + q[10], vWEd = q[10] - q[9];
     const T vSNs = q[11] + q[12], vSNd = q[12] - q[11];
     const T wWEs = q[13] + q[14], wWEd = q[14] - q[13];
     const T wSNs = q[15] + q[16], wSNd = q[16] - q[15];
-    c[0] = ((T)5 * corner - (T)292 * (sx + sy) + (T)81 * (vWEd + wSNd)) * (T)(1.0 / 2880.0);
-    c[1] = ((T)19 * dxs - (T)2 * xdc - (T)6 * vWEs + (T)3 * vSNs) * (T)(1.0 / 24.0);
-    c[2] = ((T)19 * dys - (T)2 * ydc + (T)3 * wWEs - (T)6 * wSNs) * (T)(1.0 / 24.0);
-    c[3] = ((T)62 * sx + (T)2 * sy - corner - (T)18 * vWEd) * (T)(1.0 / 48.0);
-    c[4] = ((T)5 * (vSNd + wWEd) - (T)3 * xyc) * (T)0.125;
-    c[5] = ((T)62 * sy + (T)2 * sx - corner - (T)18 * wSNd) * (T)(1.0 / 48.0);
-    c[6] = (xdc - (T)4 * dxs + (T)4 * vWEs - (T)2 * vSNs) * (T)0.05;
-    c[7] = (ydc - (T)2 * dys) * (T)0.25;
-    c[8] = (xdc - (T)2 * dxs) * (T)0.25;
-    c[9] = (ydc - (T)4 * dys - (T)2 * wWEs + (T)4 * wSNs) * (T)0.05;
-    c[10] = (vWEd - (T)2 * sx) * (T)0.25;
-    c[11] = (xyc - (T)2 * vSNd) * (T)0.25;
-    c[12] = (corner - (T)2 * (sx + sy)) * (T)0.25;
-    c[13] = (xyc - (T)2 * wWEd) * (T)0.25;
-    c[14] = (wSNd - (T)2 * sy) * (T)0.25;
+    const T s = sx + sy;
+    n[10] = fused((T)-2, sx, vWEd);
+    n[14] = fused((T)-2, sy, wSNd);
+    n[12] = fused((T)-2, s, corner);
+    n[11] = fused((T)-2, vSNd, xyc);
+    n[13] = fused((T)-2, wWEd, xyc);
+    n[7] = fused((T)-2, dys, ydc);
+    n[8] = fused((T)-2, dxs, xdc);
+    // 19 dxs - 2 xdc - 6 vWEs + 3 vSNs = 12 dxs - 2 n8 - 3 e, with e the
+    // excess of the derivative averages' slope, and so on
+    const T ex = fused((T)2, vWEs, -vSNs) - dxs, ey = fused((T)2, wSNs, -wWEs) - dys;
+    n[1] = fused((T)-3, ex, fused((T)-2, n[8], (T)12 * dxs));
+    n[2] = fused((T)-3, ey, fused((T)-2, n[7], (T)12 * dys));
+    n[6] = fused((T)2, ex, n[8]);
+    n[9] = fused((T)2, ey, n[7]);
+    n[3] = fused((T)-18, n[10], fused((T)24, sx, -n[12]));
+    n[5] = fused((T)-18, n[14], fused((T)24, sy, -n[12]));
+    n[4] = fused((T)-5, n[11] + n[13], (T)4 * xyc);
+    n[0] = fused((T)81, n[10] + n[14], fused((T)5, n[12], (T)-120 * s));
+}
+
+// Nonlinear weights of the 2D blend (eq. nonlinear-weights-2D), as the
+// polynomial needs them: with omega_m = gamma_m (1 + tau^2 r_m) / sum and
+// r_m = 1 / D_m, omega_0 / gamma_0 = a0 = (1 + tau^2 r_0) / sum and
+// omega_m - a0 gamma_m = k d_m, k = tau^2 / sum, d_m = gamma_m (r_m - r_0).
+template <class T, bool SQ>
+__device__ __forceinline__ void blend_form(const T* beta, const Scheme& s, T& a0, T& k, T* d) {
+    const T t = (fabs(beta[0] - beta[1]) + fabs(beta[0] - beta[2])) +
+                (fabs(beta[0] - beta[3]) + fabs(beta[0] - beta[4]));
+    const T tau = (T)0.25 * t, tau2 = tau * tau;
+    const T eps = (T)s.eps;
+    T r[5], g[5], gs = 0;
+#pragma unroll
+    for (int m = 0; m < 5; ++m) {
+        r[m] = rcp(SQ ? fused(beta[m], beta[m], eps) : beta[m] + eps);
+        g[m] = (T)s.gam[m];
+        gs += g[m];
+    }
+    T S = g[0] * r[0];
+#pragma unroll
+    for (int m = 1; m < 5; ++m) {
+        const T gr = g[m] * r[m];
+        d[m - 1] = fused(-g[m], r[0], gr);
+        S += gr;
+    }
+    const T inv = rcp(fused(tau2, S, gs));
+    a0 = fused(tau2, r[0], (T)1) * inv;
+    k = tau2 * inv;
 }
 
 // HWENO polynomial of one cell and component (Steps 1-3).  q: stencil with
 // the centre average subtracted.  C: coefficients of u_ij - u-bar_ij in the
-// basis 1, xi, eta, xi^2, xi eta, eta^2, xi^3, xi^2 eta, xi eta^2, eta^3,
-// xi^4, xi^3 eta, xi^2 eta^2, xi eta^3, eta^4.
+// basis 1, X, Y, X^2, X Y, Y^2, X^3, X^2 Y, X Y^2, Y^3, X^4, X^3 Y, X^2 Y^2,
+// X Y^3, Y^4 with X = 2 xi, Y = 2 eta, so that the faces lie at +-1 and the
+// face values below need no powers of one half.
 template <class T>
 __device__ __forceinline__ void reconstruct2d(const T* q, const Scheme& s, int squared, T* C,
                                               T& vhat, T& what) {
-    T c0[15];
-    appendix_a(q, c0);
+    T n[15];
+    appendix_a(q, n);
     // linear polynomials on the L-shaped stencils S1..S4: slopes only
     const T sW = -q[3], sE = q[5], sS = -q[1], sN = q[7];
-    // smoothness indicators: sum over monomials of (m! n! c_mn)^2
-    T b0 = c0[1] * c0[1] + c0[2] * c0[2] + c0[4] * c0[4];
-    b0 += (T)4 * (c0[3] * c0[3] + c0[5] * c0[5] + c0[7] * c0[7] + c0[8] * c0[8]);
-    b0 += (T)16 * c0[12] * c0[12];
-    b0 += (T)36 * (c0[6] * c0[6] + c0[9] * c0[9] + c0[11] * c0[11] + c0[13] * c0[13]);
-    b0 += (T)576 * (c0[10] * c0[10] + c0[14] * c0[14]);
     T beta[5];
-    beta[0] = s.smoothness == BETA_CLASSICAL ? beta_classical_2d(c0) : b0;
-    const T sW2 = sW * sW, sE2 = sE * sE, sS2 = sS * sS, sN2 = sN * sN;
-    beta[1] = sW2 + sS2;
-    beta[2] = sE2 + sS2;
-    beta[3] = sE2 + sN2;
-    beta[4] = sW2 + sN2;
-    T w[5];
-    nonlinear_weights<T, 4, true>(beta, s, squared, w);
+    if (s.smoothness == BETA_CLASSICAL) {
+        T c0[15];
+#pragma unroll
+        for (int l = 0; l < 15; ++l) c0[l] = n[l] * (T)(1.0 / AN[l]);
+        beta[0] = beta_classical_2d(c0);
+    } else {
+        // smoothness indicator: sum over monomials of (m! n! c_mn)^2
+        auto sq2 = [](T a, T b) { return fused(a, a, b * b); };
+        T b0 = n[12] * n[12];                                       // 16 c12^2
+        b0 = fused((T)(1.0 / 576.0), sq2(n[1], n[2]), b0);
+        b0 = fused((T)(4.0 / 2304.0), sq2(n[3], n[5]), b0);
+        b0 = fused((T)(1.0 / 256.0), n[4] * n[4], b0);
+        b0 = fused((T)0.09, sq2(n[6], n[9]), b0);
+        b0 = fused((T)0.25, sq2(n[7], n[8]), b0);
+        b0 = fused((T)2.25, sq2(n[11], n[13]), b0);
+        beta[0] = fused((T)36, sq2(n[10], n[14]), b0);
+    }
+    const T sW2 = sW * sW, sE2 = sE * sE;
+    beta[1] = fused(sS, sS, sW2);
+    beta[2] = fused(sS, sS, sE2);
+    beta[3] = fused(sN, sN, sE2);
+    beta[4] = fused(sN, sN, sW2);
     // u_ij = w0/g0 p0 + sum_m (w_m - w0 g_m/g0) p_m   (eq. hweno-reconstruction-2D)
-    const T a0 = w[0] * (T)(1.0 / s.gam[0]);
-    T bm[4];
+    T a0 = (T)1, k = (T)0, d[4] = {0, 0, 0, 0};
+    if (s.weights != W_LINEAR) {
+        if (squared) blend_form<T, true>(beta, s, a0, k, d);
+        else blend_form<T, false>(beta, s, a0, k, d);
+    }
+    // coefficient l of p0 is n[l] / AN[l], in X and Y divided by 2^degree
+    const T w64 = a0 * (T)(1.0 / 64.0), w32 = a0 * (T)(1.0 / 32.0), w160 = a0 * (T)(1.0 / 160.0);
+    const T w192 = a0 * (T)(1.0 / 192.0), w48 = a0 * (T)(1.0 / 48.0), kh = (T)0.5 * k;
+    C[0] = a0 * (T)(1.0 / 2880.0) * n[0];
+    C[1] = fused(kh, fused(sW, d[0] + d[3], sE * (d[1] + d[2])), w48 * n[1]);
+    C[2] = fused(kh, fused(sS, d[0] + d[1], sN * (d[2] + d[3])), w48 * n[2]);
+    C[3] = w192 * n[3];
+    C[5] = w192 * n[5];
+    C[6] = w160 * n[6];
+    C[9] = w160 * n[9];
+    C[7] = w32 * n[7];
+    C[8] = w32 * n[8];
+    C[4] = w64 * n[4];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) bm[m] = w[m + 1] - a0 * (T)s.gam[m + 1];
-#pragma unroll
-    for (int l = 0; l < 15; ++l) C[l] = a0 * c0[l];
-    C[1] += sW * (bm[0] + bm[3]) + sE * (bm[1] + bm[2]);
-    C[2] += sS * (bm[0] + bm[1]) + sN * (bm[2] + bm[3]);
+    for (int l = 10; l < 15; ++l) C[l] = w64 * n[l];
     // modified derivatives: integrals of u_x, u_y over the cell (scaled units)
-    vhat = C[1] + (T)0.25 * C[6] + (T)(1.0 / 12.0) * C[8];
-    what = C[2] + (T)0.25 * C[9] + (T)(1.0 / 12.0) * C[7];
+    vhat = fused((T)2, C[1] + C[6], (T)(2.0 / 3.0) * C[8]);
+    what = fused((T)2, C[2] + C[9], (T)(2.0 / 3.0) * C[7]);
 }
 
 // Values at the Gauss points of the two faces normal to the first variable
-// of C (xi for x-faces; pass the transposed coefficients for y-faces).
-// Outputs per side s (0: -1/2, 1: +1/2) and node mu: value, derivative
-// normal to the face, derivative along the face (local units, relative
-// value).
+// of C (X for x-faces; pass the transposed coefficients for y-faces).
+// Outputs per side s (0: -1, 1: +1) and node mu: value, derivative normal to
+// the face, derivative along the face (by X and Y: half of the derivatives by
+// xi and eta; relative value).  Parities in the two variables: E, O even and
+// odd parts in the normal one at the face, by powers of the other; then ee,
+// oe, eo, oo by both.  An odd part's last factor goes into the sum that
+// combines the parts.
 template <class T, int Q>
 __device__ __forceinline__ void face_values(const T* C, T (*val)[Q], T (*dn)[Q], T (*dt)[Q]) {
-    const T E0 = C[0] + (T)0.25 * C[3] + (T)0.0625 * C[10], O0 = (T)0.5 * C[1] + (T)0.125 * C[6];
-    const T E1 = C[2] + (T)0.25 * C[7], O1 = (T)0.5 * C[4] + (T)0.125 * C[11];
-    const T E2 = C[5] + (T)0.25 * C[12], O2 = (T)0.5 * C[8];
-    const T E3 = C[9], O3 = (T)0.5 * C[13];
+    const T E0 = C[0] + (C[3] + C[10]), O0 = C[1] + C[6];
+    const T E1 = C[2] + C[7], O1 = C[4] + C[11];
+    const T E2 = C[5] + C[12], O2 = C[8];
+    const T E3 = C[9], O3 = C[13];
     const T E4 = C[14];
-    const T Eb0 = C[1] + (T)0.75 * C[6], Ob0 = C[3] + (T)0.5 * C[10];
-    const T Eb1 = C[4] + (T)0.75 * C[11], Ob1 = C[7];
+    const T Eb0 = fused((T)3, C[6], C[1]), Ob0 = fused((T)2, C[10], C[3]);   // Ob: half of the odd parts
+    const T Eb1 = fused((T)3, C[11], C[4]), Ob1 = C[7];
     const T Eb2 = C[8], Ob2 = C[12];
     const T Eb3 = C[13];
-    const T g = (T)Gauss<Q>::g, g2 = g * g, g3 = g2 * g, g4 = g2 * g2;
-    // symmetric pair of nodes +-g
-    const T uee = E0 + g2 * E2 + g4 * E4, uoe = O0 + g2 * O2;
-    const T ueo = g * E1 + g3 * E3, uoo = g * O1 + g3 * O3;
-    const T nee = Eb0 + g2 * Eb2, noe = Ob0 + g2 * Ob2;
-    const T neo = g * Eb1 + g3 * Eb3, noo = g * Ob1;
-    const T tee = E1 + (T)3 * g2 * E3, toe = O1 + (T)3 * g2 * O3;
-    const T teo = (T)2 * g * E2 + (T)4 * g3 * E4, too = (T)2 * g * O2;
+    constexpr double gd = 2.0 * Gauss<Q>::g;   // nodes at +-g in [-1, 1]
+    const T g = (T)gd, g2 = (T)(gd * gd);
+    const T uee = fused(g2, fused(g2, E4, E2), E0), uoe = fused(g2, O2, O0);
+    const T ueo = fused(g2, E3, E1), uoo = fused(g2, O3, O1);             // times g
+    const T nee = fused(g2, Eb2, Eb0), noe = fused(g2, Ob2, Ob0);         // noe times 2
+    const T neo = fused(g2, Eb3, Eb1), noo = Ob1;                         // times g, 2 g
+    const T tee = fused((T)(3.0 * gd * gd), E3, E1), toe = fused((T)(3.0 * gd * gd), O3, O1);
+    const T teo = fused((T)(2.0 * gd * gd), E4, E2), too = O2;            // times 2 g
     constexpr int lo = 0, hi = Q - 1;  // nodes -g and +g
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
         const T sg = s ? (T)1 : (T)-1;
         const T ue = uee + sg * uoe, uo = ueo + sg * uoo;
-        const T ne = nee + sg * noe, no = neo + sg * noo;
+        const T ne = fused((T)2 * sg, noe, nee), no = fused((T)2 * sg, noo, neo);
         const T te = tee + sg * toe, to = teo + sg * too;
-        val[s][lo] = ue - uo; val[s][hi] = ue + uo;
-        dn[s][lo] = ne - no;  dn[s][hi] = ne + no;
-        dt[s][lo] = te - to;  dt[s][hi] = te + to;
+        val[s][lo] = fused(-g, uo, ue); val[s][hi] = fused(g, uo, ue);
+        dn[s][lo] = fused(-g, no, ne);  dn[s][hi] = fused(g, no, ne);
+        dt[s][lo] = fused((T)-2 * g, to, te); dt[s][hi] = fused((T)2 * g, to, te);
         if (Q == 3) {
             val[s][1] = E0 + sg * O0;
-            dn[s][1] = Eb0 + sg * Ob0;
+            dn[s][1] = fused((T)2 * sg, Ob0, Eb0);
             dt[s][1] = E1 + sg * O1;
         }
     }
@@ -162,28 +233,39 @@ template <class T> __device__ __forceinline__ void transpose15(const T* C, T* D)
 
 // Lax-Friedrichs flux at one edge point, all components, TWICE its value:
 // out = 2 (f, f^v, f^w) = (f(L) + alpha L) + (f(R) - alpha R).  The factor
-// 1/2 is folded into the Gauss weights of the residual, which saves one
-// multiply per output (halving and doubling are exact in binary floating
-// point); the two sides are accumulated one after the other, so that only
-// one side's values and fluxes are live at a time.
+// 1/2 is folded into the weights of the residual; the two sides are
+// accumulated one after the other, so that only one side's values and fluxes
+// are live at a time.
 template <class T, int FLUX, int K, int DIR>
 __device__ __forceinline__ void lf_edge(const Flux<T, FLUX, K, DIR>& F, const T* UL, const T* VL,
                                         const T* WL, const T* UR, const T* VR, const T* WR,
                                         T alpha, T* out) {
-    T f[K], fv[K], fw[K];
-    F.side(UL, VL, WL, f, fv, fw);
+    if constexpr (FLUX == F_EULER && K == 4) {
+        const auto L = F.prim(UL, alpha);
+        F.template flux<true>(UL, L, alpha, out);
+        F.template jvp<true>(VL, L, alpha, out + K);
+        F.template jvp<true>(WL, L, alpha, out + 2 * K);
+        const auto R = F.prim(UR, -alpha);
+        F.template flux<false>(UR, R, -alpha, out);
+        F.template jvp<false>(VR, R, -alpha, out + K);
+        F.template jvp<false>(WR, R, -alpha, out + 2 * K);
+        return;
+    } else {
+        T f[K], fv[K], fw[K];
+        F.side(UL, VL, WL, f, fv, fw);
 #pragma unroll
-    for (int c = 0; c < K; ++c) {
-        out[c] = f[c] + alpha * UL[c];
-        out[K + c] = fv[c] + alpha * VL[c];
-        out[2 * K + c] = fw[c] + alpha * WL[c];
-    }
-    F.side(UR, VR, WR, f, fv, fw);
+        for (int c = 0; c < K; ++c) {
+            out[c] = f[c] + alpha * UL[c];
+            out[K + c] = fv[c] + alpha * VL[c];
+            out[2 * K + c] = fw[c] + alpha * WL[c];
+        }
+        F.side(UR, VR, WR, f, fv, fw);
 #pragma unroll
-    for (int c = 0; c < K; ++c) {
-        out[c] = (out[c] + f[c]) - alpha * UR[c];
-        out[K + c] = (out[K + c] + fv[c]) - alpha * VR[c];
-        out[2 * K + c] = (out[2 * K + c] + fw[c]) - alpha * WR[c];
+        for (int c = 0; c < K; ++c) {
+            out[c] = (out[c] + f[c]) - alpha * UR[c];
+            out[K + c] = (out[K + c] + fv[c]) - alpha * VR[c];
+            out[2 * K + c] = (out[2 * K + c] + fw[c]) - alpha * WR[c];
+        }
     }
 }
 
@@ -252,8 +334,10 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, Q, mode, V>()))
         }
         const int nx = P_.nx, ny = P_.ny, bcx = P_.bc_x, bcy = P_.bc_y;
         const int64_t plane = (int64_t)nx * ny;
-        const T inv_dx = (T)P_.inv_dx, inv_dy = (T)P_.inv_dy;
-        const TA inv_dx_a = (TA)P_.inv_dx, inv_dy_a = (TA)P_.inv_dy;
+        // the residual's factors, with the edge sums' weight; the derivatives
+        // at the edge points are by X = 2 xi, Y = 2 eta
+        const T inv_dx = (T)(P_.inv_dx * (2.0 * WSUM<Q>)), inv_dy = (T)(P_.inv_dy * (2.0 * WSUM<Q>));
+        const TA inv_dx_a = (TA)(P_.inv_dx * WSUM<Q>), inv_dy_a = (TA)(P_.inv_dy * WSUM<Q>);
         const T rx = (T)(P_.dx * P_.inv_dy), ry = (T)(P_.dy * P_.inv_dx);
         const T ax = (T)as_double(P_.ax_bits), ay = (T)as_double(P_.ay_bits);
         const double dt = step.dt;
@@ -433,40 +517,31 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, Q, mode, V>()))
                         // other, each from its own four face values: fewer
                         // registers at the register peak of the FP64 march
                         T out[3 * K];
-                        auto side = [&](auto& F, T (*src)[64], int ll, T al, bool first) {
+                        auto side = [&](auto& F, T (*src)[64], int ll, T al, auto first) {
+                            constexpr bool FIRST = decltype(first)::value;
                             const int b = mu * 3 * K;
-                            T U[K], D[K], o[K];
+                            T D[K];
 #pragma unroll
-                            for (int k = 0; k < K; ++k) U[k] = src[b + k][ll];
-                            const auto w = F.prim(U);
-                            F.flux(U, w, o);
-#pragma unroll
-                            for (int k = 0; k < K; ++k) {
-                                const T ok = o[k] + al * U[k];
-                                out[k] = first ? ok : out[k] + ok;
-                            }
+                            for (int k = 0; k < K; ++k) D[k] = src[b + k][ll];
+                            const auto w = F.prim(D, al);
+                            F.template flux<FIRST>(D, w, al, out);
 #pragma unroll
                             for (int sk = 1; sk < 3; ++sk) {
 #pragma unroll
                                 for (int k = 0; k < K; ++k) D[k] = src[b + sk * K + k][ll];
-                                F.jvp(w.u, w.v, w.q2h, w.H, D, o);
-#pragma unroll
-                                for (int k = 0; k < K; ++k) {
-                                    const T ok = o[k] + al * D[k];
-                                    out[sk * K + k] = first ? ok : out[sk * K + k] + ok;
-                                }
+                                F.template jvp<FIRST>(D, w, al, out + sk * K);
                             }
                         };
                         if (kind == 0) {
                             if (l < 63) {   // x-edge between lanes l and l+1
-                                side(FXf, sxR, l, ax, true);
-                                side(FXf, sxL, l + 1, -ax, false);
+                                side(FXf, sxR, l, ax, std::true_type());
+                                side(FXf, sxL, l + 1, -ax, std::false_type());
 #pragma unroll
                                 for (int k = 0; k < 3 * K; ++k) FX(mu, k, l) = out[k];
                             }
                         } else {            // y-edge between rows r-1 and r, column l
-                            side(FYf, syT, l, ay, true);
-                            side(FYf, syB, l, -ay, false);
+                            side(FYf, syT, l, ay, std::true_type());
+                            side(FYf, syB, l, -ay, std::false_type());
 #pragma unroll
                             for (int k = 0; k < 3 * K; ++k) FY(mu, k, l) = out[k];
                         }
@@ -511,19 +586,11 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, Q, mode, V>()))
                 T xdd[2], gyd[2];
 #pragma unroll
                 for (int sk = 0; sk < 3; ++sk) {
-                    T fr = 0, fl = 0, g = 0;
-#pragma unroll
-                    for (int mu = 0; mu < Q; ++mu) {
-                        const T w = (T)(0.5 * Gauss<Q>::w(mu));   // fluxes are stored doubled
-                        fr += w * FX(mu, sk * K + c, lane);
-                        if constexpr (P != P_F64)
-                            fl += w * FX(mu, sk * K + c, lane > 0 ? lane - 1 : 0);
-                        g += w * FY(mu, sk * K + c, lane);
-                    }
-                    // FP64: the left edge's sum is the left lane's right-edge
-                    // sum, the same bits, taken by a lane shift instead of
-                    // further LDS reads (the FP64 march is LDS-heavy)
-                    if constexpr (P == P_F64) fl = from_left(fr);
+                    T fr = edge_sum<T, Q>([&](int mu) { return FX(mu, sk * K + c, lane); });
+                    T g = edge_sum<T, Q>([&](int mu) { return FY(mu, sk * K + c, lane); });
+                    // the left edge's sum is the left lane's right-edge sum,
+                    // taken by a lane shift instead of further LDS reads
+                    T fl = from_left(fr);
                     if (sk == 0) {
                         xdu = (TA)fr - (TA)fl;
                         gyu = (TA)g;

@@ -80,8 +80,9 @@ __global__ void __launch_bounds__(256, (P == P_F64 ? 1 : 2)) stage2d_char_kernel
         }
         const int nx = P_.nx, ny = P_.ny, bcx = P_.bc_x, bcy = P_.bc_y;
         const int64_t plane = (int64_t)nx * ny;
-        const T inv_dx = (T)P_.inv_dx, inv_dy = (T)P_.inv_dy;
-        const TA inv_dx_a = (TA)P_.inv_dx, inv_dy_a = (TA)P_.inv_dy;
+        // the residual's factors, as in stage2d_kernel
+        const T inv_dx = (T)(P_.inv_dx * (2.0 * WSUM<Q>)), inv_dy = (T)(P_.inv_dy * (2.0 * WSUM<Q>));
+        const TA inv_dx_a = (TA)(P_.inv_dx * WSUM<Q>), inv_dy_a = (TA)(P_.inv_dy * WSUM<Q>);
         const T rx = (T)(P_.dx * P_.inv_dy), ry = (T)(P_.dy * P_.inv_dx);
         const T ax = (T)as_double(P_.ax_bits), ay = (T)as_double(P_.ay_bits);
         const double dt = step.dt;
@@ -245,9 +246,9 @@ __global__ void __launch_bounds__(256, (P == P_F64 ? 1 : 2)) stage2d_char_kernel
                 T C[15], vh, wh;
                 reconstruct2d<T>(wx, sch, squared, C, vh, wh);
                 vhx = vh;
-                // derivatives in local units (d/dxi, d/deta): the back
-                // projection and the edge flux are linear in them, and the
-                // residual applies 1/dx, 1/dy once
+                // derivatives in local units (d/dX, d/dY): the back projection
+                // and the edge flux are linear in them, and the residual
+                // applies 2/dx, 2/dy once
                 T val[2][Q], dn[2][Q], dtg[2][Q];
                 face_values<T, Q>(C, val, dn, dtg);
 #pragma unroll
@@ -353,14 +354,9 @@ __global__ void __launch_bounds__(256, (P == P_F64 ? 1 : 2)) stage2d_char_kernel
                 T xdd[2], gyd[2];
 #pragma unroll
                 for (int sk = 0; sk < 3; ++sk) {
-                    T fr = 0, fl = 0, g = 0;
-#pragma unroll
-                    for (int mu = 0; mu < Q; ++mu) {
-                        const T w = (T)(0.5 * Gauss<Q>::w(mu));   // fluxes are stored doubled
-                        fr += w * sFX[mu][sk * K + c][lane];
-                        fl += w * sFX[mu][sk * K + c][lane > 0 ? lane - 1 : 0];
-                        g += w * sFY[mu][sk * K + c][lane];
-                    }
+                    const T fr = edge_sum<T, Q>([&](int mu) { return sFX[mu][sk * K + c][lane]; });
+                    const T g = edge_sum<T, Q>([&](int mu) { return sFY[mu][sk * K + c][lane]; });
+                    const T fl = from_left(fr);
                     if (sk == 0) {
                         xdu = (TA)fr - (TA)fl;
                         gyu = (TA)g;
