@@ -123,14 +123,15 @@ int tiles_2d(int nx, int ny, int rows) {
 // A workgroup marches its rows one after the other, so a launch with fewer
 // tiles than the GPU has workgroup slots takes as long as one tile however
 // small the problem is (256^2 Euler, FP64, Q = 3: 40 tiles of 32 rows on 256
-// CUs, 108 us a stage, against 30 us as 430 tiles of 3 rows).  Below two
+// CUs, 93 us a stage, against 27 us as 430 tiles of 3 rows).  Below two
 // rounds of slots the height is the one that minimises
 //     (rows + 3) * (full rounds * c(slots per CU) + c(workgroups left per CU)),
 // rows + 3: marched rows of a tile (two of them halo) and its set-up; c(n):
-// time of one row with n workgroups on a CU relative to one alone.  Measured
-// c(n) = 1 + 0.43 (n - 1) for the four-wave Euler workgroups (a row alone /
-// two to a CU: 2.9 / 4.3 us in FP64 Q = 3, 1.5 / 2.1 us in F32_ACC64 Q = 2)
-// and about 1 + 0.15 (n - 1) for the one-wave scalar ones.  From two rounds on
+// time of one row with n workgroups on a CU relative to one alone.  Taken as
+// c(n) = 1 + 0.43 (n - 1) for the four-wave Euler workgroups (a row alone
+// takes 2.4 us in FP64 Q = 3, 1.6 us in F32_ACC64 Q = 2)
+// and 1 + 0.15 (n - 1) for the one-wave scalar ones: between 256^2 and 1600 x
+// 800 its choice is within 4% of the best height.  From two rounds on
 // the dispatcher's own balance makes taller segments better (fewer halo rows).
 int split_rows(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg, int cap) {
     constexpr int64_t NCU = 256;
@@ -138,7 +139,7 @@ int split_rows(const hweno_problem* probs, int32_t nprob, const hweno_config& cf
     // workgroups that fit a CU (registers and LDS of the kernels)
     const int slots = !euler ? 12
                              : cfg.characteristic ? (f64 ? 1 : 2)
-                                                  : (f64 ? 3 : 4) - (cfg.gauss_q == 3 ? 1 : 0);
+                                                  : (f64 ? 3 : 5) - (cfg.gauss_q == 3 ? 1 : 0);
     const double g = euler ? 0.43 : 0.15;
     auto tiles = [&](int rows) {
         int64_t n = 0;

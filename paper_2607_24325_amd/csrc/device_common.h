@@ -512,18 +512,20 @@ __device__ __attribute__((noinline)) void gather_tile_speeds(const TU* out_u, ui
     const uint32_t ci = (uint32_t)(i0 + (col ? lane : 0));
     double mx = 0.0, my = 0.0;
     long long bad = LLONG_MAX;
-    for (int j = ra; j < rb; ++j) {
+    // one row ahead: a load's way through the L2 hides behind the divisions
+    using W = typename std::conditional<sizeof(TU) == 8, uint64_t, uint32_t>::type;
+    W next[K];
+    auto load = [&](int j) {
         const uint32_t off = ((uint32_t)(j * nx) + ci) * (uint32_t)sizeof(TU);
+#pragma unroll
+        for (int k = 0; k < K; ++k) next[k] = *(const __attribute__((address_space(1))) W*)(gp[k] + off);
+    };
+    if (ra < rb) load(ra);
+    for (int j = ra; j < rb; ++j) {
         double u[K];
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            TU v;
-            if constexpr (sizeof(TU) == 8)
-                v = __builtin_bit_cast(TU, *(const __attribute__((address_space(1))) uint64_t*)(gp[k] + off));
-            else
-                v = __builtin_bit_cast(TU, *(const __attribute__((address_space(1))) uint32_t*)(gp[k] + off));
-            u[k] = (double)v;
-        }
+        for (int k = 0; k < K; ++k) u[k] = (double)__builtin_bit_cast(TU, next[k]);
+        load(min(j + 1, rb - 1));
         if (col) {
             double sx, sy;
             if (wave_speed<FLUX, 2, K>(u, sch, sx, sy)) {

@@ -12,13 +12,24 @@
 //   R  each (lane, component) reconstructs its cell and writes the values of
 //      U, u_xi, u_eta (local units) at the Gauss points of its four faces to
 //      LDS;
-//   F  each thread computes the Lax-Friedrichs flux (all components) at one
-//      edge Gauss point: the x-edges of this row and the y-edges between this
-//      row and the one below;
-//   S  each (lane, component) differences the fluxes of the row below, which
-//      now has all four edges, and applies the RK stage to it.
-// Every edge flux is computed once per workgroup and used by both cells, so
-// the update is conservative to the rounding of the cell-average arithmetic.
+//   F  wave k takes one face of every cell (left, right, bottom, top), lane =
+//      column, and sums over the face's Gauss points its side of the
+//      Lax-Friedrichs flux, all components;
+//   S  each (lane, component) adds the two sides of its edges (the x-neighbour's
+//      by a lane shift, the lower row's top face from the iteration before),
+//      differences the fluxes of the row below, which now has all four edges,
+//      and applies the RK stage to it.
+// A face is its own cell's affair, so a wave reads only its own columns, sums
+// the Gauss points in registers (with three of them no wave waits for another)
+// and hands on one sum instead of a flux per point, in 12 to 24 registers less
+// than an edge point's two sides took: five workgroups instead of four fit a CU
+// in single precision (a stage of 2048^2 cells 236 -> 217 us in F32_ACC64, 412
+// -> 402 us in F64; 256^2, Q = 3, F64: 23.1 -> 21.6 us).
+// A scalar law has one wave: its face values and fluxes never leave the lane,
+// and neither LDS nor a barrier is needed (240^2 Burgers, Q = 3, F64: 11.6 ->
+// 7.8 us a stage).
+// Both cells of an edge use the sum of the same two numbers, so the update is
+// conservative to the rounding of the cell-average arithmetic.
 #pragma once
 
 #include "device_common.h"
@@ -269,39 +280,81 @@ __device__ __forceinline__ void lf_edge(const Flux<T, FLUX, K, DIR>& F, const T*
     }
 }
 
+// One side of the Lax-Friedrichs flux at a face's Gauss point, TWICE its
+// value: f(U) + al U (al = alpha for a cell's right or top face, -alpha for its
+// left or bottom one) and the same of the derivative fluxes; FIRST starts the
+// sum over the points.  ld(v, D): the face's values of kind v.
+template <bool FIRST, class T, int FLUX, int K, int DIR, class LD>
+__device__ __forceinline__ void lf_side(const Flux<T, FLUX, K, DIR>& F, T al, LD ld, T* out) {
+    if constexpr (FLUX == F_EULER && K == 4) {
+        T D[K];
+        ld(0, D);
+        const auto w = F.prim(D, al);
+        F.template flux<FIRST>(D, w, al, out);
+#pragma unroll
+        for (int v = 1; v < 3; ++v) {
+            ld(v, D);
+            F.template jvp<FIRST>(D, w, al, out + v * K);
+        }
+    } else {
+        T U[K], V[K], W[K], f[K], fv[K], fw[K];
+        ld(0, U);
+        ld(1, V);
+        ld(2, W);
+        F.side(U, V, W, f, fv, fw);
+#pragma unroll
+        for (int c = 0; c < K; ++c) {
+            out[c] = fused(al, U[c], FIRST ? f[c] : out[c] + f[c]);
+            out[K + c] = fused(al, V[c], FIRST ? fv[c] : out[K + c] + fv[c]);
+            out[2 * K + c] = fused(al, W[c], FIRST ? fw[c] : out[2 * K + c] + fw[c]);
+        }
+    }
+}
+// The sum over a face's points, up to the factor WSUM.  ld(mu, v, D).
+template <int Q, class T, int FLUX, int K, int DIR, class LD>
+__device__ __forceinline__ void lf_face(const Flux<T, FLUX, K, DIR>& F, T al, LD ld, T* out) {
+    auto at = [&](int mu) { return [&ld, mu](int v, T* D) { ld(mu, v, D); }; };
+    if constexpr (Q == 2) {
+        lf_side<true>(F, al, at(0), out);
+        lf_side<false>(F, al, at(1), out);
+    } else {
+        lf_side<true>(F, al, at(1), out);
+#pragma unroll
+        for (int k = 0; k < 3 * K; ++k) out[k] *= (T)1.6;
+        lf_side<false>(F, al, at(0), out);
+        lf_side<false>(F, al, at(2), out);
+    }
+}
+
 // Workgroups per CU the register allocation is made for (launch bounds).
-// Variant 0: the occupancy the face arrays and registers comfortably allow
-// (every stage fits four FP32-face workgroups in 128 registers, the edge
-// flux accumulating one side at a time and stage 3's speed gather being a
-// call of its own after the march; with FP64 faces the streamed edge flux
-// keeps every stage within the 168 registers of three workgroups, which
-// their 48 KB of LDS also allow); variant 1: one workgroup more per CU,
+// Variant 0: the occupancy that the registers allow without spilling (the face
+// sums take one side and quantity at a time and stage 3's speed gather is a
+// call of its own after the march: at most 97 registers in single precision,
+// 164 in FP64) and the LDS of the faces; variant 1: one workgroup more per CU,
 // which caps the registers lower (the compiler may spill).  The tuner picks.
-template <int P, int Q, int mode, int V> constexpr int stage2d_min_blocks() {
-    return V + (P == P_F64 ? (Q == 3 ? 1 : 2) : (Q == 3 ? 2 : 4));
+template <int P, int K, int Q, int V> constexpr int stage2d_min_blocks() {
+    if (P == P_F64) return Q == 3 || K == 1 ? 2 + V : 3;
+    return V + (Q == 3 || K == 1 ? 4 : 5);
 }
 
 template <int P, int K, int Q, int FLUX, int mode, int V>
-__global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, Q, mode, V>())) stage2d_kernel(StageArgs a) {
+__global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, K, Q, V>())) stage2d_kernel(StageArgs a) {
     using TU = typename PrecT<P>::TU;
     using TD = typename PrecT<P>::TD;
     using T = typename PrecT<P>::T;
     using TA = typename PrecT<P>::TA;
-    constexpr int NF = Q * 3 * K;  // face values per lane and face (all components)
-    // Face values at the Gauss points, entry (mu*3 + v)*K + comp, v = value,
-    // d/dxi, d/deta.  The doubled edge fluxes of node mu, entry sk*K + comp
-    // (sk = u, v, w flux), are written over the face values they come from:
-    // x-edge l over sxR[mu*3*K + .][l], y-edge l over syB[mu*3*K + .][l].
-    // Only the thread of that edge point reads those face values, and it
-    // reads them all before it writes; the residual of component c reads
-    // only entries of component c, which the next row's reconstruction
-    // rewrites in the same wave, so no other wave can overwrite a flux
-    // before it is read.
-    __shared__ T sxR[NF][64], sxL[NF][64], syB[NF][64], syT[NF][64];
-    auto FX = [&](int mu, int k, int l) -> T& { return sxR[mu * 3 * K + k][l]; };
-    auto FY = [&](int mu, int k, int l) -> T& { return syB[mu * 3 * K + k][l]; };
+    // Values of the four faces (left, right, bottom, top) at their Gauss
+    // points, entry (mu*3 + v)*K + comp, v = value, d/dX, d/dY.  A face's
+    // side of the flux, entry sk*K + comp (sk = u, v, w flux), is written over
+    // them: only the thread of that face and column reads its values, and it
+    // reads them all before it writes; the residual of component c reads only
+    // entries of component c, which the next row's reconstruction rewrites in
+    // the same wave, so no other wave can overwrite a flux before it is read.
+    constexpr bool SHARE = K > 1;
+    __shared__ T sF[SHARE ? 4 : 1][SHARE ? Q * 3 * K : 1][64];
     __shared__ double smx[K], smy[K];  // stage 3: per-wave maxima of the wave speeds
     __shared__ long long sbad[K];      // stage 3: per-wave first non-admissible cell
+    constexpr bool S3 = mode == MODE_S3;
 
     const int lane = threadIdx.x & 63;
     // component of this wave (uniform: the plane pointers stay in SGPRs)
@@ -313,11 +366,12 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, Q, mode, V>()))
     const Tile2D* tiles = (const Tile2D*)a.tiles + a.tile_offset;
 
     // Stage 3 also gathers the wave speeds of the state it writes (for the
-    // next step's flux and time step), after each tile's march: the gather
-    // reads the tile's new averages back (they are in the L2 the stores
-    // went through) with every wave, so the march itself carries no extra
-    // registers and no wave waits for another's gather at a barrier.
-    constexpr bool fuse_alpha = mode == MODE_S3;
+    // next step's flux and time step).  A scalar law's are taken from the
+    // value as it is written.  For Euler the tile's new averages are read back
+    // after its march by every wave (they are in the caches the stores went
+    // through), so the march itself carries no extra registers: passing each
+    // row through LDS to one wave inside the march was 320 us a stage instead
+    // of 250 at 2048^2 in F32_ACC64 and 451 instead of 423 in F64.
 
     for (int tix = blockIdx.x; tix < a.ntiles; tix += gridDim.x) {
         const Tile2D tile = tiles[tix];
@@ -385,7 +439,7 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, Q, mode, V>()))
         constexpr bool SYMD = sizeof(T) == 4 && (std::is_same<TU, double>::value || std::is_same<TU, float>::value);
         T dneg = 0;
         if constexpr (SYMD) dneg = (T)(u0 - um);
-        T ytop[Q][3];            // top-face values of the previous row (this lane, comp)
+        T top_prev[3] = {0, 0, 0};   // the previous row's top sides (this lane, comp)
         // previous row's flux sums: x differences and y sums of the
         // cell-average fluxes in the accumulation type, of the derivative
         // fluxes in T.  The FP64 path (PARTIAL) carries instead the part of
@@ -399,6 +453,8 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, Q, mode, V>()))
         T xdd_prev[2] = {0, 0}, gyd_prev[2] = {0, 0};
         T hat_prev[2] = {0, 0};
 
+        double mxl = 0.0, myl = 0.0;     // stage 3 of a scalar law: this lane's maxima
+        long long badl = LLONG_MAX;
         for (int r = j0 - 1; r <= jend; ++r) {
             // prefetch the row two above and the RK inputs of the output row
             load_row(r + 2, un_, vn_, wn_);
@@ -416,12 +472,6 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, Q, mode, V>()))
             }
 
             // ---- R: reconstruct cell (gi, r), component c -------------------
-            if (r > j0 - 1) {
-#pragma unroll
-                for (int mu = 0; mu < Q; ++mu)
-#pragma unroll
-                    for (int v = 0; v < 3; ++v) syT[(mu * 3 + v) * K + c][lane] = ytop[mu][v];
-            }
             T q[17];
             if constexpr (sizeof(T) == 4) {
                 // Single precision: the column's own differences and the
@@ -475,122 +525,87 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, Q, mode, V>()))
             T C[15], vhat, what;
             reconstruct2d<T>(q, sch, squared, C, vhat, what);
             const T ucT = (T)u0;
-            {
-                T val[2][Q], dn[2][Q], dtg[2][Q];
-                // Derivatives go to the faces in local units (d/dxi, d/deta): the
-                // edge flux is linear in them, so the 1/dx, 1/dy of u_x, u_y are
-                // applied once to the residual instead of at every face point.
-                face_values<T, Q>(C, val, dn, dtg);   // x-faces: dn = d/dxi, dt = d/deta
+            // the rows beside the segment only lend it an edge: their x faces
+            // and far y faces are left out
+            const bool inner = r >= j0 && r < jend;
+            T FV[4][Q][3];   // a scalar law's face values
+            auto put = [&](int f, const T (*val)[Q], const T (*dX)[Q], const T (*dY)[Q]) {
 #pragma unroll
-                for (int mu = 0; mu < Q; ++mu) {
-                    sxL[(mu * 3 + 0) * K + c][lane] = ucT + val[0][mu];
-                    sxL[(mu * 3 + 1) * K + c][lane] = dn[0][mu];
-                    sxL[(mu * 3 + 2) * K + c][lane] = dtg[0][mu];
-                    sxR[(mu * 3 + 0) * K + c][lane] = ucT + val[1][mu];
-                    sxR[(mu * 3 + 1) * K + c][lane] = dn[1][mu];
-                    sxR[(mu * 3 + 2) * K + c][lane] = dtg[1][mu];
-                }
+                for (int mu = 0; mu < Q; ++mu)
+#pragma unroll
+                    for (int v = 0; v < 3; ++v) {
+                        const T x = v == 0 ? ucT + val[f & 1][mu] : (v == 1 ? dX : dY)[f & 1][mu];
+                        if constexpr (SHARE) sF[f][(mu * 3 + v) * K + c][lane] = x;
+                        else FV[f][mu][v] = x;
+                    }
+            };
+            // Derivatives go to the faces in local units (d/dX, d/dY): the
+            // edge flux is linear in them, so the 2/dx, 2/dy of u_x, u_y are
+            // applied once to the residual instead of at every face point.
+            T val[2][Q], dn[2][Q], dtg[2][Q];
+            if (inner) {
+                face_values<T, Q>(C, val, dn, dtg);   // x-faces: dn = d/dX, dt = d/dY
+                put(0, val, dn, dtg);
+                put(1, val, dn, dtg);
+            }
+            {
                 T D[15];
                 transpose15(C, D);
-                face_values<T, Q>(D, val, dn, dtg);   // y-faces: dn = d/deta, dt = d/dxi
-#pragma unroll
-                for (int mu = 0; mu < Q; ++mu) {
-                    syB[(mu * 3 + 0) * K + c][lane] = ucT + val[0][mu];
-                    syB[(mu * 3 + 1) * K + c][lane] = dtg[0][mu];
-                    syB[(mu * 3 + 2) * K + c][lane] = dn[0][mu];
-                    ytop[mu][0] = ucT + val[1][mu];
-                    ytop[mu][1] = dtg[1][mu];
-                    ytop[mu][2] = dn[1][mu];
-                }
+                face_values<T, Q>(D, val, dn, dtg);   // y-faces: dn = d/dY, dt = d/dX
+                put(2, val, dtg, dn);
+                put(3, val, dtg, dn);
             }
 
-            if (r > j0 - 1) {
-                __syncthreads();  // A: face values of row r (and top faces of r-1) ready
-                // ---- F: edge fluxes ---------------------------------------
-                for (int sl = threadIdx.x; sl < 2 * Q * 64; sl += 64 * K) {
-                    const int kind = sl / (Q * 64);
-                    const int mu = (sl >> 6) % Q;
-                    const int l = sl & 63;
-                    if constexpr (P == P_F64 && FLUX == F_EULER && K == 4) {
-                        // one side at a time, and within a side the flux and
-                        // its two Jacobian-vector products one after the
-                        // other, each from its own four face values: fewer
-                        // registers at the register peak of the FP64 march
-                        T out[3 * K];
-                        auto side = [&](auto& F, T (*src)[64], int ll, T al, auto first) {
-                            constexpr bool FIRST = decltype(first)::value;
-                            const int b = mu * 3 * K;
-                            T D[K];
+            // ---- F: the faces' sides of the edge fluxes ---------------------
+            T side[4][3];   // of this lane's cell, this component
+            if constexpr (SHARE) {
+                __syncthreads();  // A: face values of row r ready
+                auto face = [&](auto fi, const auto& F, T al) {
+                    constexpr int f = decltype(fi)::value;
+                    T out[3 * K];
+                    lf_face<Q>(F, al, [&](int mu, int v, T* D) {
 #pragma unroll
-                            for (int k = 0; k < K; ++k) D[k] = src[b + k][ll];
-                            const auto w = F.prim(D, al);
-                            F.template flux<FIRST>(D, w, al, out);
+                        for (int k = 0; k < K; ++k) D[k] = sF[f][(mu * 3 + v) * K + k][lane];
+                    }, out);
 #pragma unroll
-                            for (int sk = 1; sk < 3; ++sk) {
-#pragma unroll
-                                for (int k = 0; k < K; ++k) D[k] = src[b + sk * K + k][ll];
-                                F.template jvp<FIRST>(D, w, al, out + sk * K);
-                            }
-                        };
-                        if (kind == 0) {
-                            if (l < 63) {   // x-edge between lanes l and l+1
-                                side(FXf, sxR, l, ax, std::true_type());
-                                side(FXf, sxL, l + 1, -ax, std::false_type());
-#pragma unroll
-                                for (int k = 0; k < 3 * K; ++k) FX(mu, k, l) = out[k];
-                            }
-                        } else {            // y-edge between rows r-1 and r, column l
-                            side(FYf, syT, l, ay, std::true_type());
-                            side(FYf, syB, l, -ay, std::false_type());
-#pragma unroll
-                            for (int k = 0; k < 3 * K; ++k) FY(mu, k, l) = out[k];
-                        }
-                        continue;
-                    }
-                    T UL[K], VL[K], WL[K], UR[K], VR[K], WR[K], out[3 * K];
-                    if (kind == 0) {
-                        if (l < 63) {   // x-edge between lanes l and l+1
-#pragma unroll
-                            for (int k = 0; k < K; ++k) {
-                                UL[k] = sxR[(mu * 3 + 0) * K + k][l];
-                                VL[k] = sxR[(mu * 3 + 1) * K + k][l];
-                                WL[k] = sxR[(mu * 3 + 2) * K + k][l];
-                                UR[k] = sxL[(mu * 3 + 0) * K + k][l + 1];
-                                VR[k] = sxL[(mu * 3 + 1) * K + k][l + 1];
-                                WR[k] = sxL[(mu * 3 + 2) * K + k][l + 1];
-                            }
-                            lf_edge<T, FLUX, K, 0>(FXf, UL, VL, WL, UR, VR, WR, ax, out);
-#pragma unroll
-                            for (int k = 0; k < 3 * K; ++k) FX(mu, k, l) = out[k];
-                        }
-                    } else {            // y-edge between rows r-1 and r, column l
-#pragma unroll
-                        for (int k = 0; k < K; ++k) {
-                            UL[k] = syT[(mu * 3 + 0) * K + k][l];
-                            VL[k] = syT[(mu * 3 + 1) * K + k][l];
-                            WL[k] = syT[(mu * 3 + 2) * K + k][l];
-                            UR[k] = syB[(mu * 3 + 0) * K + k][l];
-                            VR[k] = syB[(mu * 3 + 1) * K + k][l];
-                            WR[k] = syB[(mu * 3 + 2) * K + k][l];
-                        }
-                        lf_edge<T, FLUX, K, 1>(FYf, UL, VL, WL, UR, VR, WR, ay, out);
-#pragma unroll
-                        for (int k = 0; k < 3 * K; ++k) FY(mu, k, l) = out[k];
-                    }
+                    for (int k = 0; k < 3 * K; ++k) sF[f][k][lane] = out[k];
+                };
+                if (inner || c == (r < j0 ? 3 : 2)) {
+                    if (c == 0) face(std::integral_constant<int, 0>(), FXf, -ax);
+                    else if (c == 1) face(std::integral_constant<int, 1>(), FXf, ax);
+                    else if (c == 2) face(std::integral_constant<int, 2>(), FYf, -ay);
+                    else face(std::integral_constant<int, 3>(), FYf, ay);
                 }
                 __syncthreads();  // B: fluxes ready
-                // ---- S: residual and RK stage of row r-1 ------------------
-                // The derivative fluxes are differenced in T: the difference of
-                // two T values rounded to T is what a wider difference rounds to.
+#pragma unroll
+                for (int f = 0; f < 4; ++f)
+#pragma unroll
+                    for (int sk = 0; sk < 3; ++sk) side[f][sk] = sF[f][sk * K + c][lane];
+            } else {
+                auto face = [&](int f, const auto& F, T al) {
+                    lf_face<Q>(F, al, [&](int mu, int v, T* D) { D[0] = FV[f][mu][v]; }, side[f]);
+                };
+#pragma unroll
+                for (int sk = 0; sk < 3; ++sk) side[0][sk] = side[1][sk] = 0;
+                if (inner) {
+                    face(0, FXf, -ax);
+                    face(1, FXf, ax);
+                }
+                face(2, FYf, -ay);
+                face(3, FYf, ay);
+            }
+            // ---- S: residual and RK stage of row r-1 ------------------------
+            // The derivative fluxes are differenced in T: the difference of
+            // two T values rounded to T is what a wider difference rounds to.
+            {
                 TA xdu = 0, gyu = 0;
                 T xdd[2], gyd[2];
 #pragma unroll
                 for (int sk = 0; sk < 3; ++sk) {
-                    T fr = edge_sum<T, Q>([&](int mu) { return FX(mu, sk * K + c, lane); });
-                    T g = edge_sum<T, Q>([&](int mu) { return FY(mu, sk * K + c, lane); });
-                    // the left edge's sum is the left lane's right-edge sum,
-                    // taken by a lane shift instead of further LDS reads
-                    T fl = from_left(fr);
+                    const T fr = side[1][sk] + from_right(side[0][sk]);   // right edge
+                    const T fl = from_left(fr);                           // left edge
+                    const T g = top_prev[sk] + side[2][sk];               // edge to row r-1
+                    top_prev[sk] = side[3][sk];
                     if (sk == 0) {
                         xdu = (TA)fr - (TA)fl;
                         gyu = (TA)g;
@@ -637,7 +652,18 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, Q, mode, V>()))
                                 plane_at(Ow, oo) = (TD)((T)0.75 * hwr + (T)0.25 * (hat_prev[1] + dtt * Lw));
                             } else {
                                 const TA third = (TA)(1.0 / 3.0), two3 = (TA)(2.0 / 3.0);
-                                plane_at(Ou, oo) = (TU)(third * unr + two3 * (ucur + dta * Lu));
+                                const TU nu = (TU)(third * unr + two3 * (ucur + dta * Lu));
+                                plane_at(Ou, oo) = nu;
+                                if constexpr (!SHARE) {
+                                    const double w = (double)nu;
+                                    double sx, sy;
+                                    if (wave_speed<FLUX, 2, K>(&w, sch, sx, sy)) {
+                                        mxl = fmax(mxl, sx);
+                                        myl = fmax(myl, sy);
+                                    } else {
+                                        badl = min(badl, (long long)oo);
+                                    }
+                                }
                                 plane_at(Ov, oo) = (TD)((T)(1.0 / 3.0) * hvr +
                                               (T)(2.0 / 3.0) * (hat_prev[0] + dtt * Lv));
                                 plane_at(Ow, oo) = (TD)((T)(1.0 / 3.0) * hwr +
@@ -667,24 +693,30 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, Q, mode, V>()))
             vm = v0; v0 = vp; vp = vn_;
             wm = w0; w0 = wp; wp = wn_;
         }
-        __syncthreads();  // LDS reuse by the next tile; the tile's stores are visible
-        if (fuse_alpha) {
-            gather_tile_speeds<TU, FLUX, K>((const TU*)a.out.u + off_u, (uint32_t)plane, nx, tile.i0,
-                                            j0, jend, sch, smx, smy, sbad);
-            __syncthreads();
+        if constexpr (SHARE) __syncthreads();  // LDS reuse by the next tile; the stores are visible
+        if constexpr (S3) {
+            if constexpr (SHARE) {
+                gather_tile_speeds<TU, FLUX, K>((const TU*)a.out.u + off_u, (uint32_t)plane, nx,
+                                                tile.i0, j0, jend, sch, smx, smy, sbad);
+                __syncthreads();
+            } else {
+                mxl = wave_max_d(mxl);
+                myl = wave_max_d(myl);
+                if (__any(badl != LLONG_MAX)) badl = wave_min_ll(badl);
+            }
             if (threadIdx.x < 64) {
                 // the tile is read again rather than held through the march
                 const volatile Tile2D* t = &tiles[tix];
                 const int prob = t->prob, slot = t->slot;
-                double mx = smx[0], my = smy[0];
-                long long bad = sbad[0];
+                if constexpr (SHARE) {
 #pragma unroll
-                for (int v = 1; v < K; ++v) {
-                    mx = fmax(mx, smx[v]);
-                    my = fmax(my, smy[v]);
-                    bad = sbad[v] < bad ? sbad[v] : bad;
+                    for (int v = 0; v < K; ++v) {
+                        mxl = fmax(mxl, smx[v]);
+                        myl = fmax(myl, smy[v]);
+                        badl = min(badl, sbad[v]);
+                    }
                 }
-                publish_and_end(&a.probs[prob], prob, slot, a.ctl, a.flags, 1, mx, my, bad);
+                publish_and_end(&a.probs[prob], prob, slot, a.ctl, a.flags, 1, mxl, myl, badl);
             }
         }
     }
