@@ -137,9 +137,9 @@ int split_rows(const hweno_problem* probs, int32_t nprob, const hweno_config& cf
     constexpr int64_t NCU = 256;
     const bool euler = probs[0].flux == HWENO_EULER, f64 = cfg.precision == HWENO_F64;
     // workgroups that fit a CU (registers and LDS of the kernels)
+    const int q3 = cfg.gauss_q == 3 ? 1 : 0;
     const int slots = !euler ? 12
-                             : cfg.characteristic ? (f64 ? 1 : 2)
-                                                  : (f64 ? 3 : 5) - (cfg.gauss_q == 3 ? 1 : 0);
+                             : cfg.characteristic ? (f64 ? 1 : 3 - q3) : (f64 ? 3 : 5) - q3;
     const double g = euler ? 0.43 : 0.15;
     auto tiles = [&](int rows) {
         int64_t n = 0;

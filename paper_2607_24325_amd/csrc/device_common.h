@@ -478,7 +478,7 @@ __device__ __attribute__((noinline)) inline void publish_and_end(ProbDev* P, int
 }
 
 // Wave speeds of the cell averages a stage-3 launch has just written for one
-// 2D tile (rows [j0, jend), output columns [i0, i0 + STRIP_OUT) within the
+// 2D Euler tile (rows [j0, jend), output columns [i0, i0 + STRIP_OUT) within the
 // problem), gathered after the tile's march by every wave of the workgroup:
 // wave w reads a contiguous share of the rows (they come from the L2 the
 // march's stores went through, or from HBM), lane l column i0 + l, and
@@ -489,11 +489,14 @@ __device__ __attribute__((noinline)) inline void publish_and_end(ProbDev* P, int
 // one entry per wave.  Not inlined: its FP64 division chains would otherwise
 // raise the register allocation of the whole march (and it stays within the
 // registers a call may use without saving any: no scratch).
-template <class TU, int FLUX, int K>
-__device__ __attribute__((noinline)) void gather_tile_speeds(const TU* out_u, uint32_t plane, int nx,
-                                                   int i0, int j0, int jend,
-                                                   const Scheme& sch, double* s_mx, double* s_my,
-                                                   long long* s_bad) {
+template <class TU>
+__device__ __attribute__((noinline)) void gather_tile_speeds(const TU* out_u, uint32_t plane, int nx, int i0,
+                                                             int j0, int jend, double gas_gamma,
+                                                             double* s_mx, double* s_my,
+                                                             long long* s_bad) {
+    constexpr int K = 4;
+    Scheme sch;
+    sch.gas_gamma = gas_gamma;
     // the planes are global memory (global rather than flat loads) at
     // wave-uniform bases (scalar registers, 32-bit offsets per lane)
     using GC = const __attribute__((address_space(1))) char;
@@ -528,7 +531,7 @@ __device__ __attribute__((noinline)) void gather_tile_speeds(const TU* out_u, ui
         load(min(j + 1, rb - 1));
         if (col) {
             double sx, sy;
-            if (wave_speed<FLUX, 2, K>(u, sch, sx, sy)) {
+            if (wave_speed<F_EULER, 2, K>(u, sch, sx, sy)) {
                 mx = fmax(mx, sx);
                 my = fmax(my, sy);
             } else {
@@ -671,25 +674,6 @@ template <class T, int K> struct Eigen {
         if (i == 1) return kc == 0 ? vn - c : (kc == 3 ? vn + c : (kc == 1 ? vn : (T)0));
         if (K == 4 && i == 2) return kc == 2 ? (T)1 : vt;
         return kc == 0 ? H - vn * c : (kc == 3 ? H + vn * c : (kc == 1 ? hq2 : vt));
-    }
-    // row i of L or of R for a run-time (wave-uniform) i
-    __device__ __forceinline__ void lrow(int i, T* out) const {
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            T v = L(K - 1, k);
-#pragma unroll
-            for (int j = K - 2; j >= 0; --j) v = i == j ? L(j, k) : v;
-            out[k] = v;
-        }
-    }
-    __device__ __forceinline__ void rrow(int i, T* out) const {
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            T v = R(K - 1, k);
-#pragma unroll
-            for (int j = K - 2; j >= 0; --j) v = i == j ? R(j, k) : v;
-            out[k] = v;
-        }
     }
     // w = L x and x = R w (vectors in the (rho, m_n, [m_t,] E) order)
     __device__ __forceinline__ void left(const T* x, T* w) const {

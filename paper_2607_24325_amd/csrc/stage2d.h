@@ -51,10 +51,6 @@ template <> struct Gauss<3> {
 // goes into 1/dx and 1/dy: the sum over an edge's points costs no product
 // (Q = 2) or one.
 template <int Q> constexpr double WSUM = Q == 2 ? 0.25 : 5.0 / 36.0;
-template <class T, int Q, class F> __device__ __forceinline__ T edge_sum(F f) {
-    if constexpr (Q == 2) return f(0) + f(1);
-    else return fused((T)1.6, f(1), f(0) + f(2));
-}
 
 // Appendix A coefficients c_{0,1..15} (0..14 here) of the quartic p0 in terms
 // of q_1..q_17, written with the centre average subtracted from the nine
@@ -242,48 +238,10 @@ template <class T> __device__ __forceinline__ void transpose15(const T* C, T* D)
     D[12] = C[12]; D[13] = C[11]; D[14] = C[10];
 }
 
-// Lax-Friedrichs flux at one edge point, all components, TWICE its value:
-// out = 2 (f, f^v, f^w) = (f(L) + alpha L) + (f(R) - alpha R).  The factor
-// 1/2 is folded into the weights of the residual; the two sides are
-// accumulated one after the other, so that only one side's values and fluxes
-// are live at a time.
-template <class T, int FLUX, int K, int DIR>
-__device__ __forceinline__ void lf_edge(const Flux<T, FLUX, K, DIR>& F, const T* UL, const T* VL,
-                                        const T* WL, const T* UR, const T* VR, const T* WR,
-                                        T alpha, T* out) {
-    if constexpr (FLUX == F_EULER && K == 4) {
-        const auto L = F.prim(UL, alpha);
-        F.template flux<true>(UL, L, alpha, out);
-        F.template jvp<true>(VL, L, alpha, out + K);
-        F.template jvp<true>(WL, L, alpha, out + 2 * K);
-        const auto R = F.prim(UR, -alpha);
-        F.template flux<false>(UR, R, -alpha, out);
-        F.template jvp<false>(VR, R, -alpha, out + K);
-        F.template jvp<false>(WR, R, -alpha, out + 2 * K);
-        return;
-    } else {
-        T f[K], fv[K], fw[K];
-        F.side(UL, VL, WL, f, fv, fw);
-#pragma unroll
-        for (int c = 0; c < K; ++c) {
-            out[c] = f[c] + alpha * UL[c];
-            out[K + c] = fv[c] + alpha * VL[c];
-            out[2 * K + c] = fw[c] + alpha * WL[c];
-        }
-        F.side(UR, VR, WR, f, fv, fw);
-#pragma unroll
-        for (int c = 0; c < K; ++c) {
-            out[c] = (out[c] + f[c]) - alpha * UR[c];
-            out[K + c] = (out[K + c] + fv[c]) - alpha * VR[c];
-            out[2 * K + c] = (out[2 * K + c] + fw[c]) - alpha * WR[c];
-        }
-    }
-}
-
 // One side of the Lax-Friedrichs flux at a face's Gauss point, TWICE its
 // value: f(U) + al U (al = alpha for a cell's right or top face, -alpha for its
-// left or bottom one) and the same of the derivative fluxes; FIRST starts the
-// sum over the points.  ld(v, D): the face's values of kind v.
+// left or bottom one) and the same of the derivative fluxes; the 1/2 is folded
+// into the residual's factors.  FIRST starts the sum over the points.  ld(v, D): the face's values of kind v.
 template <bool FIRST, class T, int FLUX, int K, int DIR, class LD>
 __device__ __forceinline__ void lf_side(const Flux<T, FLUX, K, DIR>& F, T al, LD ld, T* out) {
     if constexpr (FLUX == F_EULER && K == 4) {
@@ -324,6 +282,22 @@ __device__ __forceinline__ void lf_face(const Flux<T, FLUX, K, DIR>& F, T al, LD
         lf_side<false>(F, al, at(0), out);
         lf_side<false>(F, al, at(2), out);
     }
+}
+
+// One wave: the maxima that gather_tile_speeds left and the end of the tile's step.
+template <int K>
+__device__ __forceinline__ void publish_gathered(const StageArgs& a, int prob, int slot,
+                                                 const double* smx, const double* smy,
+                                                 const long long* sbad) {
+    double mx = smx[0], my = smy[0];
+    long long bad = sbad[0];
+#pragma unroll
+    for (int v = 1; v < K; ++v) {
+        mx = fmax(mx, smx[v]);
+        my = fmax(my, smy[v]);
+        bad = min(bad, sbad[v]);
+    }
+    publish_and_end(&a.probs[prob], prob, slot, a.ctl, a.flags, 1, mx, my, bad);
 }
 
 // Workgroups per CU the register allocation is made for (launch bounds).
@@ -696,8 +670,8 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, K, Q, V>())) st
         if constexpr (SHARE) __syncthreads();  // LDS reuse by the next tile; the stores are visible
         if constexpr (S3) {
             if constexpr (SHARE) {
-                gather_tile_speeds<TU, FLUX, K>((const TU*)a.out.u + off_u, (uint32_t)plane, nx,
-                                                tile.i0, j0, jend, sch, smx, smy, sbad);
+                gather_tile_speeds<TU>((const TU*)a.out.u + off_u, (uint32_t)plane, nx, tile.i0, j0,
+                                       jend, sch.gas_gamma, smx, smy, sbad);
                 __syncthreads();
             } else {
                 mxl = wave_max_d(mxl);
@@ -708,15 +682,8 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, K, Q, V>())) st
                 // the tile is read again rather than held through the march
                 const volatile Tile2D* t = &tiles[tix];
                 const int prob = t->prob, slot = t->slot;
-                if constexpr (SHARE) {
-#pragma unroll
-                    for (int v = 0; v < K; ++v) {
-                        mxl = fmax(mxl, smx[v]);
-                        myl = fmax(myl, smy[v]);
-                        badl = min(badl, sbad[v]);
-                    }
-                }
-                publish_and_end(&a.probs[prob], prob, slot, a.ctl, a.flags, 1, mxl, myl, badl);
+                if constexpr (SHARE) publish_gathered<K>(a, prob, slot, smx, smy, sbad);
+                else publish_and_end(&a.probs[prob], prob, slot, a.ctl, a.flags, 1, mxl, myl, badl);
             }
         }
     }
