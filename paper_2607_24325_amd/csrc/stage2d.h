@@ -307,7 +307,7 @@ __device__ __forceinline__ void publish_gathered(const StageArgs& a, int prob, i
 // 164 in FP64) and the LDS of the faces; variant 1: one workgroup more per CU,
 // which caps the registers lower (the compiler may spill).  The tuner picks.
 template <int P, int K, int Q, int V> constexpr int stage2d_min_blocks() {
-    if (P == P_F64) return Q == 3 || K == 1 ? 2 + V : 3;
+    if (P == P_F64) return Q == 3 || K == 1 ? 2 : 3;   // LDS allows no more
     return V + (Q == 3 || K == 1 ? 4 : 5);
 }
 
