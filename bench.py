@@ -42,161 +42,161 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 # kernel sources of this hash; any change of the sources
 # invalidates them, and a configuration not profiled has none (both are
 # reported as null).
-PROFILED_SOURCES = "12f6670ea8fd1413"
+PROFILED_SOURCES = "511590bac50e3d3b"
 # path, tile_rows, grid_blocks, variant: HBM MB and VALU wave-instructions (M)
-# per stage launch, mean of the three stages, for every launch configuration
+# per stage, mean of the three stages (in 1D a third of the step kernel's), for every launch configuration
 # the tuner can choose (one eager step each; 2048^2 workload, 4096-problem 1D
 # batch, where segment heights do not apply, 256-problem 2D batch)
 _PROFILED_TABLE = """
-f32acc64 16 0 0 893.7 156.70
-f32acc64 16 512 0 840.4 155.83
-f32acc64 16 768 0 888.3 155.89
-f32acc64 16 1024 0 904.8 155.94
-f32acc64 24 0 0 878.7 150.91
-f32acc64 24 512 0 850.1 150.37
-f32acc64 24 768 0 884.3 150.42
-f32acc64 24 1024 0 897.1 150.48
-f32acc64 32 0 0 870.3 147.88
-f32acc64 32 512 0 849.8 147.50
-f32acc64 32 768 0 877.1 147.56
-f32acc64 32 1024 0 894.1 147.61
-f32acc64 48 0 0 865.6 144.99
-f32acc64 48 512 0 850.7 144.77
-f32acc64 48 768 0 871.2 144.82
-f32acc64 48 1024 0 882.4 144.88
-f32acc64 64 0 0 866.9 143.47
-f32acc64 64 512 0 845.6 143.34
-f32acc64 64 768 0 859.2 143.39
-f32acc64 64 1024 0 870.0 143.45
-f32acc64 16 0 1 2349.0 159.98
-f32acc64 16 512 1 1101.0 159.13
-f32acc64 16 768 1 1608.1 159.18
-f32acc64 16 1024 1 2184.5 159.24
-f32acc64 24 0 1 2320.8 154.15
-f32acc64 24 512 1 1053.0 153.62
-f32acc64 24 768 1 1535.8 153.67
-f32acc64 24 1024 1 2170.2 153.73
-f32acc64 32 0 1 2281.0 151.10
-f32acc64 32 512 1 1032.5 150.73
-f32acc64 32 768 1 1508.2 150.78
-f32acc64 32 1024 1 2082.7 150.84
-f32acc64 48 0 1 2202.1 148.18
-f32acc64 48 512 1 1019.2 147.97
-f32acc64 48 768 1 1467.5 148.02
-f32acc64 48 1024 1 1805.9 148.08
-f32acc64 64 0 1 2236.1 146.66
-f32acc64 64 512 1 1001.5 146.53
-f32acc64 64 768 1 1353.1 146.58
-f32acc64 64 1024 1 2048.3 146.64
-f32acc64 36 0 0 869.5 146.91
-f32acc64 36 0 1 2099.0 150.13
-f64 16 0 0 1342.3 178.61
-f64 16 512 0 1331.7 177.33
-f64 16 768 0 1355.1 177.41
-f64 16 1024 0 1368.5 177.49
-f64 24 0 0 1312.9 171.81
-f64 24 512 0 1313.8 171.00
-f64 24 768 0 1329.5 171.09
-f64 24 1024 0 1323.7 171.17
-f64 32 0 0 1296.9 168.25
-f64 32 512 0 1317.1 167.69
-f64 32 768 0 1324.5 167.77
-f64 32 1024 0 1319.5 167.86
-f64 48 0 0 1286.7 164.85
-f64 48 512 0 1305.2 164.53
-f64 48 768 0 1306.9 164.61
-f64 48 1024 0 1309.9 164.69
-f64 64 0 0 1283.0 163.07
-f64 64 512 0 1306.8 162.87
-f64 64 768 0 1304.1 162.96
-f64 64 1024 0 1287.2 163.04
-f64 16 0 1 1341.2 178.91
-f64 16 512 1 1333.7 177.65
-f64 16 768 1 1358.0 177.73
-f64 16 1024 1 1368.8 177.81
-f64 24 0 1 1313.6 172.14
-f64 24 512 1 1313.9 171.34
-f64 24 768 1 1330.5 171.42
-f64 24 1024 1 1321.3 171.51
-f64 32 0 1 1297.5 168.59
-f64 32 512 1 1313.1 168.04
-f64 32 768 1 1323.7 168.12
-f64 32 1024 1 1318.9 168.20
-f64 48 0 1 1286.9 165.20
-f64 48 512 1 1300.6 164.89
-f64 48 768 1 1307.3 164.97
-f64 48 1024 1 1311.1 165.05
-f64 64 0 1 1284.8 163.43
-f64 64 512 1 1304.0 163.24
-f64 64 768 1 1304.2 163.32
-f64 64 1024 1 1291.2 163.40
-f64 36 0 0 1294.1 167.12
-f64 36 0 1 1293.8 167.46
-f32acc64_characteristic 16 0 0 801.8 373.73
-f32acc64_characteristic 16 512 0 839.2 372.39
-f32acc64_characteristic 16 768 0 862.6 372.48
-f32acc64_characteristic 16 1024 0 867.9 372.56
-f32acc64_characteristic 24 0 0 821.8 361.13
-f32acc64_characteristic 24 512 0 817.9 360.28
-f32acc64_characteristic 24 768 0 839.4 360.37
-f32acc64_characteristic 24 1024 0 835.9 360.46
-f32acc64_characteristic 32 0 0 814.2 354.53
-f32acc64_characteristic 32 512 0 810.7 353.94
-f32acc64_characteristic 32 768 0 828.3 354.03
-f32acc64_characteristic 32 1024 0 828.5 354.11
-f32acc64_characteristic 48 0 0 805.9 348.22
-f32acc64_characteristic 48 512 0 808.0 347.89
-f32acc64_characteristic 48 768 0 812.7 347.97
-f32acc64_characteristic 48 1024 0 814.0 348.06
-f32acc64_characteristic 64 0 0 799.5 344.92
-f32acc64_characteristic 64 512 0 800.2 344.72
-f32acc64_characteristic 64 768 0 801.9 344.80
-f32acc64_characteristic 64 1024 0 800.1 344.89
-f32acc64_characteristic 36 0 0 812.9 352.43
-batched_1d 0 0 0 1857.4 145.15
-batched_1d 0 512 0 1858.0 135.52
-batched_1d 0 1024 0 1858.9 135.59
-batched_1d 0 2048 0 1861.0 135.73
-batched_2d 16 0 0 22914.4 4788.12
-batched_2d 16 512 0 27014.1 4762.48
-batched_2d 16 768 0 26950.1 4762.53
-batched_2d 16 1024 0 27213.5 4762.59
-batched_2d 24 0 0 22661.0 4629.75
-batched_2d 24 512 0 26289.6 4612.60
-batched_2d 24 768 0 26394.3 4612.66
-batched_2d 24 1024 0 26601.3 4612.71
-batched_2d 32 0 0 22756.4 4550.91
-batched_2d 32 512 0 26031.2 4537.99
-batched_2d 32 768 0 26139.6 4538.04
-batched_2d 32 1024 0 26378.1 4538.10
-batched_2d 48 0 0 23088.0 4471.57
-batched_2d 48 512 0 25638.5 4462.89
-batched_2d 48 768 0 25739.1 4462.95
-batched_2d 48 1024 0 25911.7 4463.00
-batched_2d 64 0 0 23545.5 4432.00
-batched_2d 64 512 0 25143.9 4425.45
-batched_2d 64 768 0 25516.7 4425.50
-batched_2d 64 1024 0 25782.4 4425.56
-batched_2d 16 0 1 52423.3 4803.91
-batched_2d 16 512 1 31315.1 4778.75
-batched_2d 16 768 1 41837.8 4778.80
-batched_2d 16 1024 1 55597.2 4778.86
-batched_2d 24 0 1 51582.9 4645.29
-batched_2d 24 512 1 29843.7 4628.46
-batched_2d 24 768 1 40691.1 4628.51
-batched_2d 24 1024 1 54362.9 4628.57
-batched_2d 32 0 1 51334.6 4566.32
-batched_2d 32 512 1 29146.4 4553.63
-batched_2d 32 768 1 39965.0 4553.69
-batched_2d 32 1024 1 53750.0 4553.74
-batched_2d 48 0 1 51366.1 4486.85
-batched_2d 48 512 1 28322.5 4478.33
-batched_2d 48 768 1 39269.2 4478.38
-batched_2d 48 1024 1 53096.4 4478.44
-batched_2d 64 0 1 51527.3 4447.22
-batched_2d 64 512 1 27901.3 4440.78
-batched_2d 64 768 1 38862.9 4440.84
-batched_2d 64 1024 1 52380.7 4440.89
+f32acc64 16 0 0 900.4 133.45
+f32acc64 16 512 0 840.6 133.08
+f32acc64 16 768 0 887.3 133.11
+f32acc64 16 1024 0 907.8 133.13
+f32acc64 24 0 0 885.8 128.86
+f32acc64 24 512 0 849.5 128.63
+f32acc64 24 768 0 882.7 128.65
+f32acc64 24 1024 0 898.6 128.68
+f32acc64 32 0 0 883.5 127.23
+f32acc64 32 512 0 846.8 126.30
+f32acc64 32 768 0 875.9 126.32
+f32acc64 32 1024 0 891.7 126.35
+f32acc64 48 0 0 886.0 127.23
+f32acc64 48 512 0 853.3 124.07
+f32acc64 48 768 0 871.5 124.10
+f32acc64 48 1024 0 881.0 124.12
+f32acc64 64 0 0 886.4 123.40
+f32acc64 64 512 0 844.7 122.91
+f32acc64 64 768 0 855.7 122.93
+f32acc64 64 1024 0 872.4 122.96
+f32acc64 16 0 1 1460.8 133.55
+f32acc64 16 512 1 920.0 133.18
+f32acc64 16 768 1 993.5 133.21
+f32acc64 16 1024 1 1107.9 133.23
+f32acc64 24 0 1 1471.0 128.96
+f32acc64 24 512 1 899.7 128.73
+f32acc64 24 768 1 954.7 128.75
+f32acc64 24 1024 1 1059.1 128.78
+f32acc64 32 0 1 1325.3 127.32
+f32acc64 32 512 1 902.2 126.40
+f32acc64 32 768 1 952.1 126.42
+f32acc64 32 1024 1 1055.9 126.44
+f32acc64 48 0 1 1328.1 127.32
+f32acc64 48 512 1 891.3 124.17
+f32acc64 48 768 1 932.5 124.19
+f32acc64 48 1024 1 990.0 124.22
+f32acc64 64 0 1 1208.7 123.50
+f32acc64 64 512 1 892.2 123.00
+f32acc64 64 768 1 902.4 123.03
+f32acc64 64 1024 1 1010.3 123.05
+f32acc64 36 0 0 884.5 127.23
+f32acc64 36 0 1 1327.9 127.32
+f64 16 0 0 1338.2 153.94
+f64 16 512 0 1324.0 153.09
+f64 16 768 0 1349.1 153.14
+f64 16 1024 0 1361.3 153.20
+f64 24 0 0 1311.7 148.37
+f64 24 512 0 1302.0 147.83
+f64 24 768 0 1318.8 147.89
+f64 24 1024 0 1314.8 147.94
+f64 32 0 0 1295.6 145.45
+f64 32 512 0 1296.0 145.08
+f64 32 768 0 1306.0 145.13
+f64 32 1024 0 1308.9 145.19
+f64 48 0 0 1284.3 142.66
+f64 48 512 0 1286.1 142.45
+f64 48 768 0 1294.9 142.51
+f64 48 1024 0 1295.9 142.56
+f64 64 0 0 1283.7 142.66
+f64 64 512 0 1281.2 141.07
+f64 64 768 0 1290.2 141.13
+f64 64 1024 0 1280.8 141.18
+f64 16 0 1 1339.0 153.94
+f64 16 512 1 1329.8 153.09
+f64 16 768 1 1353.7 153.14
+f64 16 1024 1 1363.9 153.20
+f64 24 0 1 1313.5 148.37
+f64 24 512 1 1303.7 147.83
+f64 24 768 1 1321.3 147.89
+f64 24 1024 1 1316.6 147.94
+f64 32 0 1 1297.1 145.45
+f64 32 512 1 1297.4 145.08
+f64 32 768 1 1307.6 145.13
+f64 32 1024 1 1311.5 145.19
+f64 48 0 1 1284.7 142.66
+f64 48 512 1 1285.1 142.45
+f64 48 768 1 1294.7 142.51
+f64 48 1024 1 1296.9 142.56
+f64 64 0 1 1284.0 142.66
+f64 64 512 1 1282.3 141.07
+f64 64 768 1 1289.3 141.13
+f64 64 1024 1 1283.0 141.18
+f64 36 0 0 1292.8 144.52
+f64 36 0 1 1292.8 144.52
+f32acc64_characteristic 16 0 0 890.3 257.02
+f32acc64_characteristic 16 512 0 847.5 256.22
+f32acc64_characteristic 16 768 0 884.1 256.27
+f32acc64_characteristic 16 1024 0 896.6 256.33
+f32acc64_characteristic 24 0 0 874.8 250.62
+f32acc64_characteristic 24 512 0 850.8 250.11
+f32acc64_characteristic 24 768 0 872.8 250.16
+f32acc64_characteristic 24 1024 0 878.1 250.22
+f32acc64_characteristic 32 0 0 863.2 247.26
+f32acc64_characteristic 32 512 0 852.6 246.91
+f32acc64_characteristic 32 768 0 865.4 246.96
+f32acc64_characteristic 32 1024 0 870.3 247.02
+f32acc64_characteristic 48 0 0 854.5 244.06
+f32acc64_characteristic 48 512 0 851.5 243.86
+f32acc64_characteristic 48 768 0 858.6 243.91
+f32acc64_characteristic 48 1024 0 859.4 243.96
+f32acc64_characteristic 64 0 0 854.5 244.06
+f32acc64_characteristic 64 512 0 845.4 242.26
+f32acc64_characteristic 64 768 0 850.6 242.31
+f32acc64_characteristic 64 1024 0 850.2 242.36
+f32acc64_characteristic 36 0 0 861.3 246.19
+batched_1d 0 0 0 489.6 133.77
+batched_1d 0 512 0 489.9 131.57
+batched_1d 0 1024 0 489.9 131.58
+batched_1d 0 2048 0 490.2 131.59
+batched_2d 16 0 0 22965.4 4201.52
+batched_2d 16 512 0 25731.2 4190.50
+batched_2d 16 768 0 26817.7 4190.53
+batched_2d 16 1024 0 26979.0 4190.55
+batched_2d 24 0 0 22634.1 4073.25
+batched_2d 24 512 0 25239.6 4065.89
+batched_2d 24 768 0 26319.2 4065.91
+batched_2d 24 1024 0 26379.7 4065.93
+batched_2d 32 0 0 22531.8 4009.40
+batched_2d 32 512 0 24636.6 4003.84
+batched_2d 32 768 0 25913.0 4003.87
+batched_2d 32 1024 0 25995.6 4003.89
+batched_2d 48 0 0 22546.1 3945.13
+batched_2d 48 512 0 24153.7 3941.40
+batched_2d 48 768 0 25601.3 3941.43
+batched_2d 48 1024 0 25647.2 3941.45
+batched_2d 64 0 0 22729.2 3913.08
+batched_2d 64 512 0 23876.1 3910.27
+batched_2d 64 768 0 25496.7 3910.29
+batched_2d 64 1024 0 25443.3 3910.31
+batched_2d 16 0 1 32156.0 4201.63
+batched_2d 16 512 1 25187.3 4190.78
+batched_2d 16 768 1 27642.5 4190.80
+batched_2d 16 1024 1 30374.3 4190.83
+batched_2d 24 0 1 32151.2 4073.33
+batched_2d 24 512 1 24747.3 4066.07
+batched_2d 24 768 1 26949.8 4066.09
+batched_2d 24 1024 1 29618.6 4066.12
+batched_2d 32 0 1 32353.0 4009.46
+batched_2d 32 512 1 24374.2 4003.98
+batched_2d 32 768 1 26666.7 4004.01
+batched_2d 32 1024 1 29130.6 4004.03
+batched_2d 48 0 1 32879.3 3945.17
+batched_2d 48 512 1 23936.4 3941.49
+batched_2d 48 768 1 26262.6 3941.52
+batched_2d 48 1024 1 28683.9 3941.54
+batched_2d 64 0 1 33312.0 3913.11
+batched_2d 64 512 1 23830.6 3910.34
+batched_2d 64 768 1 26110.9 3910.36
+batched_2d 64 1024 1 28436.5 3910.38
 """
 PROFILED = {(p, int(r), int(g), int(v)): (float(t) * 1e6, float(a) * 1e6)
             for p, r, g, v, t, a in (ln.split() for ln in _PROFILED_TABLE.strip().splitlines())}
@@ -206,16 +206,20 @@ def kernel_sources_hash() -> str:
     import hashlib
     d = os.path.join(ROOT, "paper_2607_24325_amd", "csrc")
     src = "".join(open(os.path.join(d, f)).read()
-                  for f in ("stage2d.h", "stage2d_char.h", "stage1d.h", "device_common.h", "ff.h",
-                            "internal.h"))
+                  for f in ("stage2d.h", "stage2d_char.h", "stage1d.h", "step1d.h", "device_common.h",
+                            "ff.h", "internal.h"))
     return hashlib.sha256(src.encode()).hexdigest()[:16]
 
 
 def algorithmic_bytes_per_cell_stage(K: int, D: int, su: int, sd: int) -> float:
     """Compulsory HBM traffic per cell per stage, averaged over the three
     stages: stage 1 reads U^n and writes U^(1) and the saved hats H; stages 2
-    and 3 read U^(k), u-bar^n and H and write U^(k+1)."""
+    and 3 read U^(k), u-bar^n and H and write U^(k+1).  The 1D step kernel
+    holds the state in registers through its three stages: it reads and
+    writes one set a step."""
     S = K * (su + D * sd)
+    if D == 1:
+        return 2 * S / 3.0
     H = K * D * sd
     return (6 * S + 3 * H + 2 * K * su) / 3.0
 
@@ -558,9 +562,9 @@ def profile_candidates(hw, W):
     workload in F32_ACC64, FP64 and characteristic variables, the
     4096-problem 1D batch and the 256-problem 2D batch (F32_KAHAN).  Prints
     the order as JSON lines (one untimed step per path first, marked
-    "warm"): under `rocprofv3 --pmc` the stage-kernel dispatches come three
-    per step in that order, which is how the PROFILED table above was
-    measured."""
+    "warm"): under `rocprofv3 --pmc` the kernel dispatches come in that order,
+    three stages per step in 2D and one step kernel in 1D, which is how the
+    PROFILED table above was measured."""
     spec, st = W.quadrant_vortex_2d(2048, seed=7)
     for name, prec, charwise in (("f32acc64", hw.F32_ACC64, 0), ("f64", hw.F64, 0),
                                  ("f32acc64_characteristic", hw.F32_ACC64, 1)):

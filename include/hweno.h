@@ -9,7 +9,8 @@
  * Sec. 2.2: scaled averages v-bar = (1/dy) int u_x, w-bar = (1/dx) int u_y).
  * One handle holds one or many independent problems (same dimension, flux
  * family and configuration; any sizes, domains, boundaries and end times);
- * every RK stage of every problem of a handle is one kernel launch.
+ * a step of every problem of a handle is one kernel launch in 1D and three
+ * (one per RK stage) in 2D; small 1D problems take many steps per launch.
  *
  * Conventions for every call:
  *   - Returns HWENO_OK (0) or a negative HWENO_ERR_* status; never aborts.
@@ -195,7 +196,8 @@ int hweno_step(hweno_handle* h, const double* dt_in, double* dt_out);
 /* nsteps steps (Sec. 2.1 Step 4, Sec. 2.2 Step 4) with the CFL rule, each
  * as hweno_step(h, NULL, NULL) would take it (problems at their t_end do not
  * move).  Only enqueues.  In graph mode, runs of 8 steps are replayed as one
- * graph, which spares the launch gaps between graphs.  Errors: ERR_ARG for
+ * graph, which spares the launch gaps between graphs; where every problem is
+ * 1D with at most 416 cells, all nsteps are one launch.  Errors: ERR_ARG for
  * nsteps < 0, ERR_STATE before set_state. */
 int hweno_steps(hweno_handle* h, int32_t nsteps);
 
@@ -217,8 +219,9 @@ int hweno_sync(hweno_handle* h);
  * by the kernel); grid_blocks: workgroups of the persistent launch
  * (0 = one per tile); use_graph: capture steps as HIP graphs (1) or launch
  * eagerly (0); variant: register allocation of the 2D Euler stage kernels
- * (0: for the occupancy their face arrays comfortably allow; 1: for one
- * workgroup more per CU, with fewer registers; ignored elsewhere); source
+ * (0: for the occupancy that their registers and LDS allow; 1: in single
+ * precision for one workgroup more per CU, with fewer registers; ignored
+ * elsewhere); source
  * (read only): where the configuration came from (HWENO_TUNED_*).  Changing
  * any of these never changes a result bit. */
 typedef struct {
@@ -264,9 +267,10 @@ int hweno_tuning_candidates(hweno_handle* h, hweno_tuning* out, int32_t cap, int
 
 /* Per-kernel timing of nsteps steps (CFL rule), launched eagerly on the
  * handle's stream with a HIP event pair around every kernel.  Synchronising.
- * total_ms: first to last event; stage_ms: sum of the fused stage kernels;
- * alpha_ms: wave-speed reductions (none once stage 3 has gathered the
- * speeds); other_ms: dt and time-update kernels. */
+ * total_ms: first to last event; stage_ms: sum of the fused stage and step
+ * kernels; alpha_ms: wave-speed reductions (none once stage 3 has gathered the
+ * speeds); other_ms: everything else (dt kernels with alpha_stage).
+ * stage_launches counts stages: three for a kernel that takes a whole step. */
 typedef struct {
     double total_ms;
     double stage_ms;
@@ -302,7 +306,8 @@ int hweno_timed_steps(hweno_handle* h, int32_t nsteps, hweno_timing* out);
  * call allocates nothing and copies nothing between host and device: it only
  * enqueues kernels.  A problem needs, per cell, 3 K (su + D sd) + K D sd
  * bytes (K components, D = dim, su = 8 except 4 for F32, sd = 8 for F64 and
- * 4 otherwise) plus a few KB: e.g. at most about 190 000 cells of 2D Euler
+ * 4 otherwise) plus a few KB (1D problems of at most 416 cells are stepped
+ * from state_in to state_out without it): e.g. at most about 190 000 cells of 2D Euler
  * in F64, 299 000 in F32_ACC64.
  * Every call on a GPU shares that GPU's array and leaves its contents behind
  * (each call rewrites what it reads first): calls that overlap on one GPU,

@@ -738,8 +738,9 @@ extern "C" int hweno_rhs(hweno_handle* h, int32_t prob, double* L_out, double* U
     return report_status(h, prob);
 }
 
-// One SSP-RK3 step of every unfinished problem: wave speeds and dt, three
-// fused stage kernels, time update.
+// One SSP-RK3 step of every unfinished problem: wave speeds where they are not
+// known, then the step kernel (1D) or three stage kernels (2D, and 1D with the
+// speeds of every stage), which choose dt and end the step themselves.
 // The launches of one step, in order; rec(kind, launch) issues each one
 // (and may bracket it with events).
 enum LaunchKind { LK_OTHER = 0, LK_ALPHA = 1, LK_STAGE = 2, LK_STEP = 3 };  // LK_STEP: three stages
@@ -759,8 +760,7 @@ static hipError_t launch_run(hweno_handle* h, int n, int flags) {
 }
 
 // One step.  fast: no problem that can advance has stale speeds, so the
-// reduction kernel is left out (and with at most 256 problems the dt kernel
-// clears the step counters itself, which leaves out the reset kernel too).
+// reduction kernel is left out.
 template <class Rec>
 static int enqueue_step_with(hweno_handle* h, int use_dt_in, bool fast, Rec&& rec) {
     // with the speeds of every stage, dt comes from a kernel of its own, and

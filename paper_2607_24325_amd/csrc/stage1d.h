@@ -8,7 +8,9 @@
 // problem: it stages the 258 averages and derivative means it needs in LDS
 // (coalesced, ghost cells through the boundary index map), reconstructs 256
 // cells (one per thread, every component), computes the 255 interface
-// fluxes once each, and updates the 254 interior cells.
+// fluxes once each, and updates the 254 interior cells.  Right-hand sides and
+// the option that reduces the speeds of every stage take this path; other steps
+// take all three stages at once (step1d.h).
 #pragma once
 
 #include "device_common.h"

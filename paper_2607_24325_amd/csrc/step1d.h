@@ -14,12 +14,13 @@
 // What bounds it and why this split.  A kernel per stage moves 6 state sets,
 // three saved sets and two average sets through HBM per step (300 bytes a
 // cell in F32_ACC64, 408 in FP64); this one reads and writes the state once
-// (72 and 96 bytes): 4.2 million cells of F32_ACC64 take 202 us a step instead
-// of 354.  On small problems the launches were the time (a step was five of
-// them and is one: 4000 cells in F64, 10.9 us instead of 24).  CPT trades halo
-// work (12 of 64 or 128 cells) against the length of a lane's serial chain and
-// its registers (142 and 237 in F64, 104 and 163 in F32_ACC64); see
-// step1d_cells.
+// (72 and 96 bytes): 4.2 million cells of F32_ACC64 take 160 us a step instead
+// of 354, and are then bound by vector instructions (all issue slots taken).  On
+// small problems the launches were the time (a step was five of them and is
+// one: 4000 cells in F64, 10 us instead of 24, of which 1.1 are the loads, 3.8
+// the stages and 3.8 the atomics that end the step).  CPT trades halo work (12
+// of 64 or 128 cells) against the length of a lane's serial chain and its
+// registers (142 and 200 in F64, 94 and 128 in F32_ACC64); see step1d_cells.
 #pragma once
 
 #include "stage1d.h"
