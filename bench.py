@@ -42,161 +42,161 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 # kernel sources of this hash; any change of the sources
 # invalidates them, and a configuration not profiled has none (both are
 # reported as null).
-PROFILED_SOURCES = "511590bac50e3d3b"
+PROFILED_SOURCES = "14bd86723c6c5439"
 # path, tile_rows, grid_blocks, variant: HBM MB and VALU wave-instructions (M)
 # per stage, mean of the three stages (in 1D a third of the step kernel's), for every launch configuration
 # the tuner can choose (one eager step each; 2048^2 workload, 4096-problem 1D
 # batch, where segment heights do not apply, 256-problem 2D batch)
 _PROFILED_TABLE = """
-f32acc64 16 0 0 900.4 133.45
-f32acc64 16 512 0 840.6 133.08
-f32acc64 16 768 0 887.3 133.11
-f32acc64 16 1024 0 907.8 133.13
-f32acc64 24 0 0 885.8 128.86
-f32acc64 24 512 0 849.5 128.63
-f32acc64 24 768 0 882.7 128.65
-f32acc64 24 1024 0 898.6 128.68
-f32acc64 32 0 0 883.5 127.23
-f32acc64 32 512 0 846.8 126.30
-f32acc64 32 768 0 875.9 126.32
-f32acc64 32 1024 0 891.7 126.35
-f32acc64 48 0 0 886.0 127.23
-f32acc64 48 512 0 853.3 124.07
-f32acc64 48 768 0 871.5 124.10
-f32acc64 48 1024 0 881.0 124.12
-f32acc64 64 0 0 886.4 123.40
-f32acc64 64 512 0 844.7 122.91
-f32acc64 64 768 0 855.7 122.93
-f32acc64 64 1024 0 872.4 122.96
-f32acc64 16 0 1 1460.8 133.55
-f32acc64 16 512 1 920.0 133.18
-f32acc64 16 768 1 993.5 133.21
-f32acc64 16 1024 1 1107.9 133.23
-f32acc64 24 0 1 1471.0 128.96
-f32acc64 24 512 1 899.7 128.73
-f32acc64 24 768 1 954.7 128.75
-f32acc64 24 1024 1 1059.1 128.78
-f32acc64 32 0 1 1325.3 127.32
-f32acc64 32 512 1 902.2 126.40
-f32acc64 32 768 1 952.1 126.42
-f32acc64 32 1024 1 1055.9 126.44
-f32acc64 48 0 1 1328.1 127.32
-f32acc64 48 512 1 891.3 124.17
-f32acc64 48 768 1 932.5 124.19
-f32acc64 48 1024 1 990.0 124.22
-f32acc64 64 0 1 1208.7 123.50
-f32acc64 64 512 1 892.2 123.00
-f32acc64 64 768 1 902.4 123.03
-f32acc64 64 1024 1 1010.3 123.05
-f32acc64 36 0 0 884.5 127.23
-f32acc64 36 0 1 1327.9 127.32
-f64 16 0 0 1338.2 153.94
-f64 16 512 0 1324.0 153.09
-f64 16 768 0 1349.1 153.14
-f64 16 1024 0 1361.3 153.20
-f64 24 0 0 1311.7 148.37
-f64 24 512 0 1302.0 147.83
-f64 24 768 0 1318.8 147.89
-f64 24 1024 0 1314.8 147.94
-f64 32 0 0 1295.6 145.45
-f64 32 512 0 1296.0 145.08
-f64 32 768 0 1306.0 145.13
-f64 32 1024 0 1308.9 145.19
-f64 48 0 0 1284.3 142.66
-f64 48 512 0 1286.1 142.45
-f64 48 768 0 1294.9 142.51
-f64 48 1024 0 1295.9 142.56
-f64 64 0 0 1283.7 142.66
-f64 64 512 0 1281.2 141.07
-f64 64 768 0 1290.2 141.13
-f64 64 1024 0 1280.8 141.18
-f64 16 0 1 1339.0 153.94
-f64 16 512 1 1329.8 153.09
-f64 16 768 1 1353.7 153.14
-f64 16 1024 1 1363.9 153.20
-f64 24 0 1 1313.5 148.37
-f64 24 512 1 1303.7 147.83
-f64 24 768 1 1321.3 147.89
-f64 24 1024 1 1316.6 147.94
-f64 32 0 1 1297.1 145.45
-f64 32 512 1 1297.4 145.08
-f64 32 768 1 1307.6 145.13
-f64 32 1024 1 1311.5 145.19
-f64 48 0 1 1284.7 142.66
-f64 48 512 1 1285.1 142.45
-f64 48 768 1 1294.7 142.51
-f64 48 1024 1 1296.9 142.56
+f32acc64 16 0 0 900.8 133.45
+f32acc64 16 512 0 841.6 133.08
+f32acc64 16 768 0 886.4 133.11
+f32acc64 16 1024 0 906.8 133.13
+f32acc64 24 0 0 885.2 128.86
+f32acc64 24 512 0 848.5 128.63
+f32acc64 24 768 0 884.6 128.65
+f32acc64 24 1024 0 898.9 128.68
+f32acc64 32 0 0 882.8 127.23
+f32acc64 32 512 0 845.7 126.30
+f32acc64 32 768 0 873.7 126.32
+f32acc64 32 1024 0 890.7 126.35
+f32acc64 48 0 0 885.5 127.23
+f32acc64 48 512 0 848.6 124.07
+f32acc64 48 768 0 871.0 124.10
+f32acc64 48 1024 0 880.1 124.12
+f32acc64 64 0 0 886.1 123.40
+f32acc64 64 512 0 845.0 122.91
+f32acc64 64 768 0 855.8 122.93
+f32acc64 64 1024 0 872.8 122.96
+f32acc64 16 0 1 1461.0 133.55
+f32acc64 16 512 1 921.4 133.18
+f32acc64 16 768 1 993.0 133.21
+f32acc64 16 1024 1 1107.2 133.23
+f32acc64 24 0 1 1469.1 128.96
+f32acc64 24 512 1 899.6 128.73
+f32acc64 24 768 1 952.0 128.75
+f32acc64 24 1024 1 1054.9 128.78
+f32acc64 32 0 1 1327.2 127.32
+f32acc64 32 512 1 900.6 126.40
+f32acc64 32 768 1 950.9 126.42
+f32acc64 32 1024 1 1051.7 126.44
+f32acc64 48 0 1 1325.6 127.32
+f32acc64 48 512 1 891.6 124.17
+f32acc64 48 768 1 932.1 124.19
+f32acc64 48 1024 1 987.8 124.22
+f32acc64 64 0 1 1214.5 123.50
+f32acc64 64 512 1 889.4 123.00
+f32acc64 64 768 1 902.9 123.03
+f32acc64 64 1024 1 1008.0 123.05
+f32acc64 36 0 0 884.0 127.23
+f32acc64 36 0 1 1327.5 127.32
+f64 16 0 0 1338.5 153.94
+f64 16 512 0 1325.2 153.09
+f64 16 768 0 1349.4 153.14
+f64 16 1024 0 1361.8 153.20
+f64 24 0 0 1311.2 148.37
+f64 24 512 0 1300.3 147.83
+f64 24 768 0 1319.1 147.89
+f64 24 1024 0 1314.3 147.94
+f64 32 0 0 1295.7 145.45
+f64 32 512 0 1296.9 145.08
+f64 32 768 0 1306.7 145.13
+f64 32 1024 0 1310.5 145.19
+f64 48 0 0 1284.1 142.66
+f64 48 512 0 1286.3 142.45
+f64 48 768 0 1294.7 142.51
+f64 48 1024 0 1294.7 142.56
+f64 64 0 0 1283.0 142.66
+f64 64 512 0 1283.1 141.07
+f64 64 768 0 1289.1 141.13
+f64 64 1024 0 1282.1 141.18
+f64 16 0 1 1338.7 153.94
+f64 16 512 1 1329.0 153.09
+f64 16 768 1 1351.4 153.14
+f64 16 1024 1 1361.7 153.20
+f64 24 0 1 1312.7 148.37
+f64 24 512 1 1303.1 147.83
+f64 24 768 1 1319.9 147.89
+f64 24 1024 1 1318.1 147.94
+f64 32 0 1 1296.8 145.45
+f64 32 512 1 1299.2 145.08
+f64 32 768 1 1306.9 145.13
+f64 32 1024 1 1308.8 145.19
+f64 48 0 1 1283.2 142.66
+f64 48 512 1 1285.4 142.45
+f64 48 768 1 1294.4 142.51
+f64 48 1024 1 1295.7 142.56
 f64 64 0 1 1284.0 142.66
-f64 64 512 1 1282.3 141.07
-f64 64 768 1 1289.3 141.13
-f64 64 1024 1 1283.0 141.18
-f64 36 0 0 1292.8 144.52
-f64 36 0 1 1292.8 144.52
-f32acc64_characteristic 16 0 0 890.3 257.02
-f32acc64_characteristic 16 512 0 847.5 256.22
-f32acc64_characteristic 16 768 0 884.1 256.27
+f64 64 512 1 1281.7 141.07
+f64 64 768 1 1288.5 141.13
+f64 64 1024 1 1279.0 141.18
+f64 36 0 0 1292.6 144.52
+f64 36 0 1 1292.6 144.52
+f32acc64_characteristic 16 0 0 890.4 257.02
+f32acc64_characteristic 16 512 0 848.2 256.22
+f32acc64_characteristic 16 768 0 884.2 256.27
 f32acc64_characteristic 16 1024 0 896.6 256.33
 f32acc64_characteristic 24 0 0 874.8 250.62
-f32acc64_characteristic 24 512 0 850.8 250.11
-f32acc64_characteristic 24 768 0 872.8 250.16
-f32acc64_characteristic 24 1024 0 878.1 250.22
-f32acc64_characteristic 32 0 0 863.2 247.26
-f32acc64_characteristic 32 512 0 852.6 246.91
-f32acc64_characteristic 32 768 0 865.4 246.96
-f32acc64_characteristic 32 1024 0 870.3 247.02
-f32acc64_characteristic 48 0 0 854.5 244.06
-f32acc64_characteristic 48 512 0 851.5 243.86
+f32acc64_characteristic 24 512 0 850.2 250.11
+f32acc64_characteristic 24 768 0 873.2 250.16
+f32acc64_characteristic 24 1024 0 877.8 250.22
+f32acc64_characteristic 32 0 0 863.5 247.26
+f32acc64_characteristic 32 512 0 852.4 246.91
+f32acc64_characteristic 32 768 0 865.2 246.96
+f32acc64_characteristic 32 1024 0 869.9 247.02
+f32acc64_characteristic 48 0 0 854.3 244.06
+f32acc64_characteristic 48 512 0 851.0 243.86
 f32acc64_characteristic 48 768 0 858.6 243.91
-f32acc64_characteristic 48 1024 0 859.4 243.96
-f32acc64_characteristic 64 0 0 854.5 244.06
-f32acc64_characteristic 64 512 0 845.4 242.26
-f32acc64_characteristic 64 768 0 850.6 242.31
-f32acc64_characteristic 64 1024 0 850.2 242.36
-f32acc64_characteristic 36 0 0 861.3 246.19
-batched_1d 0 0 0 489.6 133.77
-batched_1d 0 512 0 489.9 131.57
-batched_1d 0 1024 0 489.9 131.58
-batched_1d 0 2048 0 490.2 131.59
-batched_2d 16 0 0 22965.4 4201.52
-batched_2d 16 512 0 25731.2 4190.50
-batched_2d 16 768 0 26817.7 4190.53
-batched_2d 16 1024 0 26979.0 4190.55
-batched_2d 24 0 0 22634.1 4073.25
-batched_2d 24 512 0 25239.6 4065.89
-batched_2d 24 768 0 26319.2 4065.91
-batched_2d 24 1024 0 26379.7 4065.93
-batched_2d 32 0 0 22531.8 4009.40
-batched_2d 32 512 0 24636.6 4003.84
-batched_2d 32 768 0 25913.0 4003.87
-batched_2d 32 1024 0 25995.6 4003.89
-batched_2d 48 0 0 22546.1 3945.13
-batched_2d 48 512 0 24153.7 3941.40
-batched_2d 48 768 0 25601.3 3941.43
-batched_2d 48 1024 0 25647.2 3941.45
-batched_2d 64 0 0 22729.2 3913.08
-batched_2d 64 512 0 23876.1 3910.27
-batched_2d 64 768 0 25496.7 3910.29
-batched_2d 64 1024 0 25443.3 3910.31
-batched_2d 16 0 1 32156.0 4201.63
-batched_2d 16 512 1 25187.3 4190.78
-batched_2d 16 768 1 27642.5 4190.80
-batched_2d 16 1024 1 30374.3 4190.83
-batched_2d 24 0 1 32151.2 4073.33
-batched_2d 24 512 1 24747.3 4066.07
-batched_2d 24 768 1 26949.8 4066.09
-batched_2d 24 1024 1 29618.6 4066.12
-batched_2d 32 0 1 32353.0 4009.46
-batched_2d 32 512 1 24374.2 4003.98
-batched_2d 32 768 1 26666.7 4004.01
-batched_2d 32 1024 1 29130.6 4004.03
-batched_2d 48 0 1 32879.3 3945.17
-batched_2d 48 512 1 23936.4 3941.49
-batched_2d 48 768 1 26262.6 3941.52
-batched_2d 48 1024 1 28683.9 3941.54
-batched_2d 64 0 1 33312.0 3913.11
-batched_2d 64 512 1 23830.6 3910.34
-batched_2d 64 768 1 26110.9 3910.36
-batched_2d 64 1024 1 28436.5 3910.38
+f32acc64_characteristic 48 1024 0 858.9 243.96
+f32acc64_characteristic 64 0 0 854.4 244.06
+f32acc64_characteristic 64 512 0 845.7 242.26
+f32acc64_characteristic 64 768 0 850.4 242.31
+f32acc64_characteristic 64 1024 0 849.0 242.36
+f32acc64_characteristic 36 0 0 861.5 246.19
+batched_1d 0 0 0 528.2 128.60
+batched_1d 0 512 0 490.0 126.35
+batched_1d 0 1024 0 490.2 126.36
+batched_1d 0 2048 0 490.7 126.38
+batched_2d 16 0 0 22958.2 4201.52
+batched_2d 16 512 0 25763.7 4190.50
+batched_2d 16 768 0 26884.5 4190.53
+batched_2d 16 1024 0 26927.7 4190.55
+batched_2d 24 0 0 22627.4 4073.25
+batched_2d 24 512 0 25316.4 4065.89
+batched_2d 24 768 0 26316.3 4065.91
+batched_2d 24 1024 0 26380.2 4065.93
+batched_2d 32 0 0 22529.6 4009.40
+batched_2d 32 512 0 24674.5 4003.84
+batched_2d 32 768 0 25977.8 4003.87
+batched_2d 32 1024 0 26013.6 4003.89
+batched_2d 48 0 0 22535.4 3945.13
+batched_2d 48 512 0 24279.1 3941.40
+batched_2d 48 768 0 25662.8 3941.43
+batched_2d 48 1024 0 25634.7 3941.45
+batched_2d 64 0 0 22725.7 3913.08
+batched_2d 64 512 0 24033.0 3910.27
+batched_2d 64 768 0 25424.1 3910.29
+batched_2d 64 1024 0 25464.2 3910.31
+batched_2d 16 0 1 32161.6 4201.63
+batched_2d 16 512 1 25257.5 4190.78
+batched_2d 16 768 1 27680.3 4190.80
+batched_2d 16 1024 1 30334.6 4190.83
+batched_2d 24 0 1 32144.8 4073.33
+batched_2d 24 512 1 24743.8 4066.07
+batched_2d 24 768 1 26997.1 4066.09
+batched_2d 24 1024 1 29625.6 4066.12
+batched_2d 32 0 1 32353.1 4009.46
+batched_2d 32 512 1 24356.5 4003.98
+batched_2d 32 768 1 26639.5 4004.01
+batched_2d 32 1024 1 29139.7 4004.03
+batched_2d 48 0 1 32901.4 3945.17
+batched_2d 48 512 1 23944.5 3941.49
+batched_2d 48 768 1 26293.5 3941.52
+batched_2d 48 1024 1 28706.3 3941.54
+batched_2d 64 0 1 33316.8 3913.11
+batched_2d 64 512 1 23821.9 3910.34
+batched_2d 64 768 1 26101.5 3910.36
+batched_2d 64 1024 1 28435.4 3910.38
 """
 PROFILED = {(p, int(r), int(g), int(v)): (float(t) * 1e6, float(a) * 1e6)
             for p, r, g, v, t, a in (ln.split() for ln in _PROFILED_TABLE.strip().splitlines())}
