@@ -64,7 +64,7 @@ template <int Q> constexpr double WSUM = Q == 2 ? 0.25 : 5.0 / 36.0;
 // (With the blend, face values and edge flux below, 436 instructions a row and
 // wave instead of 511; a stage of 2048^2 cells 249 -> 236 us in F32_ACC64,
 // 449 -> 412 us in F64.)
-constexpr double AN[15] = {2880, 24, 24, 48, 16, 48, 20, 4, 4, 20, 4, 4, 4, 4, 4};
+constexpr double AN[15] = {2880, 2, 2, 2, 16, 2, 20, 4, 4, 20, 4, 4, 4, 4, 4};
 template <class T>
 __device__ __forceinline__ void appendix_a(const T* q, T* n) {
     // q[0..16] hold q_1..q_17
@@ -85,14 +85,15 @@ __device__ __forceinline__ void appendix_a(const T* q, T* n) {
     n[7] = fused((T)-2, dys, ydc);
     n[8] = fused((T)-2, dxs, xdc);
     // 19 dxs - 2 xdc - 6 vWEs + 3 vSNs = 12 dxs - 2 n8 - 3 e, with e the
-    // excess of the derivative averages' slope, and so on
+    // excess of the derivative averages' slope, and so on.  Slopes and curvatures
+    // come by the scale that leaves the difference that is most of them exact.
     const T ex = fused((T)2, vWEs, -vSNs) - dxs, ey = fused((T)2, wSNs, -wWEs) - dys;
-    n[1] = fused((T)-3, ex, fused((T)-2, n[8], (T)12 * dxs));
-    n[2] = fused((T)-3, ey, fused((T)-2, n[7], (T)12 * dys));
+    n[1] = fused((T)-0.25, ex, fused((T)(-1.0 / 6.0), n[8], dxs));
+    n[2] = fused((T)-0.25, ey, fused((T)(-1.0 / 6.0), n[7], dys));
     n[6] = fused((T)2, ex, n[8]);
     n[9] = fused((T)2, ey, n[7]);
-    n[3] = fused((T)-18, n[10], fused((T)24, sx, -n[12]));
-    n[5] = fused((T)-18, n[14], fused((T)24, sy, -n[12]));
+    n[3] = fused((T)-0.75, n[10], fused((T)(-1.0 / 24.0), n[12], sx));
+    n[5] = fused((T)-0.75, n[14], fused((T)(-1.0 / 24.0), n[12], sy));
     n[4] = fused((T)-5, n[11] + n[13], (T)4 * xyc);
     n[0] = fused((T)81, n[10] + n[14], fused((T)5, n[12], (T)-120 * s));
 }
@@ -107,13 +108,15 @@ __device__ __forceinline__ void blend_form(const T* beta, const Scheme& s, T& a0
                 (fabs(beta[0] - beta[3]) + fabs(beta[0] - beta[4]));
     const T tau = (T)0.25 * t, tau2 = tau * tau;
     const T eps = (T)s.eps;
-    T r[5], g[5], gs = 0;
+    T r[5], g[5];
 #pragma unroll
     for (int m = 0; m < 5; ++m) {
         r[m] = rcp(SQ ? fused(beta[m], beta[m], eps) : beta[m] + eps);
         g[m] = (T)s.gam[m];
-        gs += g[m];
     }
+    // the small weights first: added to gamma_0 one by one they leave the sum of
+    // the default ones two roundings below 1, which every polynomial would share
+    const T gs = ((g[1] + g[2]) + (g[3] + g[4])) + g[0];
     T S = g[0] * r[0];
 #pragma unroll
     for (int m = 1; m < 5; ++m) {
@@ -147,9 +150,8 @@ __device__ __forceinline__ void reconstruct2d(const T* q, const Scheme& s, int s
     } else {
         // smoothness indicator: sum over monomials of (m! n! c_mn)^2
         auto sq2 = [](T a, T b) { return fused(a, a, b * b); };
-        T b0 = n[12] * n[12];                                       // 16 c12^2
-        b0 = fused((T)(1.0 / 576.0), sq2(n[1], n[2]), b0);
-        b0 = fused((T)(4.0 / 2304.0), sq2(n[3], n[5]), b0);
+        T b0 = fused(n[3], n[3], fused(n[5], n[5], n[12] * n[12]));   // 4 c3^2, 4 c5^2, 16 c12^2
+        b0 = fused((T)0.25, sq2(n[1], n[2]), b0);
         b0 = fused((T)(1.0 / 256.0), n[4] * n[4], b0);
         b0 = fused((T)0.09, sq2(n[6], n[9]), b0);
         b0 = fused((T)0.25, sq2(n[7], n[8]), b0);
@@ -169,12 +171,12 @@ __device__ __forceinline__ void reconstruct2d(const T* q, const Scheme& s, int s
     }
     // coefficient l of p0 is n[l] / AN[l], in X and Y divided by 2^degree
     const T w64 = a0 * (T)(1.0 / 64.0), w32 = a0 * (T)(1.0 / 32.0), w160 = a0 * (T)(1.0 / 160.0);
-    const T w192 = a0 * (T)(1.0 / 192.0), w48 = a0 * (T)(1.0 / 48.0), kh = (T)0.5 * k;
+    const T w8 = a0 * (T)0.125, w4 = a0 * (T)0.25, kh = (T)0.5 * k;
     C[0] = a0 * (T)(1.0 / 2880.0) * n[0];
-    C[1] = fused(kh, fused(sW, d[0] + d[3], sE * (d[1] + d[2])), w48 * n[1]);
-    C[2] = fused(kh, fused(sS, d[0] + d[1], sN * (d[2] + d[3])), w48 * n[2]);
-    C[3] = w192 * n[3];
-    C[5] = w192 * n[5];
+    C[1] = fused(kh, fused(sW, d[0] + d[3], sE * (d[1] + d[2])), w4 * n[1]);
+    C[2] = fused(kh, fused(sS, d[0] + d[1], sN * (d[2] + d[3])), w4 * n[2]);
+    C[3] = w8 * n[3];
+    C[5] = w8 * n[5];
     C[6] = w160 * n[6];
     C[9] = w160 * n[9];
     C[7] = w32 * n[7];
