@@ -170,19 +170,17 @@ template <class T> struct Flux<T, F_EULER, 3, 0> {
     }
 };
 
-// 2D Euler, U = (rho, rho*mu, rho*nu, E); DIR selects F (x) or G (y).  What an
-// edge point needs of one side is the flux plus al times its argument (al =
-// alpha on the left, -alpha on the right): with s = (normal velocity) + al the
-// transported terms of both become one product, and the second side's terms
-// are accumulated onto the first's (FIRST: out starts with this side).  Per
-// edge point this takes 24 instructions fewer than fluxes and Lax-Friedrichs
-// terms apart.
+// 2D Euler, U = (rho, rho*mu, rho*nu, E); DIR selects F (x) or G (y).  A face's
+// points are accumulated (FIRST: out starts with this one).  Of the averages it
+// is the flux alone; of the derivatives the flux plus al times its argument (al
+// = alpha on the left, -alpha on the right), where with s = (normal velocity) +
+// al the transported terms of both become one product.
 template <class T, int DIR> struct Flux<T, F_EULER, 4, DIR> {
     T gm1;
     __device__ Flux(const Scheme& s) : gm1((T)(s.gas_gamma - 1.0)) {}
-    // velocity, half its square, pressure, total enthalpy, s
+    // velocity, half its square, pressure, E + p, total enthalpy, s
     struct Prim {
-        T u, v, q2h, p, H, s;
+        T u, v, q2h, p, Ep, H, s;
     };
     __device__ __forceinline__ Prim prim(const T* U, T al) const {
         const T rho = U[0], m = U[1], n = U[2], E = U[3];
@@ -190,17 +188,18 @@ template <class T, int DIR> struct Flux<T, F_EULER, 4, DIR> {
         const T u = m * ir, v = n * ir;
         const T q2h = (T)0.5 * fused(u, u, v * v);
         const T p = gm1 * fused(-rho, q2h, E);
-        return {u, v, q2h, p, (E + p) * ir, (DIR == 0 ? u : v) + al};
+        const T Ep = E + p;
+        return {u, v, q2h, p, Ep, Ep * ir, (DIR == 0 ? u : v) + al};
     }
     // F: m, m u + p, n u, u (E + p); G: n, m v, n v + p, v (E + p)
     template <bool FIRST>
-    __device__ __forceinline__ void flux(const T* U, const Prim& w, T al, T* out) const {
+    __device__ __forceinline__ void flux(const T* U, const Prim& w, T* out) const {
         constexpr int N = DIR == 0 ? 1 : 2, A = 3 - N;   // normal and other momentum
         const T vn = DIR == 0 ? w.u : w.v;
-        out[0] = fused(al, U[0], FIRST ? U[N] : out[0] + U[N]);
-        out[N] = fused(w.s, U[N], FIRST ? w.p : out[N] + w.p);
-        out[A] = FIRST ? w.s * U[A] : fused(w.s, U[A], out[A]);
-        out[3] = fused(w.s, U[3], FIRST ? vn * w.p : fused(vn, w.p, out[3]));
+        out[0] = FIRST ? U[N] : out[0] + U[N];
+        out[N] = fused(vn, U[N], FIRST ? w.p : out[N] + w.p);
+        out[A] = FIRST ? vn * U[A] : fused(vn, U[A], out[A]);
+        out[3] = FIRST ? vn * w.Ep : fused(vn, w.Ep, out[3]);
     }
     // (dF/dU) D or (dG/dU) D, with the common factor of three of its rows
     // taken out: for F, a = dm - u dr gives 2u dm - u^2 dr = u (dm + a),

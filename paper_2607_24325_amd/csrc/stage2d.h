@@ -51,6 +51,8 @@ template <> struct Gauss<3> {
 // goes into 1/dx and 1/dy: the sum over an edge's points costs no product
 // (Q = 2) or one.
 template <int Q> constexpr double WSUM = Q == 2 ? 0.25 : 5.0 / 36.0;
+// Half the weights' sum up to that factor.
+template <int Q> constexpr double WHALF = Q == 2 ? 1.0 : 1.8;
 
 // Appendix A coefficients c_{0,1..15} (0..14 here) of the quartic p0 in terms
 // of q_1..q_17, written with the centre average subtracted from the nine
@@ -196,9 +198,11 @@ __device__ __forceinline__ void reconstruct2d(const T* q, const Scheme& s, int s
 // xi and eta; relative value).  Parities in the two variables: E, O even and
 // odd parts in the normal one at the face, by powers of the other; then ee,
 // oe, eo, oo by both.  An odd part's last factor goes into the sum that
-// combines the parts.
+// combines the parts.  half: half the sum of a side's values, with the points'
+// weights up to WSUM.
 template <class T, int Q>
-__device__ __forceinline__ void face_values(const T* C, T (*val)[Q], T (*dn)[Q], T (*dt)[Q]) {
+__device__ __forceinline__ void face_values(const T* C, T (*val)[Q], T (*dn)[Q], T (*dt)[Q],
+                                            T* half) {
     const T E0 = C[0] + (C[3] + C[10]), O0 = C[1] + C[6];
     const T E1 = C[2] + C[7], O1 = C[4] + C[11];
     const T E2 = C[5] + C[12], O2 = C[8];
@@ -231,6 +235,7 @@ __device__ __forceinline__ void face_values(const T* C, T (*val)[Q], T (*dn)[Q],
             dn[s][1] = fused((T)2 * sg, Ob0, Eb0);
             dt[s][1] = E1 + sg * O1;
         }
+        half[s] = Q == 2 ? ue : fused((T)0.8, val[s][1], ue);
     }
 }
 
@@ -240,17 +245,24 @@ template <class T> __device__ __forceinline__ void transpose15(const T* C, T* D)
     D[12] = C[12]; D[13] = C[11]; D[14] = C[10];
 }
 
-// One side of the Lax-Friedrichs flux at a face's Gauss point, TWICE its
-// value: f(U) + al U (al = alpha for a cell's right or top face, -alpha for its
-// left or bottom one) and the same of the derivative fluxes; the 1/2 is folded
-// into the residual's factors.  FIRST starts the sum over the points.  ld(v, D): the face's values of kind v.
+// One side of the Lax-Friedrichs flux at a face's Gauss point, TWICE its value:
+// f(U), and of the derivative fluxes also al times their argument (al = alpha
+// for a cell's right or top face, -alpha for its left or bottom one); the 1/2 is
+// folded into the residual's factors.  FIRST starts the sum over the points.
+// ld(v, D): the face's values of kind v.
+//
+// The dissipation alpha (U_L - U_R) of the averages is left out here and taken
+// from the values relative to the cells' averages and the averages' difference:
+// a side's alpha U, summed over the points before the other side is taken off,
+// would be rounded at the size of alpha U, whose difference across the edge is
+// of fifth order.
 template <bool FIRST, class T, int FLUX, int K, int DIR, class LD>
 __device__ __forceinline__ void lf_side(const Flux<T, FLUX, K, DIR>& F, T al, LD ld, T* out) {
     if constexpr (FLUX == F_EULER && K == 4) {
         T D[K];
         ld(0, D);
         const auto w = F.prim(D, al);
-        F.template flux<FIRST>(D, w, al, out);
+        F.template flux<FIRST>(D, w, out);
 #pragma unroll
         for (int v = 1; v < 3; ++v) {
             ld(v, D);
@@ -264,7 +276,7 @@ __device__ __forceinline__ void lf_side(const Flux<T, FLUX, K, DIR>& F, T al, LD
         F.side(U, V, W, f, fv, fw);
 #pragma unroll
         for (int c = 0; c < K; ++c) {
-            out[c] = fused(al, U[c], FIRST ? f[c] : out[c] + f[c]);
+            out[c] = FIRST ? f[c] : out[c] + f[c];
             out[K + c] = fused(al, V[c], FIRST ? fv[c] : out[K + c] + fv[c]);
             out[2 * K + c] = fused(al, W[c], FIRST ? fw[c] : out[2 * K + c] + fw[c]);
         }
@@ -331,6 +343,13 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, K, Q, V>())) st
     __shared__ double smx[K], smy[K];  // stage 3: per-wave maxima of the wave speeds
     __shared__ long long sbad[K];      // stage 3: per-wave first non-admissible cell
     constexpr bool S3 = mode == MODE_S3;
+    // The RK inputs of the output row are loaded before the reconstruction, or, by
+    // the Euler kernels with wide averages and single-precision faces, before the
+    // faces, which are long enough for them to arrive: through the reconstruction
+    // they would hold four registers that do not fit the 96 of five workgroups a
+    // CU (16 to 32 bytes of scratch; a stage of 2048^2 cells in F32_ACC64 236
+    // instead of 226 us).  In F32, where they fit, late loads cost 2%.
+    constexpr bool LATE_RK = K > 1 && sizeof(T) == 4 && sizeof(TU) == 8;
 
     const int lane = threadIdx.x & 63;
     // component of this wave (uniform: the plane pointers stay in SGPRs)
@@ -432,20 +451,21 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, K, Q, V>())) st
         double mxl = 0.0, myl = 0.0;     // stage 3 of a scalar law: this lane's maxima
         long long badl = LLONG_MAX;
         for (int r = j0 - 1; r <= jend; ++r) {
-            // prefetch the row two above and the RK inputs of the output row
+            // prefetch the row two above
             load_row(r + 2, un_, vn_, wn_);
             TA unr = 0;
             T hvr = 0, hwr = 0;
             const bool emit = r > j0 && out_col;   // row r-1 is an output row
             const uint32_t oo = (uint32_t)((r - 1) * nx + gi);  // output row r-1 (in range if emit)
-            if (mode == MODE_S2 || mode == MODE_S3) {
+            auto load_rk = [&]() {
                 // unconditional (lanes without output read element 0) so that
                 // the loads stay in flight until the epilogue uses them
                 const uint32_t ol = emit ? oo : 0u;
                 unr = (TA)plane_at(Un, ol);
                 hvr = (T)plane_at(Hv, ol);
                 hwr = (T)plane_at(Hw, ol);
-            }
+            };
+            if constexpr ((mode == MODE_S2 || mode == MODE_S3) && !LATE_RK) load_rk();
 
             // ---- R: reconstruct cell (gi, r), component c -------------------
             T q[17];
@@ -518,19 +538,29 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, K, Q, V>())) st
             // Derivatives go to the faces in local units (d/dX, d/dY): the
             // edge flux is linear in them, so the 2/dx, 2/dy of u_x, u_y are
             // applied once to the residual instead of at every face point.
-            T val[2][Q], dn[2][Q], dtg[2][Q];
+            T val[2][Q], dn[2][Q], dtg[2][Q], half[2];
+            // The dissipation of the averages, alpha (U_L - U_R) over the points:
+            // jump_x at the right edge (unused beside the segment); the bottom
+            // edge's goes onto the side of the row below.
+            T jump_x = q[5], half_top;
             if (inner) {
-                face_values<T, Q>(C, val, dn, dtg);   // x-faces: dn = d/dX, dt = d/dY
+                face_values<T, Q>(C, val, dn, dtg, half);   // x-faces: dn = d/dX, dt = d/dY
                 put(0, val, dn, dtg);
                 put(1, val, dn, dtg);
+                jump_x = fused((T)-WHALF<Q>, q[5], half[1] - from_right(half[0]));
             }
             {
                 T D[15];
                 transpose15(C, D);
-                face_values<T, Q>(D, val, dn, dtg);   // y-faces: dn = d/dY, dt = d/dX
+                face_values<T, Q>(D, val, dn, dtg, half);   // y-faces: dn = d/dY, dt = d/dX
                 put(2, val, dtg, dn);
                 put(3, val, dtg, dn);
+                const T jump_y = fused((T)WHALF<Q>, q[1], -half[0]);
+                top_prev[0] = fused(ay, jump_y + jump_y, top_prev[0]);
+                half_top = half[1];
             }
+
+            if constexpr ((mode == MODE_S2 || mode == MODE_S3) && LATE_RK) load_rk();
 
             // ---- F: the faces' sides of the edge fluxes ---------------------
             T side[4][3];   // of this lane's cell, this component
@@ -578,10 +608,11 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, K, Q, V>())) st
                 T xdd[2], gyd[2];
 #pragma unroll
                 for (int sk = 0; sk < 3; ++sk) {
-                    const T fr = side[1][sk] + from_right(side[0][sk]);   // right edge
+                    T fr = side[1][sk] + from_right(side[0][sk]);         // right edge
+                    if (sk == 0) fr = fused(ax, jump_x + jump_x, fr);
                     const T fl = from_left(fr);                           // left edge
                     const T g = top_prev[sk] + side[2][sk];               // edge to row r-1
-                    top_prev[sk] = side[3][sk];
+                    top_prev[sk] = sk == 0 ? fused(ay, half_top + half_top, side[3][sk]) : side[3][sk];
                     if (sk == 0) {
                         xdu = (TA)fr - (TA)fl;
                         gyu = (TA)g;

@@ -278,22 +278,22 @@ __global__ void __launch_bounds__(256, (P == P_F64 ? 1 : 3)) stage2d_char_kernel
                 }
             };
             if (inner) {
-                T q[17], C[15], vh, wh, val[2][Q], dn[2][Q], dtg[2][Q];
+                T q[17], C[15], vh, wh, val[2][Q], dn[2][Q], dtg[2][Q], half[2];
                 stencil(Lx, q);
                 reconstruct2d<T>(q, sch, squared, C, vh, wh);
-                face_values<T, Q>(C, val, dn, dtg);
+                face_values<T, Q>(C, val, dn, dtg, half);
                 put(0, val, dn, dtg);
                 put(1, val, dn, dtg);
                 sH[0][c][lane] = vh;
             }
             {
-                T q[17], C[15], D[15], vh, wh, val[2][Q], dn[2][Q], dtg[2][Q];
+                T q[17], C[15], D[15], vh, wh, val[2][Q], dn[2][Q], dtg[2][Q], half[2];
                 // storage component k is position PY[k] of the y order
                 const T L[K] = {Ly[PY[0]], Ly[PY[1]], Ly[PY[2]], Ly[PY[3]]};
                 stencil(L, q);
                 reconstruct2d<T>(q, sch, squared, C, vh, wh);
                 transpose15(C, D);
-                face_values<T, Q>(D, val, dn, dtg);
+                face_values<T, Q>(D, val, dn, dtg, half);
                 put(2, val, dtg, dn);
                 put(3, val, dtg, dn);
                 sH[1][c][lane] = wh;
@@ -304,6 +304,7 @@ __global__ void __launch_bounds__(256, (P == P_F64 ? 1 : 3)) stage2d_char_kernel
             auto face = [&](auto fi, const auto& F, T al) {
                 constexpr int f = decltype(fi)::value, dir = f / 2;
                 T U[K], out[3 * K];
+                T rel[K];   // the values relative to the cell's average, over the points
 #pragma unroll
                 for (int k = 0; k < K; ++k) U[k] = sU[sd][k][lane];
                 lf_face<Q>(F, al, [&](int mu, int v, T* D) {
@@ -315,8 +316,16 @@ __global__ void __launch_bounds__(256, (P == P_F64 ? 1 : 3)) stage2d_char_kernel
                     for (int k = 0; k < K; ++k) {
                         const int s = dir ? PY[k] : k;
                         D[s] = v == 0 ? U[s] + x[k] : x[k];
+                        if (v == 0) {
+                            if (mu == (Q == 3 ? 1 : 0)) rel[s] = Q == 3 ? (T)1.6 * x[k] : x[k];
+                            else rel[s] += x[k];
+                        }
                     }
                 }, out);
+                // the dissipation of the averages: the faces' part, to which the
+                // edge adds that of the averages' difference
+#pragma unroll
+                for (int k = 0; k < K; ++k) out[k] = fused(al, rel[k], out[k]);
                 if (f == 1 || f == 2) {   // v-hat by a wave of an x face, w-hat of a y face
                     T w[K], x[K];
 #pragma unroll
@@ -342,9 +351,13 @@ __global__ void __launch_bounds__(256, (P == P_F64 ? 1 : 3)) stage2d_char_kernel
             T xdd[2], gyd[2];
 #pragma unroll
             for (int sk = 0; sk < 3; ++sk) {
-                const T fr = sF[1][sk * K + c][lane] + from_right(sF[0][sk * K + c][lane]);
+                T fr = sF[1][sk * K + c][lane] + from_right(sF[0][sk * K + c][lane]);
+                T g = top_prev[sk] + sF[2][sk * K + c][lane];
+                if (sk == 0) {
+                    fr = fused(-ax, (T)(2.0 * WHALF<Q>) * sDx[sd][c][lane], fr);
+                    g = fused(-ay, (T)(2.0 * WHALF<Q>) * sDy[sm][c][lane], g);
+                }
                 const T fl = from_left(fr);
-                const T g = top_prev[sk] + sF[2][sk * K + c][lane];
                 top_prev[sk] = sF[3][sk * K + c][lane];
                 if (sk == 0) {
                     xdu = (TA)fr - (TA)fl;

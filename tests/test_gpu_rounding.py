@@ -3,6 +3,9 @@ rounds as much itself, cannot see it."""
 import numpy as np
 import pytest
 
+import extended
+import oracle as O
+from gpu_util import oproblem
 from paper_2607_24325_amd import hweno as hw
 from paper_2607_24325_amd import workloads as W
 
@@ -34,3 +37,43 @@ def test_hats_of_linear_fields(prec):
             for v in (1, 2):
                 err = np.abs(hats[v, 0, 1:-1, 1:-1] / s[v - 1] - 1.0).max()
                 assert err <= bar, (s, v, err)
+
+
+@pytest.mark.parametrize("prec", [hw.F64, hw.F32_ACC64, hw.F32_KAHAN])
+@pytest.mark.parametrize("q", [2, 3])
+@pytest.mark.parametrize("charwise", [0, 1])
+def test_dissipation_rounds_at_the_size_of_its_jumps(charwise, q, prec):
+    """A density wave in a gas nearly at rest: the speed of sound makes alpha U
+    some fifty times the fluxes of mass and energy, while the dissipation itself
+    is alpha times the values' jumps at the faces, which are of fifth order.  The
+    operator of these two averages then rounds at the size of the fluxes and of
+    alpha times what the values vary over a cell: sixteen roundings of it (four
+    times as many in characteristic variables, where a value is a sum of four
+    products), two faces a direction.  Taken off after being summed at its own
+    size, alpha U costs several times that."""
+    n, u0 = 48, 2.0 ** -6
+    spec = W.Spec(dim=2, flux=W.EULER, nx=n, ny=n, t_end=1.0)
+
+    def init(x, y, i, j):
+        rho = 1.0 + 0.25 * np.sin(2 * np.pi * x + 0.3) * np.cos(2 * np.pi * y)
+        return np.stack([rho, u0 * rho, u0 * rho, 2.5 + u0 * u0 * rho])
+    st = W.project_2d(spec, init)
+    cfg = hw.default_config(2, precision=prec, gauss_q=q, characteristic=charwise)
+    with hw.Handle([spec], cfg) as h:
+        h.set_state(0, st)
+        st = h.get_state(0)[0]   # as stored
+        ax, ay = h.alpha(0)
+        L = h.rhs(0)[0]
+    p = oproblem(spec, cfg)
+    assert (ax, ay) == tuple(O.alpha(p, st))
+    ref = extended.rhs(p, st, ax, ay)[0]
+    unit = 2.0 ** -53 if prec == hw.F64 else 2.0 ** -24
+    for c in (0, 3):
+        flux = u0 * (st[0, 0].max() if c == 0 else (st[0, 3] + 1.0).max())
+        vary = 0.5 * max(np.abs(st[1, c]).max(), np.abs(st[2, c]).max())
+        if charwise:   # fields carry the density's variation into the energy
+            vary = 0.5 * max(np.abs(st[1, 0]).max(), np.abs(st[2, 0]).max())
+        bar = (64 if charwise else 16) * unit * (flux + max(ax, ay) * vary) * (1 / spec.dx + 1 / spec.dy)
+        err = np.abs(L[0, c] - ref[0, c]).max()
+        print(f"component {c}: error {err:.2e}, bar {bar:.2e}")
+        assert err <= bar, (c, err, bar)
