@@ -212,11 +212,13 @@ int hweno_run_to_time(hweno_handle* h, int64_t* steps_out);
 /* Waits for the handle's stream and reports a pending device-side error. */
 int hweno_sync(hweno_handle* h);
 
-/* Launch configuration of the stage kernels.  tile_rows: the most rows one
- * workgroup marches through in 2D (8..1024; with one workgroup per tile a
- * problem too small to fill the GPU is cut into shorter segments, of equal
- * heights to within one row), ignored in 1D (cells per tile are fixed
- * by the kernel); grid_blocks: workgroups of the persistent launch
+/* Launch configuration of the stage kernels.  tile_rows: rows one workgroup
+ * marches through in 2D (8..1024; segments of equal heights to within one row),
+ * ignored in 1D (cells per tile are fixed by the kernel).  With one workgroup
+ * per tile, problems whose tiles of that height would not occupy every workgroup
+ * slot of the GPU are cut into shorter segments; of 32, the height a handle starts
+ * with, the same holds for tiles that occupy every slot less than twice.
+ * grid_blocks: workgroups of the persistent launch
  * (0 = one per tile); use_graph: capture steps as HIP graphs (1) or launch
  * eagerly (0); variant: register allocation of the 2D Euler stage kernels
  * (0: for the occupancy that their registers and LDS allow; 1: in single

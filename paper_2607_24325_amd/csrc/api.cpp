@@ -131,22 +131,22 @@ int tiles_2d(int nx, int ny, int rows) {
 // c(n) = 1 + 0.43 (n - 1) for the four-wave Euler workgroups (a row alone
 // takes 2.4 us in FP64 Q = 3, 1.6 us in F32_ACC64 Q = 2)
 // and 1 + 0.15 (n - 1) for the one-wave scalar ones: between 256^2 and 1600 x
-// 800 its choice is within 4% of the best height.  From two rounds on
+// 800 its choice is within 5% of the best height.  From two rounds on
 // the dispatcher's own balance makes taller segments better (fewer halo rows).
+// So much for the height a handle starts with, of which 2048^2 cells make 2240
+// tiles, less than two rounds of the 1280 slots in single precision: 29 rows.  A
+// height of the caller's own is shortened only where its tiles leave slots empty.
 int split_rows(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg, int cap) {
     constexpr int64_t NCU = 256;
-    const bool euler = probs[0].flux == HWENO_EULER, f64 = cfg.precision == HWENO_F64;
-    // workgroups that fit a CU (registers and LDS of the kernels)
-    const int q3 = cfg.gauss_q == 3 ? 1 : 0;
-    const int slots = !euler ? 12
-                             : cfg.characteristic ? (f64 ? 1 : 3 - q3) : (f64 ? 3 : 5) - q3;
+    const bool euler = probs[0].flux == HWENO_EULER;
+    const int slots = stage2d_slots(cfg.precision, euler, cfg.gauss_q, cfg.characteristic);
     const double g = euler ? 0.43 : 0.15;
     auto tiles = [&](int rows) {
         int64_t n = 0;
         for (int p = 0; p < nprob; ++p) n += tiles_2d(probs[p].nx, probs[p].ny, rows);
         return n;
     };
-    if (tiles(cap) >= 2 * NCU * slots) return cap;
+    if (tiles(cap) >= (cap == DEFAULT_ROWS ? 2 : 1) * NCU * slots) return cap;
     const int64_t most = std::max(tiles(8), SPLIT_TILES);
     auto c = [&](int64_t n) { return n > 0 ? 1.0 + g * (double)(n - 1) : 0.0; };
     auto cost = [&](int rows) {
@@ -512,7 +512,7 @@ static int setup(hweno_handle* h, const hweno_problem* probs, int32_t nprob,
     ctl.slots = slots;
     HIP_TRY(h, hipMemcpy(h->d_ctl, &ctl, sizeof ctl, hipMemcpyHostToDevice));
     h->state_set.assign(nprob, 0);
-    h->tun.tile_rows = 32;
+    h->tun.tile_rows = DEFAULT_ROWS;
     h->tun.grid_blocks = 0;
     h->tun.use_graph = 1;
     h->tun.variant = 0;

@@ -205,6 +205,14 @@ hipError_t launch_dt(ProbDev* probs, StepCtl* ctl, int nprob, int use_dt_in, int
 hipError_t launch_step1d(int prec, int flux, int cells, const Step1Args& a, int grid, hipStream_t s);
 // Steps of nprob problems of at most `waves` waves each.
 hipError_t launch_run1d(int prec, int flux, int waves, int nprob, const Run1Args& a, hipStream_t s);
+// Workgroups of the 2D stage kernels that share a CU, by their registers and LDS.
+// The one-wave workgroups of the scalar laws (8 in FP64 with three Gauss points,
+// up to 20 in single precision) are taken as 12 throughout.
+constexpr int stage2d_slots(int prec, bool euler, int Q, bool charwise) {
+    return !euler ? 12
+                  : charwise ? (prec == P_F64 ? 1 : Q == 3 ? 2 : 3)
+                             : (prec == P_F64 ? 3 : 5) - (Q == 3 ? 1 : 0);
+}
 // Waves that hold the largest of these 1D problems in one workgroup; 0 where
 // it does not fit.
 int run1d_waves(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg);
@@ -238,8 +246,10 @@ int validate_problems(const hweno_problem* probs, int32_t nprob, const hweno_con
 // Sets the thread's last error (hweno_last_error(NULL)); returns code.
 int thread_error(int code, const char* fmt, ...);
 Scheme scheme_of(const hweno_problem& p0, const hweno_config& cfg);
-// Segment height of the 2D tiles of one launch over these problems: at most
-// `cap` rows, fewer where that would leave the GPU idle.
+// Segment height a handle starts with; as tile_rows, the library's to shorten.
+constexpr int DEFAULT_ROWS = 32;
+// Segment height of the 2D tiles of one launch over these problems: `cap` rows,
+// fewer where that would leave the GPU idle.
 int split_rows(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg, int cap);
 // Tiles of one problem at that height, and the first row of segment s.
 int tiles_2d(int nx, int ny, int rows);

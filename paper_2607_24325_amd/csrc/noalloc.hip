@@ -115,14 +115,14 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
     // 1D: the step kernel, or stage by stage with the speeds of every stage
     const int cells1d = dim == 1 && !cfg->alpha_stage ? step1d_cells(prob, 1, *cfg) : 0;
     const int out1d = cells1d ? 64 * cells1d - STEP1D_HALO : TILE1D_OUT;
-    // segments as hweno_step cuts them; 32 rows where only their shorter list fits
-    int rows = dim == 2 ? split_rows(prob, 1, *cfg, 32) : 0, ntiles = 0;
+    // segments as hweno_step cuts them; the uncut ones where only their shorter list fits
+    int rows = dim == 2 ? split_rows(prob, 1, *cfg, DEFAULT_ROWS) : 0, ntiles = 0;
     size_t tb = 0, need = 0;
-    for (;; rows = 32) {
+    for (;; rows = DEFAULT_ROWS) {
         ntiles = dim == 1 ? (pr.nx + TILE1D_OUT - 1) / TILE1D_OUT : tiles_2d(pr.nx, pr.ny, rows);
         tb = up256((size_t)ntiles * (dim == 1 ? sizeof(Tile1D) : sizeof(Tile2D)));
         need = 3 * (ub + db) + db + up256(sizeof(ProbDev)) + 256 + tb + cb;
-        if (need <= HWENO_NOALLOC_SCRATCH_BYTES || dim == 1 || rows == 32) break;
+        if (need <= HWENO_NOALLOC_SCRATCH_BYTES || dim == 1 || rows == DEFAULT_ROWS) break;
     }
     if (need > HWENO_NOALLOC_SCRATCH_BYTES)
         return thread_error(HWENO_ERR_ARG,
