@@ -222,7 +222,8 @@ int hweno_sync(hweno_handle* h);
  * (0 = one per tile); use_graph: capture steps as HIP graphs (1) or launch
  * eagerly (0); variant: register allocation of the 2D Euler stage kernels
  * (0: for the occupancy that their registers and LDS allow; 1: in single
- * precision for one workgroup more per CU, with fewer registers; ignored
+ * precision with two Gauss points, component-wise, for one workgroup more per
+ * CU, with fewer registers; ignored
  * elsewhere); source
  * (read only): where the configuration came from (HWENO_TUNED_*).  Changing
  * any of these never changes a result bit. */
@@ -244,8 +245,8 @@ int hweno_set_tuning(hweno_handle* h, const hweno_tuning* t);
 
 /* Times candidate launch configurations (segment heights 16-64 and those
  * whose tile count just fits two or three rounds of the GPU's workgroup
- * slots, persistent grid sizes, register variants; the caller's use_graph
- * is kept) on a few steps
+ * slots, persistent grid sizes, register variants, as far as their launches
+ * differ; the caller's use_graph is kept) on a few steps
  * of the handle's current state, which it restores: after at least 50 ms of
  * warm-up steps, every candidate on three steps, then the four fastest and
  * the configuration in use on six steps, twice; the configuration in use is
@@ -256,7 +257,6 @@ int hweno_set_tuning(hweno_handle* h, const hweno_tuning* t);
  * cells to the nearest power of two) is applied without timing, and a newly
  * timed winner is appended (one JSON object per line).  Synchronising.
  * best (may be NULL) receives the configuration in use afterwards. */
-int hweno_autotune(hweno_handle* h, hweno_tuning* best);
 int hweno_autotune(hweno_handle* h, hweno_tuning* best);
 
 /* The candidate launch configurations hweno_autotune times for this handle

@@ -1050,49 +1050,63 @@ static void cache_store(const char* path, const std::string& key, const hweno_tu
     std::fclose(f);
 }
 
-// The launch configurations the tuner times.  2D: segment heights (the halo
-// rows recomputed per segment against the number of workgroups), one
-// workgroup per tile or a persistent grid of 2-4 per CU, and for the Euler
-// kernels both register variants.  1D: tiles are fixed by the kernel; one
-// workgroup per tile or a persistent grid.
+// The launch configurations the tuner times, the one a handle starts with first.
+// 2D: segment heights (the halo rows recomputed per segment against the number of
+// workgroups), one workgroup per tile or a persistent grid of 2-4 per CU, and both
+// register variants of the Euler kernels that have two.  1D: tiles are fixed
+// by the kernel; one workgroup per tile or a persistent grid.  A configuration
+// whose launch is one already listed is left out: heights cut to the same segments,
+// grids of no fewer workgroups than there are tiles, everything but one where
+// workgroups hold whole problems.
 static std::vector<hweno_tuning> tuning_candidates(hweno_handle* h) {
     std::vector<hweno_tuning> cands;
+    std::vector<uint64_t> seen;
     int dev = 0, ncu = 256;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-    const int graph = h->tun.use_graph;
+    auto add = [&](int rows, int grid, int variant) {
+        uint64_t key = 0xcbf29ce484222325u;   // FNV-1a over what reaches the launch
+        auto mix = [&](uint64_t v) { key = (key ^ v) * 0x100000001b3u; };
+        int64_t ntiles = h->ntiles_step;
+        if (h->dim == 2) {
+            const int r = grid > 0 ? rows : split_rows(h->probs.data(), h->nprob, h->cfg, rows);
+            ntiles = 0;
+            for (const hweno_problem& p : h->probs) {
+                mix((p.ny + r - 1) / r);
+                ntiles += tiles_2d(p.nx, p.ny, r);
+            }
+        }
+        if (!h->waves1d) mix(grid > 0 && grid < ntiles ? grid : 0);
+        mix(variant);
+        if (std::find(seen.begin(), seen.end(), key) != seen.end()) return;
+        seen.push_back(key);
+        cands.push_back({rows, grid, h->tun.use_graph, variant, 0, 0});
+    };
     if (h->dim == 1) {
-        for (int g : {0, 2 * ncu, 4 * ncu, 8 * ncu}) cands.push_back({64, g, graph, 0, 0, 0});
+        for (int g : {0, 2 * ncu, 4 * ncu, 8 * ncu}) add(DEFAULT_ROWS, g, 0);
         return cands;
     }
-    const int nvar = (h->flux == F_EULER && !h->sch.charwise) ? 2 : 1;
+    const bool euler = h->flux == F_EULER;
+    const int nvar = stage2d_two_variants(h->prec, euler, h->cfg.gauss_q, h->sch.charwise) ? 2 : 1;
     for (int v = 0; v < nvar; ++v)
-        for (int rows : {16, 24, 32, 48, 64})
-            for (int g : {0, 2 * ncu, 3 * ncu, 4 * ncu}) cands.push_back({rows, g, graph, v, 0, 0});
+        for (int rows : {DEFAULT_ROWS, 16, 24, 48, 64})
+            for (int g : {0, 2 * ncu, 3 * ncu, 4 * ncu}) add(rows, g, v);
     // With one workgroup per tile, a tile count just above a whole number of
     // rounds of the GPU's workgroup slots leaves a last round that runs the
     // chip mostly idle.  Also try the lowest segment heights whose tile count
-    // fits 2 or 3 rounds at 3 or 4 resident workgroups per CU (the Euler
-    // kernels' occupancy in double and single precision).
-    auto ntiles = [&](int rows) {
-        long long n = 0;
-        for (const hweno_problem& p : h->probs)
-            n += (long long)((p.nx + STRIP_OUT - 1) / STRIP_OUT) * ((p.ny + rows - 1) / rows);
-        return n;
-    };
-    std::vector<int> fit;
-    for (int per_cu : {3, 4})
-        for (int rounds : {2, 3}) {
-            const long long slots = (long long)rounds * per_cu * ncu;
-            for (int rows = 16; rows <= 64; ++rows)
-                if (ntiles(rows) <= slots) {
-                    if (rows % 8 != 0 && std::find(fit.begin(), fit.end(), rows) == fit.end())
-                        fit.push_back(rows);
-                    break;
-                }
-        }
+    // fits 2 or 3 rounds.
     for (int v = 0; v < nvar; ++v)
-        for (int rows : fit) cands.push_back({rows, 0, graph, v, 0, 0});
+        for (int rounds : {2, 3}) {
+            const int64_t slots = (int64_t)rounds * ncu *
+                                  (stage2d_slots(h->prec, euler, h->cfg.gauss_q, h->sch.charwise) + v);
+            for (int rows = 16; rows <= 64; ++rows) {
+                int64_t n = 0;
+                for (const hweno_problem& p : h->probs) n += tiles_2d(p.nx, p.ny, rows);
+                if (n > slots) continue;
+                add(rows, 0, v);
+                break;
+            }
+        }
     return cands;
 }
 

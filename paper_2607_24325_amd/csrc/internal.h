@@ -179,9 +179,8 @@ struct Run1Args {
 // --- launchers (defined in the .hip files) ------------------------------
 hipError_t launch_stage1d(int prec, int flux, int mode, const StageArgs& a, int grid,
                           hipStream_t s);
-// variant: register variant of the Euler stage kernels (0 or 1; see
-// stage2d_min_blocks), ignored for the scalar laws and the characteristic
-// kernel.
+// variant: register variant of the Euler stage kernels (0 or 1), ignored where
+// there is one (stage2d_two_variants).
 hipError_t launch_stage2d(int prec, int flux, int Q, int mode, int variant, const StageArgs& a,
                           int grid, hipStream_t s);
 // all_problems: zero the speeds of every problem (queries), or only of those
@@ -212,6 +211,11 @@ constexpr int stage2d_slots(int prec, bool euler, int Q, bool charwise) {
     return !euler ? 12
                   : charwise ? (prec == P_F64 ? 1 : Q == 3 ? 2 : 3)
                              : (prec == P_F64 ? 3 : 5) - (Q == 3 ? 1 : 0);
+}
+// Whether the stage kernel has a variant 1, for one workgroup more per CU: where
+// LDS, which holds the faces, would allow it.
+constexpr bool stage2d_two_variants(int prec, bool euler, int Q, bool charwise) {
+    return euler && !charwise && prec != P_F64 && Q == 2;
 }
 // Waves that hold the largest of these 1D problems in one workgroup; 0 where
 // it does not fit.

@@ -314,19 +314,20 @@ __device__ __forceinline__ void publish_gathered(const StageArgs& a, int prob, i
     publish_and_end(&a.probs[prob], prob, slot, a.ctl, a.flags, 1, mx, my, bad);
 }
 
-// Workgroups per CU the register allocation is made for (launch bounds).
-// Variant 0: the occupancy that the registers allow without spilling (the face
-// sums take one side and quantity at a time and stage 3's speed gather is a
-// call of its own after the march: at most 97 registers in single precision,
-// 164 in FP64) and the LDS of the faces; variant 1: one workgroup more per CU,
-// which caps the registers lower (the compiler may spill).  The tuner picks.
-template <int P, int K, int Q, int V> constexpr int stage2d_min_blocks() {
-    if (P == P_F64) return Q == 3 || K == 1 ? 2 : 3;   // LDS allows no more
-    return V + (Q == 3 || K == 1 ? 4 : 5);
+// Waves per SIMD the register allocation must allow (launch bounds); for the
+// four-wave Euler workgroups also workgroups per CU.  Variant 0: what registers
+// and the LDS of the faces allow without spilling (the face sums take one side and
+// quantity at a time and stage 3's speed gather is a call of its own after the
+// march: at most 96 registers in single precision with two Gauss points, 103 with
+// three, 144 and 170 in FP64); variant 1 (stage2d_two_variants): one more, which
+// caps the registers lower (the compiler spills).  The tuner picks.  The one-wave
+// scalar laws use no LDS; in FP64 they take up to 191 registers.
+template <int P, int K, int Q, int V> constexpr int stage2d_min_waves() {
+    return K == 1 ? (P == P_F64 ? 2 : 4) : stage2d_slots(P, true, Q, false) + V;
 }
 
 template <int P, int K, int Q, int FLUX, int mode, int V>
-__global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, K, Q, V>())) stage2d_kernel(StageArgs a) {
+__global__ void __launch_bounds__(64 * K, (stage2d_min_waves<P, K, Q, V>())) stage2d_kernel(StageArgs a) {
     using TU = typename PrecT<P>::TU;
     using TD = typename PrecT<P>::TD;
     using T = typename PrecT<P>::T;
@@ -722,8 +723,8 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_blocks<P, K, Q, V>())) st
     }
 }
 
-// Launches the stage kernel of one precision: Euler in either register
-// variant, the scalar laws in variant 0.
+// Launches the stage kernel of one precision: Euler in either register variant
+// where there are two, the scalar laws in variant 0.
 template <int P, int K, int Q, int FLUX, int V>
 void stage2d_launch_modes(int mode, const StageArgs& a, int grid, hipStream_t s) {
     constexpr int threads = 64 * K;
@@ -735,17 +736,20 @@ void stage2d_launch_modes(int mode, const StageArgs& a, int grid, hipStream_t s)
     }
 }
 
+template <int P, int Q>
+void stage2d_launch_euler(int mode, int variant, const StageArgs& a, int grid, hipStream_t s) {
+    if constexpr (stage2d_two_variants(P, true, Q, false)) {
+        if (variant) return stage2d_launch_modes<P, 4, Q, F_EULER, 1>(mode, a, grid, s);
+    }
+    stage2d_launch_modes<P, 4, Q, F_EULER, 0>(mode, a, grid, s);
+}
+
 template <int P>
 hipError_t stage2d_launch_prec(int flux, int Q, int mode, int variant, const StageArgs& a,
                                int grid, hipStream_t s) {
     if (flux == F_EULER) {
-        if (Q == 2) {
-            if (variant) stage2d_launch_modes<P, 4, 2, F_EULER, 1>(mode, a, grid, s);
-            else stage2d_launch_modes<P, 4, 2, F_EULER, 0>(mode, a, grid, s);
-        } else {
-            if (variant) stage2d_launch_modes<P, 4, 3, F_EULER, 1>(mode, a, grid, s);
-            else stage2d_launch_modes<P, 4, 3, F_EULER, 0>(mode, a, grid, s);
-        }
+        if (Q == 2) stage2d_launch_euler<P, 2>(mode, variant, a, grid, s);
+        else stage2d_launch_euler<P, 3>(mode, variant, a, grid, s);
     } else if (flux == F_BURGERS) {
         if (Q == 2) stage2d_launch_modes<P, 1, 2, F_BURGERS, 0>(mode, a, grid, s);
         else stage2d_launch_modes<P, 1, 3, F_BURGERS, 0>(mode, a, grid, s);
