@@ -197,8 +197,9 @@ int hweno_step(hweno_handle* h, const double* dt_in, double* dt_out);
  * as hweno_step(h, NULL, NULL) would take it (problems at their t_end do not
  * move).  Only enqueues.  In graph mode, runs of 8 steps are replayed as one
  * graph, which spares the launch gaps between graphs; where every problem is
- * 1D with at most 416 cells, all nsteps are one launch.  Errors: ERR_ARG for
- * nsteps < 0, ERR_STATE before set_state. */
+ * 1D with at most 416 cells, a launch takes up to 4096 steps (with more than 256
+ * problems proportionally fewer).  Errors: ERR_ARG for nsteps < 0, ERR_STATE
+ * before set_state. */
 int hweno_steps(hweno_handle* h, int32_t nsteps);
 
 /* Advances every problem to its t_end with SSP-RK3 steps (Sec. 2.1 Step 4,

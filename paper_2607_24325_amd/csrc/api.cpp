@@ -874,10 +874,10 @@ static int capture_multi(hweno_handle* h) {
 static int launch_steps(hweno_handle* h, int64_t n) {
     int64_t done = 0;
     int rc = HWENO_OK;
-    if (h->waves1d) {   // at most this many steps a launch (some 20 ms)
-        constexpr int64_t MOST = 4096;
-        for (; done < n; done += MOST)
-            HIP_TRY(h, launch_run(h, (int)std::min(MOST, n - done), STEP_CHOOSE));
+    if (h->waves1d) {
+        const int64_t most = run1d_steps(h->nprob);
+        for (; done < n; done += most)
+            HIP_TRY(h, launch_run(h, (int)std::min(most, n - done), STEP_CHOOSE));
         if (n > 0) h->speeds_fresh = 1;
         return rc;
     }
@@ -949,14 +949,15 @@ extern "C" int hweno_run_to_time(hweno_handle* h, int64_t* steps_out) {
     HIP_TRY(h, hipMemcpyAsync(&ctl, h->d_ctl, sizeof ctl, hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
     const int64_t steps0 = ctl.steps;
-    int batch = h->waves1d ? 1024 : 4;
+    const int most = h->waves1d ? run1d_steps(h->nprob) : 64;
+    int batch = h->waves1d ? std::min(1024, most) : 4;
     for (;;) {
         rc = launch_steps(h, batch);
         if (rc) return rc;
         HIP_TRY(h, hipMemcpyAsync(&ctl, h->d_ctl, sizeof ctl, hipMemcpyDeviceToHost, h->stream));
         HIP_TRY(h, hipStreamSynchronize(h->stream));
         if (ctl.nactive == 0) break;
-        batch = std::min(batch * 2, h->waves1d ? 4096 : 64);
+        batch = std::min(batch * 2, most);
     }
     if (steps_out) *steps_out = ctl.steps - steps0;
     return hweno_sync(h);

@@ -220,6 +220,8 @@ constexpr bool stage2d_two_variants(int prec, bool euler, int Q, bool charwise) 
 // Waves that hold the largest of these 1D problems in one workgroup; 0 where
 // it does not fit.
 int run1d_waves(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg);
+// Most steps of so many problems that one launch of the run kernel takes.
+int run1d_steps(int nprob);
 // Cells per lane of the 1D step kernel for these problems.
 int step1d_cells(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg);
 // What the host asks of a problem's table entry.
