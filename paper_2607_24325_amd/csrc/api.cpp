@@ -277,7 +277,7 @@ static Layout layout_of(const hweno_problem* probs, int32_t nprob, const hweno_c
     prec_sizes(cfg->precision, &su, &sd);
     size_t nu = 0, nd = 0, maxst = 0, tiles = 0, steps1d = 0, slots = 0;
     int nch = 0;
-    const int cells1d = D == 1 ? step1d_cells(probs, nprob, *cfg) : 0;
+    const int cells1d = D == 1 ? step1d_cells(probs, nprob) : 0;
     for (int p = 0; p < nprob; ++p) {
         const size_t nc = (size_t)probs[p].nx * probs[p].ny;
         nu += (size_t)K * nc;
@@ -518,7 +518,7 @@ static int setup(hweno_handle* h, const hweno_problem* probs, int32_t nprob,
     h->tun.variant = 0;
     h->tun.source = HWENO_TUNED_DEFAULT;
     // speeds of every stage need a reduction between the stages
-    if (h->dim == 1 && !cfg->alpha_stage) h->cells1d = step1d_cells(probs, nprob, *cfg);
+    if (h->dim == 1 && !cfg->alpha_stage) h->cells1d = step1d_cells(probs, nprob);
     if (h->dim == 1) h->waves1d = run1d_waves(probs, nprob, *cfg);
     return build_tiles(h);
 }

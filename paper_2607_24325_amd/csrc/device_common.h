@@ -629,52 +629,41 @@ template <class T> __device__ __forceinline__ T beta_classical_2d(const T* c) {
 
 // ------------------------------------------- characteristic variables ---
 //
-// Eigenvectors of the Euler flux Jacobian at a cell's own average, for the
-// reconstruction in local characteristic variables (remark closing Sec.
-// 2.2).  U = (rho, m_n, [m_t,] E) with m_n the momentum along the direction
-// and m_t across it; columns of R (rows of L = R^-1) belong to the
-// eigenvalues v_n - c, v_n, [v_n (shear),] v_n + c.
-template <class T, int K> struct Eigen {
-    // the entries are closed forms in these scalars; no matrix is stored, so
-    // that rows picked by a run-time index stay in registers
-    T vn, vt, c, H, hq2, b1, b2, ec, hb1;
+// Eigenvectors of the 1D Euler flux Jacobian at a cell's own average, for the
+// reconstruction in local characteristic variables (remark closing Sec. 2.2).
+// U = (rho, m, E); columns of R (rows of L = R^-1) belong to the eigenvalues
+// u - c, u, u + c.
+template <class T> struct Eigen {
+    static constexpr int K = 3;
+    // the entries are closed forms in these scalars; no matrix is stored
+    T u, c, H, hq2, b1, b2, ec, hb1;
     __device__ __forceinline__ Eigen(const T* U, T gm1) {
         const T ir = rcp(U[0]);
-        vn = U[1] * ir;
-        vt = K == 4 ? U[2] * ir : (T)0;
-        hq2 = (T)0.5 * (vn * vn + vt * vt);
-        const T p = gm1 * (U[K - 1] - U[0] * hq2);
+        u = U[1] * ir;
+        hq2 = (T)0.5 * (u * u);
+        const T p = gm1 * (U[2] - U[0] * hq2);
         const T c2 = (gm1 + (T)1) * p * ir;
         c = sqrt(c2);
         const T ic = rcp(c);
-        H = (U[K - 1] + p) * ir;
+        H = (U[2] + p) * ir;
         b1 = gm1 * ic * ic;
         b2 = b1 * hq2;
         ec = (T)0.5 * ic;
         hb1 = (T)0.5 * b1;
     }
-    // L[i][k] (row i: field, column k: component), constant indices
+    // L[i][k] (row i: field, column k: component)
     __device__ __forceinline__ T L(int i, int k) const {
-        if (K == 3) {
-            if (i == 1) return k == 0 ? (T)1 - b2 : (k == 1 ? b1 * vn : -b1);
-            const T s = i == 0 ? (T)1 : (T)-1;   // fields v-c (0) and v+c (2)
-            return k == 0 ? (T)0.5 * b2 + s * vn * ec : (k == 1 ? -(hb1 * vn) - s * ec : hb1);
-        }
-        if (i == 1) return k == 0 ? (T)1 - b2 : (k == 1 ? b1 * vn : (k == 2 ? b1 * vt : -b1));
-        if (i == 2) return k == 0 ? -vt : (k == 2 ? (T)1 : (T)0);
-        const T s = i == 0 ? (T)1 : (T)-1;       // fields v-c (0) and v+c (3)
-        return k == 0 ? (T)0.5 * b2 + s * vn * ec
-                      : (k == 1 ? -(hb1 * vn) - s * ec : (k == 2 ? -hb1 * vt : hb1));
+        if (i == 1) return k == 0 ? (T)1 - b2 : (k == 1 ? b1 * u : -b1);
+        const T s = i == 0 ? (T)1 : (T)-1;   // fields u-c (0) and u+c (2)
+        return k == 0 ? (T)0.5 * b2 + s * u * ec : (k == 1 ? -(hb1 * u) - s * ec : hb1);
     }
-    // R[i][k] (row i: component, column k: field), constant indices
+    // R[i][k] (row i: component, column k: field)
     __device__ __forceinline__ T R(int i, int k) const {
-        const int kc = K == 3 ? (k == 2 ? 3 : k) : k;   // 1D has no shear field
-        if (i == 0) return kc == 2 ? (T)0 : (T)1;
-        if (i == 1) return kc == 0 ? vn - c : (kc == 3 ? vn + c : (kc == 1 ? vn : (T)0));
-        if (K == 4 && i == 2) return kc == 2 ? (T)1 : vt;
-        return kc == 0 ? H - vn * c : (kc == 3 ? H + vn * c : (kc == 1 ? hq2 : vt));
+        if (i == 0) return (T)1;
+        if (i == 1) return k == 0 ? u - c : (k == 2 ? u + c : u);
+        return k == 0 ? H - u * c : (k == 2 ? H + u * c : hq2);
     }
-    // w = L x and x = R w (vectors in the (rho, m_n, [m_t,] E) order)
+    // w = L x and x = R w
     __device__ __forceinline__ void left(const T* x, T* w) const {
 #pragma unroll
         for (int k = 0; k < K; ++k) {

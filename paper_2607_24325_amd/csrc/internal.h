@@ -223,7 +223,7 @@ int run1d_waves(const hweno_problem* probs, int32_t nprob, const hweno_config& c
 // Most steps of so many problems that one launch of the run kernel takes.
 int run1d_steps(int nprob);
 // Cells per lane of the 1D step kernel for these problems.
-int step1d_cells(const hweno_problem* probs, int32_t nprob, const hweno_config& cfg);
+int step1d_cells(const hweno_problem* probs, int32_t nprob);
 // What the host asks of a problem's table entry.
 struct ProbStatus {
     double t, ax, ay;

@@ -113,7 +113,7 @@ extern "C" int hweno_step_noalloc(const hweno_problem* prob, const hweno_config*
     const size_t ub = up256((size_t)ncell * K * su), db = up256((size_t)ncell * K * D * sd);
     const size_t cb = up256((size_t)nchunks * sizeof(Chunk));
     // 1D: the step kernel, or stage by stage with the speeds of every stage
-    const int cells1d = dim == 1 && !cfg->alpha_stage ? step1d_cells(prob, 1, *cfg) : 0;
+    const int cells1d = dim == 1 && !cfg->alpha_stage ? step1d_cells(prob, 1) : 0;
     const int out1d = cells1d ? 64 * cells1d - STEP1D_HALO : TILE1D_OUT;
     // segments as hweno_step cuts them; the uncut ones where only their shorter list fits
     int rows = dim == 2 ? split_rows(prob, 1, *cfg, DEFAULT_ROWS) : 0, ntiles = 0;

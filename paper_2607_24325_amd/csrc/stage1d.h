@@ -84,7 +84,7 @@ __device__ __forceinline__ void recon1d_cell(const T* Uc, const T* dm, const T* 
                                              const T* vp, T dx, const Scheme& sch, int squared,
                                              T g0inv, T* E, T* O, T* De, T* Do) {
     if constexpr (CH) {
-        const Eigen<T, K> ev(Uc, (T)(sch.gas_gamma - 1.0));
+        const Eigen<T> ev(Uc, (T)(sch.gas_gamma - 1.0));
         T dvm[K], dvp[K], wm[K], wp[K], wvm[K], wvp[K], e[K], o[K], de[K], dd[K];
 #pragma unroll
         for (int c = 0; c < K; ++c) {

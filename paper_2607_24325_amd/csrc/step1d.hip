@@ -19,7 +19,7 @@ hipError_t launch_run1d_kahan(int flux, int waves, int nprob, const Run1Args& a,
 // a second (a step of 4000 cells, F64: 10.9 us with one, 14.3 with two); from
 // some 130 000 cells the halo of 12 in 64 costs more than it (100 000 cells:
 // 16.4 against 16.5 us, 200 000: 24.4 against 23.3, 4 million: 300 against 252).
-int step1d_cells(const hweno_problem* probs, int32_t nprob, const hweno_config&) {
+int step1d_cells(const hweno_problem* probs, int32_t nprob) {
     int64_t waves = 0;
     for (int p = 0; p < nprob; ++p) waves += tiles_1d(probs[p].nx, 1);
     return waves <= 2500 ? 1 : 2;
