@@ -42,161 +42,137 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 # kernel sources of this hash; any change of the sources
 # invalidates them, and a configuration not profiled has none (both are
 # reported as null).
-PROFILED_SOURCES = "14bd86723c6c5439"
+PROFILED_SOURCES = "5af97090c2d6653b"
 # path, tile_rows, grid_blocks, variant: HBM MB and VALU wave-instructions (M)
 # per stage, mean of the three stages (in 1D a third of the step kernel's), for every launch configuration
 # the tuner can choose (one eager step each; 2048^2 workload, 4096-problem 1D
 # batch, where segment heights do not apply, 256-problem 2D batch)
 _PROFILED_TABLE = """
-f32acc64 16 0 0 900.8 133.45
-f32acc64 16 512 0 841.6 133.08
-f32acc64 16 768 0 886.4 133.11
-f32acc64 16 1024 0 906.8 133.13
-f32acc64 24 0 0 885.2 128.86
-f32acc64 24 512 0 848.5 128.63
-f32acc64 24 768 0 884.6 128.65
-f32acc64 24 1024 0 898.9 128.68
-f32acc64 32 0 0 882.8 127.23
-f32acc64 32 512 0 845.7 126.30
-f32acc64 32 768 0 873.7 126.32
-f32acc64 32 1024 0 890.7 126.35
-f32acc64 48 0 0 885.5 127.23
-f32acc64 48 512 0 848.6 124.07
-f32acc64 48 768 0 871.0 124.10
-f32acc64 48 1024 0 880.1 124.12
-f32acc64 64 0 0 886.1 123.40
-f32acc64 64 512 0 845.0 122.91
-f32acc64 64 768 0 855.8 122.93
-f32acc64 64 1024 0 872.8 122.96
-f32acc64 16 0 1 1461.0 133.55
-f32acc64 16 512 1 921.4 133.18
-f32acc64 16 768 1 993.0 133.21
-f32acc64 16 1024 1 1107.2 133.23
-f32acc64 24 0 1 1469.1 128.96
-f32acc64 24 512 1 899.6 128.73
-f32acc64 24 768 1 952.0 128.75
-f32acc64 24 1024 1 1054.9 128.78
-f32acc64 32 0 1 1327.2 127.32
-f32acc64 32 512 1 900.6 126.40
-f32acc64 32 768 1 950.9 126.42
-f32acc64 32 1024 1 1051.7 126.44
-f32acc64 48 0 1 1325.6 127.32
-f32acc64 48 512 1 891.6 124.17
-f32acc64 48 768 1 932.1 124.19
-f32acc64 48 1024 1 987.8 124.22
-f32acc64 64 0 1 1214.5 123.50
-f32acc64 64 512 1 889.4 123.00
-f32acc64 64 768 1 902.9 123.03
-f32acc64 64 1024 1 1008.0 123.05
-f32acc64 36 0 0 884.0 127.23
-f32acc64 36 0 1 1327.5 127.32
-f64 16 0 0 1338.5 153.94
-f64 16 512 0 1325.2 153.09
-f64 16 768 0 1349.4 153.14
-f64 16 1024 0 1361.8 153.20
-f64 24 0 0 1311.2 148.37
-f64 24 512 0 1300.3 147.83
-f64 24 768 0 1319.1 147.89
-f64 24 1024 0 1314.3 147.94
-f64 32 0 0 1295.7 145.45
-f64 32 512 0 1296.9 145.08
-f64 32 768 0 1306.7 145.13
-f64 32 1024 0 1310.5 145.19
-f64 48 0 0 1284.1 142.66
-f64 48 512 0 1286.3 142.45
-f64 48 768 0 1294.7 142.51
-f64 48 1024 0 1294.7 142.56
-f64 64 0 0 1283.0 142.66
-f64 64 512 0 1283.1 141.07
-f64 64 768 0 1289.1 141.13
-f64 64 1024 0 1282.1 141.18
-f64 16 0 1 1338.7 153.94
-f64 16 512 1 1329.0 153.09
-f64 16 768 1 1351.4 153.14
-f64 16 1024 1 1361.7 153.20
-f64 24 0 1 1312.7 148.37
-f64 24 512 1 1303.1 147.83
-f64 24 768 1 1319.9 147.89
-f64 24 1024 1 1318.1 147.94
-f64 32 0 1 1296.8 145.45
-f64 32 512 1 1299.2 145.08
-f64 32 768 1 1306.9 145.13
-f64 32 1024 1 1308.8 145.19
-f64 48 0 1 1283.2 142.66
-f64 48 512 1 1285.4 142.45
-f64 48 768 1 1294.4 142.51
-f64 48 1024 1 1295.7 142.56
-f64 64 0 1 1284.0 142.66
-f64 64 512 1 1281.7 141.07
-f64 64 768 1 1288.5 141.13
-f64 64 1024 1 1279.0 141.18
-f64 36 0 0 1292.6 144.52
-f64 36 0 1 1292.6 144.52
-f32acc64_characteristic 16 0 0 890.4 257.02
-f32acc64_characteristic 16 512 0 848.2 256.22
-f32acc64_characteristic 16 768 0 884.2 256.27
-f32acc64_characteristic 16 1024 0 896.6 256.33
-f32acc64_characteristic 24 0 0 874.8 250.62
-f32acc64_characteristic 24 512 0 850.2 250.11
-f32acc64_characteristic 24 768 0 873.2 250.16
-f32acc64_characteristic 24 1024 0 877.8 250.22
-f32acc64_characteristic 32 0 0 863.5 247.26
-f32acc64_characteristic 32 512 0 852.4 246.91
-f32acc64_characteristic 32 768 0 865.2 246.96
-f32acc64_characteristic 32 1024 0 869.9 247.02
-f32acc64_characteristic 48 0 0 854.3 244.06
-f32acc64_characteristic 48 512 0 851.0 243.86
-f32acc64_characteristic 48 768 0 858.6 243.91
-f32acc64_characteristic 48 1024 0 858.9 243.96
-f32acc64_characteristic 64 0 0 854.4 244.06
-f32acc64_characteristic 64 512 0 845.7 242.26
-f32acc64_characteristic 64 768 0 850.4 242.31
-f32acc64_characteristic 64 1024 0 849.0 242.36
-f32acc64_characteristic 36 0 0 861.5 246.19
+f32acc64 32 0 0 872.6 127.56
+f32acc64 32 512 0 864.8 126.63
+f32acc64 32 768 0 871.2 126.66
+f32acc64 32 1024 0 874.6 126.68
+f32acc64 16 0 0 895.6 133.82
+f32acc64 16 512 0 852.4 133.47
+f32acc64 16 768 0 881.0 133.49
+f32acc64 16 1024 0 900.1 133.51
+f32acc64 24 0 0 879.9 129.20
+f32acc64 24 512 0 866.0 128.98
+f32acc64 24 768 0 881.7 129.00
+f32acc64 24 1024 0 888.8 129.03
+f32acc64 48 0 0 862.7 124.48
+f32acc64 48 512 0 875.2 124.39
+f32acc64 48 768 0 868.3 124.41
+f32acc64 48 1024 0 863.8 124.44
+f32acc64 64 0 0 866.6 123.71
+f32acc64 64 512 0 868.2 123.22
+f32acc64 64 768 0 856.1 123.24
+f32acc64 64 1024 0 856.1 123.26
+f32acc64 32 0 1 1303.9 127.65
+f32acc64 32 512 1 886.6 126.73
+f32acc64 32 768 1 960.2 126.75
+f32acc64 32 1024 1 1039.6 126.78
+f32acc64 16 0 1 1454.3 133.91
+f32acc64 16 512 1 917.7 133.56
+f32acc64 16 768 1 1009.5 133.59
+f32acc64 16 1024 1 1093.4 133.61
+f32acc64 24 0 1 1455.8 129.30
+f32acc64 24 512 1 895.2 129.08
+f32acc64 24 768 1 969.7 129.10
+f32acc64 24 1024 1 1039.4 129.12
+f32acc64 48 0 1 1408.7 124.57
+f32acc64 48 512 1 876.4 124.49
+f32acc64 48 768 1 945.5 124.51
+f32acc64 48 1024 1 975.6 124.53
+f32acc64 64 0 1 1197.0 123.81
+f32acc64 64 512 1 867.9 123.31
+f32acc64 64 768 1 911.7 123.34
+f32acc64 64 1024 1 1000.0 123.36
+f32acc64 19 0 0 889.6 131.62
+f64 32 0 0 1292.9 145.61
+f64 32 512 0 1284.1 145.21
+f64 32 768 0 1300.3 145.27
+f64 32 1024 0 1305.2 145.33
+f64 16 0 0 1339.2 154.17
+f64 16 512 0 1327.9 153.26
+f64 16 768 0 1350.8 153.32
+f64 16 1024 0 1363.8 153.38
+f64 24 0 0 1312.6 148.56
+f64 24 512 0 1302.9 147.98
+f64 24 768 0 1322.3 148.04
+f64 24 1024 0 1319.0 148.10
+f64 48 0 0 1285.4 142.80
+f64 48 512 0 1286.5 142.58
+f64 48 768 0 1298.1 142.63
+f64 48 1024 0 1299.8 142.69
+f64 64 0 0 1277.9 141.33
+f64 64 512 0 1281.6 141.19
+f64 64 768 0 1290.5 141.25
+f64 64 1024 0 1283.4 141.31
+f32acc64_characteristic 32 0 0 863.9 247.85
+f32acc64_characteristic 32 512 0 858.0 247.52
+f32acc64_characteristic 32 768 0 865.9 247.57
+f32acc64_characteristic 32 1024 0 869.8 247.62
+f32acc64_characteristic 16 0 0 890.3 257.63
+f32acc64_characteristic 16 512 0 857.7 256.87
+f32acc64_characteristic 16 768 0 883.9 256.91
+f32acc64_characteristic 16 1024 0 896.5 256.96
+f32acc64_characteristic 24 0 0 874.7 251.21
+f32acc64_characteristic 24 512 0 857.0 250.73
+f32acc64_characteristic 24 768 0 872.5 250.78
+f32acc64_characteristic 24 1024 0 877.8 250.83
+f32acc64_characteristic 48 0 0 854.4 244.64
+f32acc64_characteristic 48 512 0 859.0 244.45
+f32acc64_characteristic 48 768 0 858.8 244.50
+f32acc64_characteristic 48 1024 0 858.8 244.55
+f32acc64_characteristic 64 0 0 848.4 242.96
+f32acc64_characteristic 64 512 0 852.0 242.85
+f32acc64_characteristic 64 768 0 851.0 242.90
+f32acc64_characteristic 64 1024 0 850.4 242.94
 batched_1d 0 0 0 528.2 128.60
 batched_1d 0 512 0 490.0 126.35
 batched_1d 0 1024 0 490.2 126.36
 batched_1d 0 2048 0 490.7 126.38
-batched_2d 16 0 0 22958.2 4201.52
-batched_2d 16 512 0 25763.7 4190.50
-batched_2d 16 768 0 26884.5 4190.53
-batched_2d 16 1024 0 26927.7 4190.55
-batched_2d 24 0 0 22627.4 4073.25
-batched_2d 24 512 0 25316.4 4065.89
-batched_2d 24 768 0 26316.3 4065.91
-batched_2d 24 1024 0 26380.2 4065.93
-batched_2d 32 0 0 22529.6 4009.40
-batched_2d 32 512 0 24674.5 4003.84
-batched_2d 32 768 0 25977.8 4003.87
-batched_2d 32 1024 0 26013.6 4003.89
-batched_2d 48 0 0 22535.4 3945.13
-batched_2d 48 512 0 24279.1 3941.40
-batched_2d 48 768 0 25662.8 3941.43
-batched_2d 48 1024 0 25634.7 3941.45
-batched_2d 64 0 0 22725.7 3913.08
-batched_2d 64 512 0 24033.0 3910.27
-batched_2d 64 768 0 25424.1 3910.29
-batched_2d 64 1024 0 25464.2 3910.31
-batched_2d 16 0 1 32161.6 4201.63
-batched_2d 16 512 1 25257.5 4190.78
-batched_2d 16 768 1 27680.3 4190.80
-batched_2d 16 1024 1 30334.6 4190.83
-batched_2d 24 0 1 32144.8 4073.33
-batched_2d 24 512 1 24743.8 4066.07
-batched_2d 24 768 1 26997.1 4066.09
-batched_2d 24 1024 1 29625.6 4066.12
-batched_2d 32 0 1 32353.1 4009.46
-batched_2d 32 512 1 24356.5 4003.98
-batched_2d 32 768 1 26639.5 4004.01
-batched_2d 32 1024 1 29139.7 4004.03
-batched_2d 48 0 1 32901.4 3945.17
-batched_2d 48 512 1 23944.5 3941.49
-batched_2d 48 768 1 26293.5 3941.52
-batched_2d 48 1024 1 28706.3 3941.54
-batched_2d 64 0 1 33316.8 3913.11
-batched_2d 64 512 1 23821.9 3910.34
-batched_2d 64 768 1 26101.5 3910.36
-batched_2d 64 1024 1 28435.4 3910.38
+batched_2d 32 0 0 22432.8 4017.74
+batched_2d 32 512 0 26664.9 4012.59
+batched_2d 32 768 0 26757.2 4012.61
+batched_2d 32 1024 0 26566.9 4012.63
+batched_2d 16 0 0 22918.8 4210.68
+batched_2d 16 512 0 27691.1 4200.45
+batched_2d 16 768 0 27658.7 4200.48
+batched_2d 16 1024 0 27537.7 4200.50
+batched_2d 24 0 0 22543.7 4081.87
+batched_2d 24 512 0 27030.6 4075.03
+batched_2d 24 768 0 27001.1 4075.05
+batched_2d 24 1024 0 26899.6 4075.07
+batched_2d 48 0 0 22409.8 3953.20
+batched_2d 48 512 0 26325.5 3949.74
+batched_2d 48 768 0 26464.3 3949.76
+batched_2d 48 1024 0 26236.1 3949.78
+batched_2d 64 0 0 22556.9 3921.01
+batched_2d 64 512 0 26060.9 3918.40
+batched_2d 64 768 0 26209.6 3918.42
+batched_2d 64 1024 0 25988.2 3918.44
+batched_2d 32 0 1 31284.8 4017.80
+batched_2d 32 512 1 25136.7 4012.72
+batched_2d 32 768 1 27256.4 4012.75
+batched_2d 32 1024 1 28544.6 4012.77
+batched_2d 16 0 1 31322.9 4210.80
+batched_2d 16 512 1 26352.8 4200.73
+batched_2d 16 768 1 28529.7 4200.75
+batched_2d 16 1024 1 30118.9 4200.77
+batched_2d 24 0 1 31157.8 4081.95
+batched_2d 24 512 1 25581.0 4075.21
+batched_2d 24 768 1 27704.5 4075.23
+batched_2d 24 1024 1 29130.9 4075.26
+batched_2d 48 0 1 31742.1 3953.24
+batched_2d 48 512 1 24609.0 3949.83
+batched_2d 48 768 1 26746.7 3949.85
+batched_2d 48 1024 1 27959.3 3949.88
+batched_2d 64 0 1 32213.5 3921.05
+batched_2d 64 512 1 24325.8 3918.47
+batched_2d 64 768 1 26513.2 3918.49
+batched_2d 64 1024 1 27659.8 3918.51
 """
 PROFILED = {(p, int(r), int(g), int(v)): (float(t) * 1e6, float(a) * 1e6)
             for p, r, g, v, t, a in (ln.split() for ln in _PROFILED_TABLE.strip().splitlines())}

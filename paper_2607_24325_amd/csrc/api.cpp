@@ -123,7 +123,7 @@ int tiles_2d(int nx, int ny, int rows) {
 // A workgroup marches its rows one after the other, so a launch with fewer
 // tiles than the GPU has workgroup slots takes as long as one tile however
 // small the problem is (256^2 Euler, FP64, Q = 3: 40 tiles of 32 rows on 256
-// CUs, 93 us a stage, against 27 us as 430 tiles of 3 rows).  Below two
+// CUs, 91 us a stage, against 25 us as 430 tiles of 3 rows).  Below two
 // rounds of slots the height is the one that minimises
 //     (rows + 3) * (full rounds * c(slots per CU) + c(workgroups left per CU)),
 // rows + 3: marched rows of a tile (two of them halo) and its set-up; c(n):

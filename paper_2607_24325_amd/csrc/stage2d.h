@@ -16,19 +16,19 @@
 //      column, and sums over the face's Gauss points its side of the
 //      Lax-Friedrichs flux, all components;
 //   S  each (lane, component) adds the two sides of its edges (the x-neighbour's
-//      by a lane shift, the lower row's top face from the iteration before),
-//      differences the fluxes of the row below, which now has all four edges,
-//      and applies the RK stage to it.
+//      by a lane shift, the lower row's top face from the iteration before) and
+//      the dissipation of its average, differences the fluxes of the row below,
+//      which now has all four edges, and applies the RK stage to it.
 // A face is its own cell's affair, so a wave reads only its own columns, sums
 // the Gauss points in registers (with three of them no wave waits for another)
-// and hands on one sum instead of a flux per point, in 12 to 24 registers less
-// than an edge point's two sides took: five workgroups instead of four fit a CU
-// in single precision (a stage of 2048^2 cells 236 -> 217 us in F32_ACC64, 412
-// -> 402 us in F64; 256^2, Q = 3, F64: 23.1 -> 21.6 us).
+// and hands on one sum instead of a flux per point, in fewer registers than an
+// edge point's two sides took: five workgroups instead of four fit a CU in single
+// precision (a stage of 2048^2 cells by events 235 -> 225 us in F32_ACC64, 252 ->
+// 240 us in F32_KAHAN, 404 us either way in F64; 256^2, Q = 3, F64: 25.6 -> 24.8 us).
 // A scalar law has one wave: its face values and fluxes never leave the lane,
-// and neither LDS nor a barrier is needed (240^2 Burgers, Q = 3, F64: 11.6 ->
-// 7.8 us a stage).
-// Both cells of an edge use the sum of the same two numbers, so the update is
+// and neither LDS nor a barrier is needed (240^2 Burgers, Q = 3, F64: 15.7 ->
+// 11.6 us a stage).
+// Both cells of an edge use the same sum of the same numbers, so the update is
 // conservative to the rounding of the cell-average arithmetic.
 #pragma once
 
@@ -62,10 +62,10 @@ template <int Q> constexpr double WHALF = Q == 2 ? 1.0 : 1.8;
 // so they come as the numerators n[l] = AN[l] c[l], whose scales go into the
 // one product per coefficient that weights p0 below, and the cubic and quartic
 // numerators, which are differences of the lower ones, are formed first and
-// taken back out of those: 51 instructions instead of 74 for the c themselves.
+// taken back out of those: 47 instructions instead of 74 for the c themselves.
 // (With the blend, face values and edge flux below, 436 instructions a row and
-// wave instead of 511; a stage of 2048^2 cells 249 -> 236 us in F32_ACC64,
-// 449 -> 412 us in F64.)
+// wave instead of 511, 416 with the faces split over the waves; a stage of 2048^2
+// cells 247 -> 235 us in F32_ACC64, 435 -> 404 us in F64.)
 constexpr double AN[15] = {2880, 2, 2, 2, 16, 2, 20, 4, 4, 20, 4, 4, 4, 4, 4};
 template <class T>
 __device__ __forceinline__ void appendix_a(const T* q, T* n) {
@@ -348,8 +348,8 @@ __global__ void __launch_bounds__(64 * K, (stage2d_min_waves<P, K, Q, V>())) sta
     // the Euler kernels with wide averages and single-precision faces, before the
     // faces, which are long enough for them to arrive: through the reconstruction
     // they would hold four registers that do not fit the 96 of five workgroups a
-    // CU (16 to 32 bytes of scratch; a stage of 2048^2 cells in F32_ACC64 236
-    // instead of 226 us).  In F32, where they fit, late loads cost 2%.
+    // CU (8 to 32 bytes of scratch and 2 to 3% of a stage of 2048^2 cells in
+    // F32_ACC64).  In F32, where they fit, late loads cost 2%.
     constexpr bool LATE_RK = K > 1 && sizeof(T) == 4 && sizeof(TU) == 8;
 
     const int lane = threadIdx.x & 63;

@@ -31,7 +31,7 @@
 // (no selection by the wave's field), and R is applied in factored form: 25.0
 // million instructions a stage of 768 x 512 cells in F32_ACC64 instead of 35.2,
 // in 155 instead of 220 registers and 43 instead of 55 KB of LDS, so that three
-// workgroups instead of two share a CU: 56 us instead of 73.
+// workgroups instead of two share a CU: 56 us instead of 71.
 #pragma once
 
 #include "stage2d.h"

@@ -14,13 +14,13 @@
 // What bounds it and why this split.  A kernel per stage moves 6 state sets,
 // three saved sets and two average sets through HBM per step (300 bytes a
 // cell in F32_ACC64, 408 in FP64); this one reads and writes the state once
-// (72 and 96 bytes): 4.2 million cells of F32_ACC64 take 160 us a step instead
+// (72 and 96 bytes): 4.2 million cells of F32_ACC64 take 150 us a step instead
 // of 354, and are then bound by vector instructions (all issue slots taken).  On
 // small problems the launches were the time (a step was five of them and is
 // one: 4000 cells in F64, 10 us instead of 24, of which 1.1 are the loads, 3.8
 // the stages and 3.8 the atomics that end the step).  CPT trades halo work (12
 // of 64 or 128 cells) against the length of a lane's serial chain and its
-// registers (142 and 200 in F64, 94 and 128 in F32_ACC64); see step1d_cells.
+// registers (148 and 206 in F64, 96 and 128 in F32_ACC64); see step1d_cells.
 #pragma once
 
 #include "stage1d.h"
@@ -212,8 +212,8 @@ __device__ __forceinline__ void advance1d(TU (&u)[K][CPT], TD (&v)[K][CPT], cons
 
 // Waves per SIMD the register allocation must allow.  Two cells per lane in
 // single precision, component-wise, take 132 registers by themselves; at 128
-// (16 bytes of scratch) a fourth wave fits: 4 million cells of F32_ACC64 158
-// instead of 169 us a step.  Elsewhere the compiler's own choice is as good
+// (16 bytes of scratch) a fourth wave fits: 4 million cells of F32_ACC64 150
+// instead of 168 us a step.  Elsewhere the compiler's own choice is as good
 // or a further wave would spill (FP64, one cell: 20-40% slower).
 template <int P, bool CH, int CPT> constexpr int step1d_min_waves() {
     return CPT == 2 && P != P_F64 && !CH ? 4 : 1;

@@ -15,10 +15,11 @@ hipError_t launch_run1d_acc64(int flux, int waves, int nprob, const Run1Args& a,
 hipError_t launch_run1d_kahan(int flux, int waves, int nprob, const Run1Args& a, hipStream_t s);
 
 // One cell per lane while the waves leave most of the GPU idle: the three
-// stages are one serial chain, 3.5 us for one cell of a lane and 3 us more for
-// a second (a step of 4000 cells, F64: 10.9 us with one, 14.3 with two); from
-// some 130 000 cells the halo of 12 in 64 costs more than it (100 000 cells:
-// 16.4 against 16.5 us, 200 000: 24.4 against 23.3, 4 million: 300 against 252).
+// stages are one serial chain, 3.5 us for one cell of a lane and 2.5 us more for
+// a second (a step of 4000 cells, F64: 10.5 us with one, 13.1 with two);
+// between 130 000 and 200 000 cells the halo of 12 in 64 comes to cost more than
+// that (130 000: 17.0 against 19.7 us, 200 000: 21.2 against 20.8, 4 million: 277
+// against 246).
 int step1d_cells(const hweno_problem* probs, int32_t nprob) {
     int64_t waves = 0;
     for (int p = 0; p < nprob; ++p) waves += tiles_1d(probs[p].nx, 1);
